@@ -128,8 +128,8 @@ SW_API const char* sw_version(void);
 SW_API int sw_ctx_create(int device, void* hip_stream, sw_ctx** out);
 SW_API int sw_ctx_destroy(sw_ctx* ctx);
 
-/* enable != 0 (the default): CG iterations after the first chunk of each
- * solve are replayed from HIP graphs of two iterations (one per case and
+/* enable != 0 (the default): CG iterations after the first ones of each
+ * solve are replayed from HIP graphs of several iterations (one per case and
  * precision, one per batch), captured on first use on a stream of the
  * library's own and launched on the context stream; 0: every kernel is
  * launched directly.  The kernels and their results are the same either
@@ -154,7 +154,8 @@ enum {
 };
 /* enable != 0: bracket every launch of those kernels with HIP events on the
  * context stream (a few microseconds of overhead per launch) and reset the
- * totals; 0: stop.  Synchronises the stream. */
+ * totals; 0: stop.  While it is on, every CG iteration runs as these three
+ * kernels (otherwise the direction may be formed inside the operator pass).  Synchronises the stream. */
 SW_API int sw_ctx_profile(sw_ctx* ctx, int32_t enable);
 /* The same for the kernel classes whose bits (1 << SW_PROF_*) are set in
  * `mask` only (0: stop), and for one launch in `every` (>= 1) of each such

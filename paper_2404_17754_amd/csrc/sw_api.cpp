@@ -6,7 +6,8 @@
 //      + C_abs v  (one EBE pass with two inputs + one face pass)
 //   2. ||b||^2, tolerance, initial guess
 //   3. preconditioned CG on A du = b in chunks of iterations that run with
-//      no host round trip (device-side convergence flag); FP64, or FP32 inner
+//      no host round trip (device-side convergence test), two or three kernels
+//      an iteration (see two_kernel_cg); FP64, or FP32 inner
 //      solves inside FP64 iterative refinement
 //   4. FP64 true residual ||b - A du|| / ||b|| checked against rtol
 //   5. Newmark update of (u, v, a), increment history, receiver record.
@@ -105,8 +106,8 @@ struct sw_ctx {
   hipStream_t stream;
   KernelProfiler prof;
   int grid_cap = 0;  // workgroup cap of the persistent FP32 passes (0: none)
-  // CG iterations after a solve's first chunk replay captured HIP graphs of
-  // two iterations; they are captured on a stream of the library's own
+  // CG iterations replay captured HIP graphs of several iterations; they are
+  // captured on a stream of the library's own
   bool graphs = true;
   hipStream_t cap_stream = nullptr;
 };
@@ -177,12 +178,16 @@ struct sw_case {
   double *diag6, *pinv64, *pmax;
   __half* pinv16;  // block-Jacobi inverse / its largest diagonal entry, FP16 (FP32 CG)
   float *r32, *d32, *z32, *p32, *q32;
+  // second direction buffers of two-kernel iterations (p_old; by parity): FP64
+  // cases have one of their own, the FP32 one lies in p, free in an inner solve
+  double* p_alt = nullptr;
+  float* p32_alt = nullptr;
   uint16_t* p16;  // SW_MIXED_FP16: the inner CG's direction in bfloat16 (else null)
   // flexible outer CG (SW_MIXED_FP32_FLEX): directions and their images of
   // the current and the previous iteration (by parity), dot products
   double *fp[2] = {nullptr, nullptr}, *fq[2] = {nullptr, nullptr}, *fdots = nullptr;
-  // captured pair of CG iterations (FP64, FP32) and the grid cap it was
-  // captured with
+  // captured CG iterations (FP64, FP32) and the grid cap they were captured
+  // with
   hipGraphExec_t cg_graph[2] = {nullptr, nullptr};
   int cg_graph_cap[2] = {-1, -1};
   // workgroup cap of this case's persistent FP32 pass chosen by
@@ -220,6 +225,8 @@ struct sw_case {
   int64_t step = 0;
   int hist_head = 3, hist_count = 0;
   int last_iters = 16;
+  static constexpr int MAX_ROUNDS = 8;
+  int round_iters[MAX_ROUNDS] = {};  // inner iterations of the last step's refinement rounds
   double last_bb = 0.0;
   sw_case_stats stats{};
 };
@@ -503,6 +510,7 @@ size_t mesh_layout(const HostLayout& L, bool det, Carver& cv, MeshDev* md) {
   auto tn = cv.take<int32_t>(std::max<size_t>(L.tile_nodes.size(), 1));
   auto tib = cv.take<int32_t>(nT);
   auto tni = cv.take<int32_t>(nT);
+  auto tob = cv.take<int32_t>(nT);
   auto tfo = cv.take<int32_t>(nT + 1);
   auto xyz = cv.take<double>(3 * L.n_nodes);
   auto geo32 = cv.take<float>(10 * L.tet_stride);
@@ -537,6 +545,7 @@ size_t mesh_layout(const HostLayout& L, bool det, Carver& cv, MeshDev* md) {
     md->tile_nodes = tn;
     md->tile_int_base = tib;
     md->tile_nint = tni;
+    md->tile_own_base = tob;
     md->tile_face_off = tfo;
     md->xyz = xyz;
     md->geo32 = geo32;
@@ -609,6 +618,7 @@ int mesh_create(sw_ctx* ctx, const sw_mesh_desc* d, void* ws, size_t ws_bytes, s
   HIPC(up(md.tile_nodes, L.tile_nodes, s));
   HIPC(up(md.tile_int_base, L.tile_int_base, s));
   HIPC(up(md.tile_nint, L.tile_nint, s));
+  HIPC(up(md.tile_own_base, L.tile_own_base, s));
   HIPC(up(md.tile_face_off, L.tile_face_off, s));
   HIPC(up(md.xyz, L.xyz, s));
   HIPC(up(md.fconn, L.fconn, s));
@@ -678,6 +688,7 @@ static size_t case_layout(const sw_mesh* m, const sw_case_desc* d, Carver& cv, s
   float* f32[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   if (mixed)
     for (int i = 0; i < 5; ++i) f32[i] = cv.take<float>(nd);
+  double* p_alt = mixed || d->deterministic ? nullptr : cv.take<double>(nd);
   uint16_t* p16 = d->precision == SW_MIXED_FP16 ? cv.take<uint16_t>(nd) : nullptr;
   double* fvec[4] = {nullptr, nullptr, nullptr, nullptr};
   double* fdots = nullptr;
@@ -737,6 +748,8 @@ static size_t case_layout(const sw_mesh* m, const sw_case_desc* d, Carver& cv, s
     c->z32 = f32[2];
     c->p32 = f32[3];
     c->q32 = f32[4];
+    c->p_alt = p_alt;
+    c->p32_alt = mixed ? reinterpret_cast<float*>(vec[7]) : nullptr;
     c->p16 = p16;
     c->fp[0] = fvec[0];
     c->fp[1] = fvec[1];
@@ -834,15 +847,19 @@ void op_scales(const sw_case* c, int op, double* sM, double* sK, double* sC) {
 
 // y = op x (internal order).  y's shared-node entries must be zero on entry
 // (interior entries are overwritten).
-int apply_f64(sw_case* c, int op, const double* x, double* y, CgCtl* ctl, int iter, hipStream_t s) {
+TileArgs<double> args_f64(const sw_case* c, int op, const double* x, double* y) {
   TileArgs<double> A{};
   op_scales(c, op, &A.sM, &A.sK, &A.sC);
   A.x1 = x;
   A.a1 = 1.0;
-  A.xf = x;
   A.y = y;
+  A.n_mat = c->n_mat;
   A.eout = c->det_e;
   A.fout = c->det_f;
+  return A;
+}
+int apply_f64(sw_case* c, int op, const double* x, double* y, CgCtl* ctl, int iter, hipStream_t s) {
+  const TileArgs<double> A = args_f64(c, op, x, y);
   launch_tile_f64(c->mesh->dev, c->emat, c->mats, A, ctl, iter, s);
   LAUNCHED();
   return SW_OK;
@@ -851,7 +868,7 @@ int apply_f64(sw_case* c, int op, const double* x, double* y, CgCtl* ctl, int it
   return apply_f64(c, op, x, y, ctl, iter, c->ctx->stream);
 }
 
-int apply_f32(sw_case* c, int op, const float* x, float* y, CgCtl* ctl, int iter, hipStream_t s) {
+TileArgs<float> args_f32(const sw_case* c, int op, const float* x, float* y) {
   TileArgs<float> A{};
   double sM, sK, sC;
   op_scales(c, op, &sM, &sK, &sC);
@@ -860,9 +877,12 @@ int apply_f32(sw_case* c, int op, const float* x, float* y, CgCtl* ctl, int iter
   A.sC = (float)sC;
   A.x1 = x;
   A.a1 = 1.0f;
-  A.xf = x;
   A.y = y;
   A.n_mat = c->n_mat;
+  return A;
+}
+int apply_f32(sw_case* c, int op, const float* x, float* y, CgCtl* ctl, int iter, hipStream_t s) {
+  const TileArgs<float> A = args_f32(c, op, x, y);
   launch_tile_f32(c->mesh->dev, c->emat, c->mats, A, ctl, iter, case_grid_cap(c), s);
   LAUNCHED();
   return SW_OK;
@@ -987,6 +1007,7 @@ extern "C" int sw_case_create(sw_ctx* ctx, sw_mesh* m, const sw_case_desc* d, vo
   HIPX(hipMemcpyAsync(c->rec, rec.data(), 4 * rec.size(), hipMemcpyHostToDevice, s));
   HIPX(hipMemcpyAsync(c->vin, d->v_in, 8 * 3 * (size_t)(d->n_steps + 1), hipMemcpyHostToDevice, s));
   double* zero_vecs[] = {c->u, c->v, c->a, c->b, c->x, c->r, c->z, c->p, c->q};
+  if (c->p_alt) launch_fill_f64(nd, c->p_alt, 0.0, s);
   for (double* zv : zero_vecs) launch_fill_f64(nd, zv, 0.0, s);
   launch_fill_f64(4 * nd, c->hist, 0.0, s);
   if (c->precision != SW_FP64) {
@@ -1107,9 +1128,15 @@ int read_ctl(sw_case* c, CgCtl* dev, CgCtl* host) {
   return c->ctx->prof.on ? prof_flush(c->ctx) : SW_OK;
 }
 
-// Runs CG iterations of the solve in `ctl` until its done flag is set.  The
-// first chunk is sized from the previous solve's count; later ones are short
-// so that few launches are spent after convergence.
+// Whether the case's iterations run as two kernels now.  Three kernels serve
+// the deterministic and the 16-bit modes, and the profiler, which times the
+// operator, the update and the direction each for itself.
+template <bool F32>
+bool two_kernel(const sw_case* c) {
+  return !c->ctx->prof.on && !c->det && !(F32 && c->p16) &&
+         two_kernel_cg(c->mesh->dev, c->n_mat, F32 ? case_grid_cap(c) : 0, F32);
+}
+
 // One CG iteration of the single-case solve on stream s: the operator pass
 // (iteration `iter` of the solve: parity and the first-iteration test), the
 // update and the direction kernels (iter_abs: the iteration's index in the
@@ -1119,6 +1146,23 @@ int cg_iteration(sw_case* c, CgCtl* ctl, int iter, int iter_abs, hipStream_t s, 
   const int64_t nn = c->mesh->n_nodes;
   sw_ctx* cx = c->ctx;
   int rc;
+  if (two_kernel<F32>(c)) {
+    const MeshDev& m = c->mesh->dev;
+    const int par = iter & 1;
+    if (F32) {
+      TileArgs<float> A = args_f32(c, SW_OP_A, c->z32, c->q32);
+      float* p[2] = {c->p32, c->p32_alt};
+      launch_tile_dir_f32(m, c->emat, c->mats, A, p[par ^ 1], p[par], ctl, iter, c->max_iter, s);
+      launch_cg_step_f32(nn, m.n_interior, par, c->pinv16, c->r32, c->z32, c->q32, p[par], c->d32, ctl, s);
+    } else {
+      TileArgs<double> A = args_f64(c, SW_OP_A, c->z, c->q);
+      double* p[2] = {c->p, c->p_alt};
+      launch_tile_dir_f64(m, c->emat, c->mats, A, p[par ^ 1], p[par], ctl, iter, c->max_iter, s);
+      launch_cg_step_f64(nn, m.n_interior, par, c->pinv64, c->r, c->z, c->q, p[par], c->x, ctl, s);
+    }
+    LAUNCHED();
+    return SW_OK;
+  }
   if (F32) {
     int ev = prof ? prof_begin(cx, SW_PROF_TILE_F32) : -1;
     rc = c->p16 ? apply_f32_h(c, c->p16, c->q32, ctl, iter, s) : apply_f32(c, SW_OP_A, c->p32, c->q32, ctl, iter, s);
@@ -1156,15 +1200,20 @@ int capture_stream(sw_ctx* cx, hipStream_t* out) {
   return SW_OK;
 }
 
-// Instantiated graph of two CG iterations of this case's solve (an even
-// iteration then an odd one, past the first: the direction kernels take
-// the iteration index from the control block), captured once per case and
-// precision (again when the grid cap changes).  The captured kernels read
-// and write only the case's vectors and control block, so every replay
-// continues the solve in the control block.  *out stays null if capture is
-// not available (the caller then launches the kernels directly).
+// Iterations of a captured graph: even (the kernels' arguments repeat with the
+// iteration's parity).  The host needs 4-5 us to launch a kernel directly and
+// about as much for a whole graph, while an iteration of a small mesh takes
+// 14 us on the GPU and a skipped one 4 us.
+constexpr int GRAPH_ITERS = 8;
+
+// Instantiated graph of GRAPH_ITERS CG iterations of this case's solve (from
+// an even iteration past the first: the direction kernels take the iteration
+// index from the control block), captured once per case and precision (again
+// when the grid cap changes).  The captured kernels read and write only the
+// case's vectors and control block, so every replay continues the solve in
+// the control block.
 template <bool F32>
-int cg_pair_graph(sw_case* c, CgCtl* ctl, hipGraphExec_t* out) {
+int cg_graph(sw_case* c, CgCtl* ctl, hipGraphExec_t* out) {
   const int slot = F32 ? 1 : 0;
   if (c->cg_graph[slot] && c->cg_graph_cap[slot] == case_grid_cap(c)) {
     *out = c->cg_graph[slot];
@@ -1178,7 +1227,7 @@ int cg_pair_graph(sw_case* c, CgCtl* ctl, hipGraphExec_t* out) {
   int rc = capture_stream(c->ctx, &cs);
   if (rc) return rc;
   HIPC(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-  for (int k = 0; k < 2 && !rc; ++k) rc = cg_iteration<F32>(c, ctl, 2 + k, -1, cs, false);
+  for (int k = 0; k < GRAPH_ITERS && !rc; ++k) rc = cg_iteration<F32>(c, ctl, 2 + k, -1, cs, false);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(cs, &g);
   if (rc) return rc;
@@ -1193,36 +1242,46 @@ int cg_pair_graph(sw_case* c, CgCtl* ctl, hipGraphExec_t* out) {
   return SW_OK;
 }
 
+// Runs CG iterations of the solve in `ctl` until it is done: a first chunk of
+// the expected count (rounded up to an even one), then two at a time, the
+// host reading the control block after each chunk.  Iterations past the end
+// of the solve return at once.
 template <bool F32>
-int cg_loop(sw_case* c, CgCtl* ctl, int iter_base, int first_chunk, int* iters_out) {
-  const int64_t nn = c->mesh->n_nodes;
+int cg_loop(sw_case* c, CgCtl* ctl, int iter_base, int expected, int* iters_out) {
   hipStream_t s = c->ctx->stream;
   sw_ctx* cx = c->ctx;
   int it = 0;
-  // the first chunk has an even count, so that the chunks of two that follow
-  // start at even iterations (the parity a captured pair assumes)
-  int chunk = std::max(2, first_chunk + (first_chunk & 1));
+  int end = std::max(2, expected + (expected & 1));
   CgCtl h;
+  const bool two = two_kernel<F32>(c);
   for (;;) {
-    hipGraphExec_t g = nullptr;
-    if (it > 0 && chunk == 2 && cx->graphs && !cx->prof.on) {
-      int rc = cg_pair_graph<F32>(c, ctl, &g);
-      if (rc) return rc;
-    }
-    if (g) {
-      HIPC(hipGraphLaunch(g, s));
-    } else {
-      for (int k = 0; k < chunk; ++k) {
-        int rc = cg_iteration<F32>(c, ctl, it + k, iter_base + it + k, s, true);
+    while (it < end) {
+      hipGraphExec_t g = nullptr;
+      if (it > 0 && end - it >= GRAPH_ITERS && cx->graphs && !cx->prof.on) {
+        int rc = cg_graph<F32>(c, ctl, &g);
+        if (rc) return rc;
+      }
+      if (g) {
+        HIPC(hipGraphLaunch(g, s));
+        it += GRAPH_ITERS;
+        continue;
+      }
+      for (int k = 0; k < 2; ++k, ++it) {
+        int rc = cg_iteration<F32>(c, ctl, it, iter_base + it, s, true);
         if (rc) return rc;
       }
     }
     LAUNCHED();
-    it += chunk;
     int rc = read_ctl(c, ctl, &h);
     if (rc) return rc;
     if (h.done) break;
-    chunk = 2;
+    if (two) {
+      // the next operator pass would find the same and set the flag
+      double rr = 0.0;
+      for (int k = 0; k < NSLOT; ++k) rr += h.rr[it & 1][k];
+      if (!(rr > h.tol2) || h.iters >= c->max_iter) break;
+    }
+    end = it + 2;
   }
   *iters_out = h.iters - iter_base > 0 ? h.iters - iter_base : 0;
   return SW_OK;
@@ -1433,7 +1492,7 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
   if (rc) return rc;
   launch_fill_f64(1, &c->ctl64->bb, 0.0, s);
   launch_norm2(nd, c->b, &c->ctl64->bb, s, c->det);
-  launch_ctl_prepare(c->ctl64, c->rtol, s);
+  launch_ctl_prepare(c->ctl64, c->rtol, 0, s);
   // guess: the projection needs two past increments, the network four and
   // their neighbour means, extrapolation one; otherwise zero
   int g = guess_kind(c);
@@ -1460,13 +1519,13 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
       if (rr0 <= h.bb) break;
       *flags |= SW_FLAG_GUESS_FALLBACK;
       g = GUESS_EXTRAP;
-      launch_ctl_prepare(c->ctl64, c->rtol, s);
+      launch_ctl_prepare(c->ctl64, c->rtol, 0, s);
       rc = set_guess(c, g);
       if (rc) return rc;
     }
     for (;;) {
       int it = 0;
-      rc = cg_loop<false>(c, c->ctl64, *iters, c->last_iters - *iters - 1, &it);
+      rc = cg_loop<false>(c, c->ctl64, *iters, c->last_iters - *iters, &it);
       if (rc) return rc;
       *iters += it;
       rc = true_residual(c, &h, false);
@@ -1488,7 +1547,7 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
         break;
       }
       // restart CG from the current iterate on the true residual b - A x
-      launch_ctl_prepare(c->ctl64, c->rtol, s);
+      launch_ctl_prepare(c->ctl64, c->rtol, *iters, s);
       launch_cg_init_f64(nn, c->b, c->q, c->pinv64, c->r, c->z, c->p, c->q, c->ctl64, s, c->det);
       LAUNCHED();
     }
@@ -1503,7 +1562,9 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
     // disagrees.
     const bool flex = c->precision == SW_MIXED_FP32_FLEX;
     const int64_t ni3 = 3 * c->mesh->dev.n_interior;
-    int inner_est = std::max(1, c->last_iters / 2);
+    // expected iterations of an inner solve: those of the same round of the
+    // last step, else of the round before
+    int round = 0, inner_est = std::max(1, c->last_iters / 2);
     bool first = true;
     // a projected guess comes with its residual from the stored images
     bool image_res = projected(g);
@@ -1550,14 +1611,16 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
       const double tol = std::min(0.5, std::max(c->inner_rtol, 0.9 * need));
       launch_fill_f64(sizeof(CgCtl) / 8, (double*)c->ctl32, 0.0, s);
       launch_fill_f64(1, &c->ctl32->bb, 1.0, s);
-      launch_ctl_prepare(c->ctl32, tol, s);
+      launch_ctl_prepare(c->ctl32, tol, *iters, s);
       launch_ir_begin(nn, c->r, c->pinv16, c->r32, c->z32, c->p32, c->p16, c->d32, c->ctl64, c->ctl32, s);
       LAUNCHED();
       int it = 0;
-      rc = cg_loop<true>(c, c->ctl32, *iters, inner_est - 1, &it);
+      if (round < sw_case::MAX_ROUNDS && c->round_iters[round] > 0) inner_est = c->round_iters[round];
+      rc = cg_loop<true>(c, c->ctl32, *iters, inner_est, &it);
       if (rc) return rc;
       *iters += it;
       inner_est = std::max(1, it);
+      if (round < sw_case::MAX_ROUNDS) c->round_iters[round++] = inner_est;
       if (!flex) {
         launch_ir_update(nd, c->x, c->d32, c->ctl64, s);
         LAUNCHED();
@@ -2627,7 +2690,6 @@ extern "C" int sw_batch_create(sw_ctx* ctx, sw_case* const* cases, int32_t n, vo
     t.A.sC = c->cC;
     t.A.x1 = c->x;
     t.A.a1 = 1.0;
-    t.A.xf = c->x;
     t.A.y = c->q;
     TileLane<float>& f = cg32[l];
     f = tile_lane<float>(c);
@@ -2636,7 +2698,6 @@ extern "C" int sw_batch_create(sw_ctx* ctx, sw_case* const* cases, int32_t n, vo
     f.A.sC = (float)c->cC;
     f.A.x1 = c->p32;
     f.A.a1 = 1.0f;
-    f.A.xf = c->p32;
     f.A.y = c->q32;
     f.ctl = c->ctl32;
   }

@@ -9,10 +9,37 @@ namespace sw {
 
 constexpr int TPB = 256;
 
+// One step of a butterfly over a row of 16 lanes, in the vector registers
+// (CTRL: a DPP lane selection that permutes the row).
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  union {
+    double d;
+    int i[2];
+  } u{v}, w;
+  w.i[0] = __builtin_amdgcn_mov_dpp(u.i[0], CTRL, 0xf, 0xf, true);
+  w.i[1] = __builtin_amdgcn_mov_dpp(u.i[1], CTRL, 0xf, 0xf, true);
+  return v + w.d;
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  union {
+    double d;
+    int i[2];
+  } u{v};
+  u.i[0] = __builtin_amdgcn_readlane(u.i[0], lane);
+  u.i[1] = __builtin_amdgcn_readlane(u.i[1], lane);
+  return u.d;
+}
+
+// Sum over the wavefront, in every lane.  In the vector registers: six
+// shuffles through the LDS crossbar cost 0.7 us for a pair of sums, at the
+// end of every kernel with a dot product.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  v = dpp_add<0xB1>(v);   // lane ^ 1
+  v = dpp_add<0x4E>(v);   // lane ^ 2
+  v = dpp_add<0x141>(v);  // the other four of eight
+  v = dpp_add<0x140>(v);  // the other eight of sixteen
+  return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
 // Sum of v over a TPB-thread workgroup, valid on thread 0.
@@ -45,23 +72,25 @@ __device__ __forceinline__ double block_sum_n(double v, double* sh) {
   return t;
 }
 
-// Two sums at once (sh holds 2 * TPB / 64 doubles), valid on thread 0.
+// Two sums at once over an NT-thread workgroup (sh holds 2 * NT / 64
+// doubles), valid on thread 0.
+template <int NT = TPB>
 __device__ __forceinline__ void block_sum2(double& a, double& b, double* sh) {
   a = wave_sum(a);
   b = wave_sum(b);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   if (lane == 0) {
     sh[wid] = a;
-    sh[TPB / 64 + wid] = b;
+    sh[NT / 64 + wid] = b;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     a = 0.0;
     b = 0.0;
 #pragma unroll
-    for (int i = 0; i < TPB / 64; ++i) {
+    for (int i = 0; i < NT / 64; ++i) {
       a += sh[i];
-      b += sh[TPB / 64 + i];
+      b += sh[NT / 64 + i];
     }
   }
 }
@@ -79,6 +108,21 @@ __device__ __forceinline__ double slot_sum(const double* s) {
 #pragma unroll
   for (int i = 0; i < N; ++i) t += s[i];
   return t;
+}
+
+// Totals of two sets of NSLOT = 32 partial sums, one load per lane of the
+// wavefront.  Added up one after the other by every work-item (slot_sum),
+// two sets cost 3.3 us at the start of a kernel (the scalar registers hold
+// less than one set, so the loads wait for the additions).
+__device__ __forceinline__ void slot_sum2(const double* a, const double* b, double& ta, double& tb) {
+  const int lane = threadIdx.x & 63;
+  double v = lane < 32 ? a[lane] : b[lane - 32];
+  v = dpp_add<0xB1>(v);   // lane ^ 1
+  v = dpp_add<0x4E>(v);   // lane ^ 2
+  v = dpp_add<0x141>(v);  // the other four of eight
+  v = dpp_add<0x140>(v);  // the other eight of sixteen
+  ta = read_lane(v, 0) + read_lane(v, 16);
+  tb = read_lane(v, 32) + read_lane(v, 48);
 }
 
 }  // namespace sw

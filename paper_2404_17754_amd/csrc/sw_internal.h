@@ -21,7 +21,7 @@ struct MatDev {
 // address; readers add the slots up.
 constexpr int NSLOT = 32;
 struct CgCtl {
-  double pAp[NSLOT];     // p . A p (element energies)
+  double pAp[2][NSLOT];  // p . A p (ring by iteration parity in two-kernel iterations, else [0])
   double rz[2][NSLOT];   // r . z, ring indexed by iteration parity
   double rr[2][NSLOT];   // r . r, same ring
   double bb;       // ||b||^2 of the right-hand side
@@ -29,6 +29,7 @@ struct CgCtl {
   double rr_true;  // ||b - A x||^2 recomputed in FP64
   double scale;    // mixed precision: residual scaling of the inner system
   double alpha;    // step length of the last update kernel's iteration
+  double rz_prev;  // r . z before the last step kernel (two-kernel iterations)
   int32_t done;    // 1 once converged or capped
   int32_t iters;   // iterations of the current solve
   int32_t live;    // 1 when the last update kernel ran its iteration (the
@@ -51,6 +52,7 @@ struct MeshDev {
   const int32_t* tile_nodes;
   const int32_t* tile_int_base;
   const int32_t* tile_nint;
+  const int32_t* tile_own_base;  // shared nodes from this id on are first touched by the tile (or a later one)
   const int32_t* tile_face_off;  // [n_tiles + 1]
   const double* xyz;             // [n_nodes][3]
   const float* geo32;            // [10][tet_stride]: FP32 grad L1..L3 (9) and volume
@@ -84,7 +86,7 @@ struct TileArgs {
   const uint16_t* x1h;
   const T* x2;
   T a1, a2;
-  const T* xf;
+  const T* xf;         // nullptr: the pass's input xe
   const double* vin;   // 3 values or nullptr
   T* y;
   int accumulate;      // interior nodes: 0 overwrite, 1 add
@@ -190,6 +192,18 @@ void launch_tile_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, 
 // of 8); 0 keeps three per compute unit.
 void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
                      CgCtl* ctl, int iter, int grid_cap, hipStream_t s);
+// Two-kernel CG iterations: whether a solve's iterations run so, the operator
+// pass (a.x1 = z; forms and stores p = z + beta p_old, a.y = A p) and the
+// vector kernel after it (x += alpha p, r -= alpha q, z = P r).
+bool two_kernel_cg(const MeshDev& m, int n_mat, int grid_cap, bool f32);
+void launch_tile_dir_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
+                         const double* p_old, double* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s);
+void launch_tile_dir_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
+                         const float* p_old, float* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s);
+void launch_cg_step_f64(int64_t n_nodes, int64_t n_interior, int par, const double* pinv, double* r, double* z,
+                        double* q, const double* p, double* x, CgCtl* ctl, hipStream_t s);
+void launch_cg_step_f32(int64_t n_nodes, int64_t n_interior, int par, const __half* pinv, float* r, float* z,
+                        float* q, const float* p, float* x, CgCtl* ctl, hipStream_t s);
 // FP32 element geometry for the FP32 operator (once per mesh).
 void launch_geom(const MeshDev& m, float* geo32, double* geo64, hipStream_t s);
 // Diagonal 3x3 blocks (6 values per node) of cM M + cK K + cC C_abs.
@@ -227,8 +241,9 @@ void launch_cg_dir_f32(int64_t n_nodes, int par, int iter_abs, int max_iter, con
 void launch_cg_dir_h(int64_t n_nodes, int par, int iter_abs, int max_iter, const float* z, uint16_t* p16, float* x,
                      CgCtl* ctl, hipStream_t s);
 
-// ctl setup: bb must already be in ctl; sets tol2 = rtol^2 bb, clears the rest
-void launch_ctl_prepare(CgCtl* ctl, double rtol, hipStream_t s);
+// ctl setup: bb must already be in ctl; sets tol2 = rtol^2 bb and the step's
+// iterations so far, clears the rest
+void launch_ctl_prepare(CgCtl* ctl, double rtol, int iters, hipStream_t s);
 // *out += x.x (det: one workgroup, a fixed-order sum)
 void launch_norm2(int64_t n, const double* x, double* out, hipStream_t s, bool det = false);
 

@@ -104,7 +104,7 @@ __device__ __forceinline__ void cg_update_body(int64_t n, int64_t n_int, int par
     if (lead) ctl->live = 0;
     return;
   }
-  const T alpha = (T)(slot_sum<NSLOT>(ctl->rz[par]) / slot_sum<NSLOT>(ctl->pAp));
+  const T alpha = (T)(slot_sum<NSLOT>(ctl->rz[par]) / slot_sum<NSLOT>(ctl->pAp[0]));
   if (lead) {
     ctl->alpha = (double)alpha;
     ctl->live = 1;
@@ -169,7 +169,7 @@ __device__ __forceinline__ void cg_dir_body(int64_t n, int par, int iter_abs, in
       ctl->iters = iter_abs + 1;
       if (stop) ctl->done = 1;
     }
-    if (threadIdx.x < NSLOT) ctl->pAp[threadIdx.x] = 0.0;
+    if (threadIdx.x < NSLOT) ctl->pAp[0][threadIdx.x] = 0.0;
   }
   if constexpr (sizeof(T) == 4) {
     // elementwise over the 3n values, four at a time (16-byte accesses; the
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(TPB) void k_cg_dir_h(int64_t n, int par, int iter_a
       ctl->iters = iter_abs + 1;
       if (stop) ctl->done = 1;
     }
-    if (threadIdx.x < NSLOT) ctl->pAp[threadIdx.x] = 0.0;
+    if (threadIdx.x < NSLOT) ctl->pAp[0][threadIdx.x] = 0.0;
   }
   // four values per work-item (8-byte direction, 16-byte x and z accesses)
   typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -258,6 +258,64 @@ __global__ __launch_bounds__(TPB) void k_cg_dir_h(int64_t n, int par, int iter_a
     const float pv = bf16_value(p16[i]);
     x[i] += alpha * pv;
     if (!stop) p16[i] = bf16_round(z[i] + beta * pv);
+  }
+}
+
+// Vector kernel of a two-kernel iteration (after k_tile_dir, which formed
+// p and q = A p): alpha = rz[par] / pAp[par]; x += alpha p; r -= alpha q;
+// z = P r; q = 0 (shared nodes); rz[par^1] += r.z, rr[par^1] += r.r.  r.z of
+// this iteration is kept in rz_prev for the next one's beta, whose pass
+// clears rz[par].
+template <typename T, typename PT, int NT>
+__global__ __launch_bounds__(NT) void k_cg_step(int64_t n, int64_t n_int, int par, const PT* __restrict__ P,
+                                                T* __restrict__ r, T* __restrict__ z, T* __restrict__ q,
+                                                const T* __restrict__ p, T* __restrict__ x, CgCtl* ctl) {
+  __shared__ double sh[2 * NT / 64];
+  const int done = ctl->done;
+  double rz0, pAp;
+  slot_sum2(ctl->rz[par], ctl->pAp[par], rz0, pAp);
+  const T alpha = (T)(rz0 / pAp);
+  double rz = 0.0, rr = 0.0;
+  if (done) return;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      ctl->rz_prev = rz0;
+      ctl->iters += 1;
+    }
+    if (threadIdx.x < NSLOT) ctl->pAp[par ^ 1][threadIdx.x] = 0.0;
+  }
+  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
+    T rv[3], qv[3], pv[3], xv[3], zv[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      rv[c] = r[3 * i + c];
+      qv[c] = q[3 * i + c];
+      pv[c] = p[3 * i + c];
+      xv[c] = x[3 * i + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rv[c] -= alpha * qv[c];
+    bj_apply<T, PT>(P, i, rv, zv);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      x[3 * i + c] = xv[c] + alpha * pv[c];
+      r[3 * i + c] = rv[c];
+      z[3 * i + c] = zv[c];
+    }
+    if (i >= n_int) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) q[3 * i + c] = (T)0;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      rz += (double)rv[c] * (double)zv[c];
+      rr += (double)rv[c] * (double)rv[c];
+    }
+  }
+  block_sum2<NT>(rz, rr, sh);
+  if (threadIdx.x == 0) {
+    atomic_add(&ctl->rz[par ^ 1][blockIdx.x % NSLOT], rz);
+    atomic_add(&ctl->rr[par ^ 1][blockIdx.x % NSLOT], rr);
   }
 }
 
@@ -295,6 +353,21 @@ void launch_cg_update_f32(int64_t n, int64_t n_int, int par, const __half* P, fl
                           CgCtl* ctl, hipStream_t s) {
   hipLaunchKernelGGL((k_cg_update<float, __half>), dim3(vgrid(n)), dim3(TPB), 0, s, n, n_int, par, P, r, z, q, ctl);
 }
+constexpr int STEP_NT = 512;
+static inline unsigned step_grid(int64_t n) {
+  const int64_t g = (n + STEP_NT - 1) / STEP_NT;
+  return (unsigned)(g > 1024 ? 1024 : (g == 0 ? 1 : g));
+}
+void launch_cg_step_f64(int64_t n, int64_t n_int, int par, const double* P, double* r, double* z, double* q,
+                        const double* p, double* x, CgCtl* ctl, hipStream_t s) {
+  hipLaunchKernelGGL((k_cg_step<double, double, STEP_NT>), dim3(step_grid(n)), dim3(STEP_NT), 0, s, n, n_int, par, P,
+                     r, z, q, p, x, ctl);
+}
+void launch_cg_step_f32(int64_t n, int64_t n_int, int par, const __half* P, float* r, float* z, float* q,
+                        const float* p, float* x, CgCtl* ctl, hipStream_t s) {
+  hipLaunchKernelGGL((k_cg_step<float, __half, STEP_NT>), dim3(step_grid(n)), dim3(STEP_NT), 0, s, n, n_int, par, P,
+                     r, z, q, p, x, ctl);
+}
 void launch_cg_dir_h(int64_t n, int par, int iter_abs, int max_iter, const float* z, uint16_t* p16, float* x,
                      CgCtl* ctl, hipStream_t s) {
   hipLaunchKernelGGL(k_cg_dir_h, dim3(vgrid(n)), dim3(TPB), 0, s, n, par, iter_abs, max_iter, z, p16, x, ctl);
@@ -310,10 +383,10 @@ void launch_cg_dir_f32(int64_t n, int par, int iter_abs, int max_iter, const flo
 
 // ------------------------------------------------------------ scalars
 
-__device__ __forceinline__ void ctl_prepare_body(CgCtl* ctl, double rtol) {
+__device__ __forceinline__ void ctl_prepare_body(CgCtl* ctl, double rtol, int iters) {
   const int i = threadIdx.x;
   if (i < NSLOT) {
-    ctl->pAp[i] = 0.0;
+    ctl->pAp[0][i] = ctl->pAp[1][i] = 0.0;
     ctl->rz[0][i] = ctl->rz[1][i] = 0.0;
     ctl->rr[0][i] = ctl->rr[1][i] = 0.0;
   }
@@ -321,12 +394,12 @@ __device__ __forceinline__ void ctl_prepare_body(CgCtl* ctl, double rtol) {
     ctl->tol2 = rtol * rtol * ctl->bb;
     ctl->rr_true = 0.0;
     ctl->done = 0;
-    ctl->iters = 0;
+    ctl->iters = iters;
   }
 }
-__global__ void k_ctl_prepare(CgCtl* ctl, double rtol) { ctl_prepare_body(ctl, rtol); }
-void launch_ctl_prepare(CgCtl* ctl, double rtol, hipStream_t s) {
-  hipLaunchKernelGGL(k_ctl_prepare, dim3(1), dim3(64), 0, s, ctl, rtol);
+__global__ void k_ctl_prepare(CgCtl* ctl, double rtol, int iters) { ctl_prepare_body(ctl, rtol, iters); }
+void launch_ctl_prepare(CgCtl* ctl, double rtol, int iters, hipStream_t s) {
+  hipLaunchKernelGGL(k_ctl_prepare, dim3(1), dim3(64), 0, s, ctl, rtol, iters);
 }
 
 __global__ __launch_bounds__(TPB) void k_norm2(int64_t n, const double* __restrict__ x, double* out) {
@@ -712,7 +785,7 @@ __global__ __launch_bounds__(TPB) void k_lane_op(const LaneDev* __restrict__ lan
     acc = block_sum(acc, sh);
     if (threadIdx.x == 0) atomic_add(&L.ctl64->bb, acc);
   } else if constexpr (OP == LANE_PREPARE64) {
-    if (blockIdx.x == 0) ctl_prepare_body(L.ctl64, L.rtol);
+    if (blockIdx.x == 0) ctl_prepare_body(L.ctl64, L.rtol, 0);
   } else if constexpr (OP == LANE_GUESS) {
     if (L.guess_order >= -1) guess_poly_body(nd, L.hist, L.hist_head, L.guess_order, L.x, L.ctl64);
   } else if constexpr (OP == LANE_RRTRUE_RESET) {
@@ -735,7 +808,7 @@ __global__ __launch_bounds__(TPB) void k_lane_op(const LaneDev* __restrict__ lan
     if (blockIdx.x == 0) {
       CgCtl* c = L.ctl32;
       if (threadIdx.x < NSLOT) {
-        c->pAp[threadIdx.x] = 0.0;
+        c->pAp[0][threadIdx.x] = c->pAp[1][threadIdx.x] = 0.0;
         c->rz[0][threadIdx.x] = c->rz[1][threadIdx.x] = 0.0;
         c->rr[0][threadIdx.x] = c->rr[1][threadIdx.x] = 0.0;
       }

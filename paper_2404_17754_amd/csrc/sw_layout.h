@@ -38,6 +38,8 @@ struct HostLayout {
   std::vector<int32_t> tile_nodes;     // internal node ids, per tile: interior then shared
   std::vector<int32_t> tile_int_base;  // first interior node id of each tile
   std::vector<int32_t> tile_nint;      // interior node count of each tile
+  std::vector<int32_t> tile_own_base;  // first id of the shared nodes no earlier tile touches: of a tile's
+                                       // shared nodes, those from this id on are its own to store
   std::vector<int32_t> tile_face_off;  // [n_tiles + 1]
   std::vector<uint16_t> conn_loc;      // [10][tet_stride] 3 x tile-local node index (offset of the node's
                                        // first value in 3-value-per-node tile arrays)

@@ -303,9 +303,10 @@ void build_layout(int64_t n_nodes, int64_t n_tets, int64_t n_faces, const double
   int32_t next = 0;
   L.tile_int_base.resize(n_tiles);
   L.tile_nint.resize(n_tiles);
+  L.tile_own_base.resize(n_tiles);
   for (int pass = 0; pass < 2; ++pass) {
     for (int32_t t = 0; t < n_tiles; ++t) {
-      if (pass == 0) L.tile_int_base[t] = next;
+      (pass == 0 ? L.tile_int_base : L.tile_own_base)[t] = next;
       for (int32_t i = L.tile_elem_off[t]; i < L.tile_elem_off[t + 1]; ++i) {
         const int32_t e = L.elem_order[i];
         for (int k = 0; k < 10; ++k) {

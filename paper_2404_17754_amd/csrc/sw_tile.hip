@@ -32,9 +32,8 @@ __device__ __forceinline__ U ldc(const U* p, int64_t i) {
   return ((const __attribute__((address_space(4))) U*)p)[i];
 }
 
-// Input value i of a pass (x1), and of its dashpot term (xf): in the 16-bit
-// passes of the SW_MIXED_FP16 inner CG both come from the bfloat16 input
-// x1h (x1 and xf null), so every term of A acts on the same stored values.
+// Input value i of a pass (x1): in the 16-bit passes of the SW_MIXED_FP16
+// inner CG it comes from the bfloat16 input x1h (x1 null).
 template <typename T>
 __device__ __forceinline__ T x1_at(const TileArgs<T>& A, int64_t i) {
   return A.x1[i];
@@ -43,15 +42,6 @@ template <>
 __device__ __forceinline__ float x1_at<float>(const TileArgs<float>& A, int64_t i) {
   return A.x1h ? bf16_value(A.x1h[i]) : A.x1[i];
 }
-template <typename T>
-__device__ __forceinline__ T xf_at(const TileArgs<T>& A, int64_t i) {
-  return A.xf[i];
-}
-template <>
-__device__ __forceinline__ float xf_at<float>(const TileArgs<float>& A, int64_t i) {
-  return A.x1h ? bf16_value(A.x1h[i]) : A.xf[i];
-}
-
 // Per-element inputs fetched from global memory: tile-local connectivity
 // (stored as 3 x the local index: the offset of the node's first value in
 // the tile's 3-value-per-node LDS arrays, which saves the address
@@ -118,7 +108,7 @@ __device__ __forceinline__ void elem_geometry(const ElemIn<T>& in, Geo<T>& G) {
 // slots of A.eout instead of the LDS accumulator.
 template <typename T, int NT, bool PF, bool STIFF, bool MASS, bool DYN, bool MATL, bool DET, typename Hook>
 __device__ __forceinline__ void tile_element_loop(const MeshDev& m, const uint8_t* __restrict__ emat,
-                                                  const MatDev* __restrict__ mats, const float* matl,
+                                                  const MatDev* __restrict__ mats, const T* matl,
                                                   const TileArgs<T>& A, int t, const int32_t* gid, const T* xs,
                                                   double* ys, Hook&& hook) {
   const int eb = ldc(m.tile_elem_off, t);
@@ -177,7 +167,7 @@ __device__ __forceinline__ void tile_element_loop(const MeshDev& m, const uint8_
 // face slots of A.fout).
 template <typename T, int NT, bool PF, bool MATL, bool DET, typename Hook>
 __device__ __forceinline__ void tile_elements(const MeshDev& m, const uint8_t* __restrict__ emat,
-                                              const MatDev* __restrict__ mats, const float* matl,
+                                              const MatDev* __restrict__ mats, const T* matl,
                                               const TileArgs<T>& A, int t, const int32_t* gid, const T* xs,
                                               double* ys, Hook&& hook) {
   if constexpr (sizeof(T) == 8) {
@@ -227,7 +217,7 @@ __device__ __forceinline__ void tile_elements(const MeshDev& m, const uint8_t* _
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
 #pragma unroll
-          for (int c = 0; c < 3; ++c) w[k][c] = xf_at(A, 3 * gn[k] + c);
+          for (int c = 0; c < 3; ++c) w[k][c] = A.xf ? A.xf[3 * gn[k] + c] : xs[3 * ln[k] + c];
         }
         const T n[3] = {(T)g.n[0], (T)g.n[1], (T)g.n[2]};
         face_dashpot_apply<T>(n, (T)g.area, (T)mt.zp, (T)mt.zs, A.sC, w, out);
@@ -367,7 +357,7 @@ __device__ __forceinline__ void tile_body(const MeshDev& m, const uint8_t* __res
   const double energy = tile_scatter<T, NT>(m, A, t, gid, xs, ys);
   if (iter >= 0) {
     const double s = block_sum_n<NT>(energy, sh);
-    if (threadIdx.x == 0) atomic_add(&ctl->pAp[t % NSLOT], s);
+    if (threadIdx.x == 0) atomic_add(&ctl->pAp[0][t % NSLOT], s);
   }
 }
 
@@ -439,8 +429,109 @@ __global__ __launch_bounds__(NT) void k_tile_lanes(const TileLane<T>* __restrict
   tile_body<T, NT>(L.m, L.emat, L.mats, L.A, L.ctl, iter, w.y, smem_raw, sh);
 }
 
-// Largest material table the pipelined pass copies into LDS.
+// Largest material table the CG passes copy into LDS.
 constexpr int PIPE_MATS = 32;
+
+// Operator pass of a two-kernel CG iteration (k_cg_step follows it), bound by
+// latency: its chain is launch, control block and node ids (1.4 us), the
+// values of z and p_old (1 us), the elements (4.4 us, half of it the LDS
+// atomics of one compute unit), the scatter and the sum (1.2 us).  The
+// direction p = z + beta p_old is formed while the tile's nodes are gathered
+// and the tile's own nodes of p are stored, so the iteration has no direction
+// kernel.  One workgroup per tile.  p_old and p are two buffers, since
+// neighbouring tiles still read p_old; a tile stores its interior nodes and
+// the shared nodes no earlier tile touches (tile_own_base).
+// par: the iteration's parity; first: the solve's first iteration (p = z).
+template <typename T, int NT, int NPT, int WPE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void k_tile_dir(MeshDev m, const uint8_t* __restrict__ emat,
+                                                 const MatDev* __restrict__ mats, TileArgs<T> A,
+                                                 const T* __restrict__ p_old, T* __restrict__ p, CgCtl* ctl, int par,
+                                                 int first, int max_iter) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double sh[NT / 64];
+  __shared__ T matl[3 * PIPE_MATS];
+  double* ys = reinterpret_cast<double*>(smem_raw);
+  int32_t* gid = reinterpret_cast<int32_t*>(ys + 3 * m.max_tile_nodes);
+  T* xs = reinterpret_cast<T*>(gid + m.max_tile_nodes + (m.max_tile_nodes & 1));
+  // workgroup b runs on XCD b mod 8: each XCD takes a contiguous eighth of
+  // the tiles, so neighbours, which share nodes, meet in one L2
+  const int xcd = blockIdx.x & 7;
+  const int hi = (int)(((int64_t)m.n_tiles * (xcd + 1)) >> 3);
+  const int t = (int)(((int64_t)m.n_tiles * xcd) >> 3) + (int)(blockIdx.x >> 3);
+  const bool lead = blockIdx.x == 0;
+  // every load of the gather goes out before the first is waited for
+  const int n0 = t < hi ? ldc(m.tile_node_off, t) : 0;
+  const int nt = t < hi ? ldc(m.tile_node_off, t + 1) - n0 : 0;
+  const int nint = t < hi ? ldc(m.tile_nint, t) : 0;
+  const int own = t < hi ? ldc(m.tile_own_base, t) : 0;
+  int32_t g[NPT];
+#pragma unroll
+  for (int q = 0; q < NPT; ++q) {
+    const int j = threadIdx.x + q * NT;
+    g[q] = j < nt ? m.tile_nodes[n0 + j] : 0;
+  }
+  // material constants (lam, mu, rho) of one entry per work-item, for the LDS copy
+  const bool has_mat = (int)threadIdx.x < 3 * A.n_mat;
+  const double mat = has_mat ? (&mats[threadIdx.x / 3].lam)[threadIdx.x % 3] : 0.0;
+  // the previous iteration's residual decides whether this one runs: the
+  // same test in every workgroup, on values no workgroup of this launch writes
+  const double tol2 = ctl->tol2, rz_prev = ctl->rz_prev;
+  const int iters = ctl->iters, done = ctl->done;
+  double rr, rz;
+  slot_sum2(ctl->rr[par], ctl->rz[par], rr, rz);
+  const T beta = first ? (T)0 : (T)(rz / rz_prev);
+  const bool stop = first ? rr <= tol2 : (!(rr > tol2) || iters >= max_iter);  // NaN stops too
+  if (done) return;
+  if (stop) {
+    if (lead && threadIdx.x == 0) ctl->done = 1;
+    return;
+  }
+  if (lead && threadIdx.x < NSLOT) {
+    ctl->rz[par ^ 1][threadIdx.x] = 0.0;
+    ctl->rr[par ^ 1][threadIdx.x] = 0.0;
+  }
+  if (t >= hi) return;
+  const T* __restrict__ z = A.x1;
+  auto gather = [&] {
+    T zv[NPT][3], pv[NPT][3];
+    if (has_mat) matl[threadIdx.x] = (T)mat;
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) zv[q][c] = z[3 * (int64_t)g[q] + c];
+    }
+    if (!first) {
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) pv[q][c] = p_old[3 * (int64_t)g[q] + c];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) pv[q][0] = pv[q][1] = pv[q][2] = (T)0;
+    }
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int j = threadIdx.x + q * NT;
+      if (j < nt) {
+        gid[j] = g[q];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const T v = zv[q][c] + beta * pv[q][c];
+          xs[3 * j + c] = v;
+          ys[3 * j + c] = 0.0;
+          if (j < nint || g[q] >= own) p[3 * (int64_t)g[q] + c] = v;
+        }
+      }
+    }
+    __syncthreads();
+  };
+  tile_elements<T, NT, false, true, false>(m, emat, mats, matl, A, t, gid, xs, ys, gather);
+  __syncthreads();
+  const double energy = tile_scatter<T, NT>(m, A, t, gid, xs, ys);
+  const double e = block_sum_n<NT>(energy, sh);
+  if (threadIdx.x == 0) atomic_add(&ctl->pAp[par][t % NSLOT], e);
+}
 
 // FP32 operator pass of a CG iteration (input scaled by 1, no second input),
 // persistent and software-pipelined.  Each workgroup walks a run of tiles;
@@ -567,7 +658,7 @@ __global__ __launch_bounds__(NT) void k_tile_pipe(MeshDev m, const uint8_t* __re
     t = tn;
   }
   const double e = block_sum_n<NT>(energy, sh);
-  if (threadIdx.x == 0) atomic_add(&ctl->pAp[blockIdx.x % NSLOT], e);
+  if (threadIdx.x == 0) atomic_add(&ctl->pAp[0][blockIdx.x % NSLOT], e);
 }
 
 // The same persistent pipeline over the (lane, tile) items of several cases:
@@ -674,7 +765,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     __syncthreads();
     const double energy = tile_scatter<float, NT>(L.m, L.A, t, gid, xs, ys);
     const double e = block_sum_n<NT>(energy, sh);
-    if (threadIdx.x == 0) atomic_add(&L.ctl->pAp[t % NSLOT], e);
+    if (threadIdx.x == 0) atomic_add(&L.ctl->pAp[0][t % NSLOT], e);
     __syncthreads();
     if (!more) break;
 #pragma unroll
@@ -721,6 +812,8 @@ static size_t tile_lds(int max_tile_nodes) {
 
 constexpr int PIPE_NT = 256, PIPE_NPT = 5;
 static_assert(PIPE_NT * PIPE_NPT >= TILE_MAX_NODES, "the pipelined pass must cover a whole tile");
+static_assert(512 * 3 >= TILE_MAX_NODES && 256 * 5 >= TILE_MAX_NODES, "k_tile_dir must cover a whole tile");
+static_assert(3 * PIPE_MATS <= 256, "one work-item per entry of the material table");
 
 template <typename T>
 static void launch_tile(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<T>& a, CgCtl* ctl,
@@ -743,6 +836,48 @@ static void launch_tile(const MeshDev& m, const uint8_t* emat, const MatDev* mat
   hipLaunchKernelGGL((k_tile<T, NT>), dim3(m.n_tiles), dim3(NT), lds, s, m, emat, mats, a, ctl, iter);
 }
 
+// Whether a solve's iterations run as two kernels (k_tile_dir, k_cg_step)
+// rather than three.  In FP64 always: 1374 us an iteration (share of the
+// step's other work included) against 1597 on 9.6 M tets, 17 against 26 on
+// 3000.  In FP32 up to 4000 tiles: 67 us against 86 at 1500 tiles, 128
+// against 141 at 3000, but 270 against 255 at 6750, where the vectors no
+// longer stay in the caches and the pipelined pass and the non-temporal
+// accesses of the three kernels gain more.  A cap on the persistent pass's
+// workgroups that binds asks for that pass.
+constexpr int TWO_KERNEL_TILES_F32 = 4000;
+bool two_kernel_cg(const MeshDev& m, int n_mat, int grid_cap, bool f32) {
+  return n_mat >= 1 && n_mat <= PIPE_MATS &&
+         (!f32 || (m.n_tiles <= TWO_KERNEL_TILES_F32 && (grid_cap == 0 || grid_cap >= m.n_tiles)));
+}
+
+// FP32: 512 work-items, one element each in a full tile, two workgroups per
+// compute unit (126 registers: four waves per SIMD): 28.1 us an iteration
+// against 30.1 with 256 at 375 tiles, 48 against 53 at 844, the same at 81.
+// FP64 needs twice the registers, one workgroup of 512 per compute unit, so
+// only while every tile has a compute unit of its own: 19.6 us against 20.1
+// at 6 tiles, but 45.6 against 41.4 at 375.
+template <typename T>
+static void launch_tile_dir(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<T>& a,
+                            const T* p_old, T* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
+  const size_t lds = tile_lds<T>(m.max_tile_nodes);
+  const dim3 grid(8 * ((m.n_tiles + 7) / 8));
+  constexpr bool f32 = sizeof(T) == 4;
+  if (f32 || m.n_tiles <= 256)
+    hipLaunchKernelGGL((k_tile_dir<T, 512, 3, f32 ? 4 : 2>), grid, dim3(512), lds, s, m, emat, mats, a, p_old, p, ctl,
+                       iter & 1, iter == 0, max_iter);
+  else if constexpr (!f32)
+    hipLaunchKernelGGL((k_tile_dir<T, 256, 5, 2>), grid, dim3(256), lds, s, m, emat, mats, a, p_old, p, ctl, iter & 1,
+                       iter == 0, max_iter);
+}
+void launch_tile_dir_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
+                         const double* p_old, double* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
+  launch_tile_dir<double>(m, emat, mats, a, p_old, p, ctl, iter, max_iter, s);
+}
+void launch_tile_dir_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
+                         const float* p_old, float* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
+  launch_tile_dir<float>(m, emat, mats, a, p_old, p, ctl, iter, max_iter, s);
+}
+
 static unsigned node_grid(int64_t n_nodes) {
   unsigned g = nblocks(n_nodes);
   return g > 8192 ? 8192 : (g == 0 ? 1 : g);
@@ -763,7 +898,7 @@ void launch_tile_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, 
   hipLaunchKernelGGL(k_node_gather, dim3(node_grid(m.n_nodes)), dim3(TPB), 0, s, m, a.eout, a.fout, a.y, 3, 0,
                      a.accumulate, elems, faces, ctl, iter);
   if (iter >= 0)
-    hipLaunchKernelGGL(k_dot_slots, dim3(NSLOT), dim3(TPB), 0, s, 3 * m.n_nodes, a.x1, a.y, ctl->pAp, ctl);
+    hipLaunchKernelGGL(k_dot_slots, dim3(NSLOT), dim3(TPB), 0, s, 3 * m.n_nodes, a.x1, a.y, ctl->pAp[0], ctl);
 }
 void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
                      CgCtl* ctl, int iter, int grid_cap, hipStream_t s) {
