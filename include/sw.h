@@ -136,10 +136,10 @@ SW_API int sw_ctx_destroy(sw_ctx* ctx);
  * way; while the profiler is on, kernels are launched directly. */
 SW_API int sw_ctx_set_graphs(sw_ctx* ctx, int32_t enable);
 
-/* Workgroup count of the persistent FP32 operator passes (single case and
- * batch lanes) of objects on this context: 0 (default) = three per compute
- * unit, else at most max_workgroups (a positive multiple of 8, one run per
- * XCD), so that each workgroup walks more tiles.  A tuning and test knob;
+/* Workgroup count of the FP32 operator passes (single case and batch lanes)
+ * of objects on this context: 0 (default) = one per tile, else at most
+ * max_workgroups (a positive multiple of 8, one run per XCD), so that each
+ * workgroup walks several tiles.  A tuning and test knob;
  * results are the same to rounding.  SW_EINVAL for other values. */
 SW_API int sw_ctx_set_grid_cap(sw_ctx* ctx, int32_t max_workgroups);
 
@@ -268,7 +268,8 @@ SW_API int sw_case_waveform_device(const sw_case* c, const double** out);
  * synchronous.  For testing and for callers composing their own solvers. */
 SW_API int sw_case_apply(sw_case* c, int32_t op, const double* x_dev, double* y_dev);
 /* Same with the FP32 operator used by the SW_MIXED_FP32 inner solve; for
- * SW_OP_A it runs the very pass an inner CG iteration launches. */
+ * SW_OP_A it runs the pass of an inner CG iteration (on small and middle
+ * meshes without the direction that the iteration's own pass forms first). */
 SW_API int sw_case_apply_f32(sw_case* c, int32_t op, const float* x_dev, float* y_dev);
 /* Right-hand side b of the next step (from the current state) into y_dev. */
 SW_API int sw_case_rhs(sw_case* c, double* y_dev);
@@ -446,14 +447,16 @@ SW_API int sw_batch_step(sw_batch* b, int32_t n_steps);
  * (free between steps; left zero) and keeps the fastest for later steps.
  * Candidates k = 2 * order + grid: order 0 = one mesh after the other,
  * 1 = the meshes interleaved tile by tile (each with the lanes of a tile
- * adjacent); grid 0 = three workgroups per compute unit, 1 = two.  Writes
+ * adjacent); grid 0 = one workgroup per tile, 1 = two per compute unit.  Writes
  * the chosen k and (optional) the mean pass time of each candidate (ms, 4
  * values).  Results do not depend on the schedule beyond rounding.
  * Synchronous. */
 SW_API int sw_batch_autotune(sw_batch* b, int32_t reps, int32_t* choice, double* ms);
-/* The same for a single case's persistent FP32 pass (mixed precisions):
- * candidates k = 0, 1, 2 are three, two and one workgroups per compute
- * unit; ms: 3 values (optional).  Synchronous. */
+/* The same for a single case's FP32 pass (mixed precisions): candidates
+ * k = 0, 1, 2 are one workgroup per tile, and two and one per compute unit;
+ * ms: 3 values (optional).  A case whose CG iterations form the direction
+ * inside the operator pass keeps one workgroup per tile for its march.
+ * Synchronous. */
 SW_API int sw_case_autotune(sw_case* c, int32_t reps, int32_t* choice, double* ms);
 /* Statistics of every lane (out: n entries, lane order; as
  * sw_case_stats_get of each case). */

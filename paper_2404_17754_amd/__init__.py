@@ -67,7 +67,7 @@ class Context:
         L.check(self.lib.sw_ctx_set_graphs(self.h, 1 if enable else 0))
 
     def set_grid_cap(self, max_workgroups):
-        """Cap the workgroups of the persistent FP32 passes (0: default)."""
+        """Cap the workgroups of the FP32 operator passes (0: one per tile)."""
         L.check(self.lib.sw_ctx_set_grid_cap(self.h, int(max_workgroups)))
 
     def profile(self, enable=True, kinds=None, every=1):

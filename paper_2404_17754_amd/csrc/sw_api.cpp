@@ -105,7 +105,7 @@ struct sw_ctx {
   int device;
   hipStream_t stream;
   KernelProfiler prof;
-  int grid_cap = 0;  // workgroup cap of the persistent FP32 passes (0: none)
+  int grid_cap = 0;  // workgroup cap of the FP32 passes (0: none)
   // CG iterations replay captured HIP graphs of several iterations; they are
   // captured on a stream of the library's own
   bool graphs = true;
@@ -190,7 +190,7 @@ struct sw_case {
   // with
   hipGraphExec_t cg_graph[2] = {nullptr, nullptr};
   int cg_graph_cap[2] = {-1, -1};
-  // workgroup cap of this case's persistent FP32 pass chosen by
+  // workgroup cap of this case's FP32 pass chosen by
   // sw_case_autotune (-1: the context's)
   int grid_cap = -1;
   double* wave;
@@ -254,6 +254,7 @@ struct sw_batch {
   int n = 0;
   int64_t max_nodes = 0;
   int max_tile_nodes = 0;
+  int max_mat = 0;
   int n_work = 0;
   // device tables (in the caller's workspace)
   LaneDev* d_lanes = nullptr;
@@ -264,7 +265,7 @@ struct sw_batch {
   TileLane<double>* d_true = nullptr;
   TileLane<float>* d_cg32 = nullptr;
   int2* d_work = nullptr;
-  int2* d_items = nullptr;  // (lane, tile), tile-major, for the persistent FP32 pass
+  int2* d_items = nullptr;  // (lane, tile), tile-major, for the FP32 pass
   int n_items = 0;
   // host copies
   std::vector<LaneDev> lanes;
@@ -504,7 +505,8 @@ const HostLayout& layout_for(const sw_mesh_desc* d) {
 
 size_t mesh_layout(const HostLayout& L, bool det, Carver& cv, MeshDev* md) {
   const int32_t nT = L.n_tiles;
-  auto conn_loc = cv.take<uint16_t>(10 * L.tet_stride);
+  auto conn8 = cv.take<uint4>(L.tet_stride);
+  auto conn2 = cv.take<uint32_t>(L.tet_stride);
   auto teo = cv.take<int32_t>(nT + 1);
   auto tno = cv.take<int32_t>(nT + 1);
   auto tn = cv.take<int32_t>(std::max<size_t>(L.tile_nodes.size(), 1));
@@ -539,7 +541,8 @@ size_t mesh_layout(const HostLayout& L, bool det, Carver& cv, MeshDev* md) {
     md->n_interior = L.n_interior;
     md->tet_stride = L.tet_stride;
     md->face_stride = L.face_stride;
-    md->conn_loc = conn_loc;
+    md->conn8 = conn8;
+    md->conn2 = conn2;
     md->tile_elem_off = teo;
     md->tile_node_off = tno;
     md->tile_nodes = tn;
@@ -612,7 +615,10 @@ int mesh_create(sw_ctx* ctx, const sw_mesh_desc* d, void* ws, size_t ws_bytes, s
   MeshDev md;
   mesh_layout(L, det, cv, &md);
   hipStream_t s = ctx->stream;
-  HIPC(up(md.conn_loc, L.conn_loc, s));
+  // the connectivity goes through the place of the FP64 geometry, written later
+  static_assert(sizeof(L.conn_loc[0]) <= sizeof(double), "conn_loc must fit into geo64");
+  HIPC(up((const uint16_t*)md.geo64, L.conn_loc, s));
+  launch_pack_conn(md, (const uint16_t*)md.geo64, (uint4*)md.conn8, (uint32_t*)md.conn2, s);
   HIPC(up(md.tile_elem_off, L.tile_elem_off, s));
   HIPC(up(md.tile_node_off, L.tile_node_off, s));
   HIPC(up(md.tile_nodes, L.tile_nodes, s));
@@ -926,6 +932,7 @@ int build_rhs(sw_case* c, double* y) {
   A.vin = c->vin + 3 * (c->step + 1);
   A.y = y;
   A.accumulate = 0;
+  A.n_mat = c->n_mat;
   A.eout = c->det_e;
   A.fout = c->det_f;
   launch_tile_f64(c->mesh->dev, c->emat, c->mats, A, nullptr, -1, s);
@@ -939,6 +946,7 @@ int build_rhs(sw_case* c, double* y) {
   B.a2 = -c->beta;
   B.y = y;
   B.accumulate = 1;
+  B.n_mat = c->n_mat;
   B.eout = c->det_e;
   B.fout = c->det_f;
   launch_tile_f64(c->mesh->dev, c->emat, c->mats, B, nullptr, -1, s);
@@ -1134,7 +1142,7 @@ int read_ctl(sw_case* c, CgCtl* dev, CgCtl* host) {
 template <bool F32>
 bool two_kernel(const sw_case* c) {
   return !c->ctx->prof.on && !c->det && !(F32 && c->p16) &&
-         two_kernel_cg(c->mesh->dev, c->n_mat, F32 ? case_grid_cap(c) : 0, F32);
+         two_kernel_cg(c->mesh->dev, F32 ? case_grid_cap(c) : 0, F32);
 }
 
 // One CG iteration of the single-case solve on stream s: the operator pass
@@ -2265,7 +2273,7 @@ std::vector<int2> batch_work(sw_case* const* cases, int n) {
   return work;
 }
 
-// Items of the persistent FP32 pass, tile by tile with the lanes of one
+// Items of the FP32 pass, tile by tile with the lanes of one
 // mesh adjacent (they share the tile's mesh data).  schedule 0: one mesh
 // after the other; 1: the meshes interleaved tile by tile (tile t of every
 // mesh, then tile t + 1), which spreads each mesh over all XCDs.
@@ -2324,6 +2332,7 @@ TileLane<T> tile_lane(const sw_case* c) {
   t.m = c->mesh->dev;
   t.emat = c->emat;
   t.mats = c->mats;
+  t.A.n_mat = c->n_mat;
   return t;
 }
 
@@ -2348,7 +2357,8 @@ void batch_cg_iteration(sw_batch* b, int i, bool dev_index, hipStream_t s, bool 
   sw_ctx* cx = b->ctx;
   const int n = b->n;
   int ev = prof ? prof_begin(cx, SW_PROF_TILE_F32) : -1;
-  launch_tile_lanes_pipe_f32(b->d_cg32, b->d_items, b->n_items, b->max_tile_nodes, b->d_st, i, batch_grid_cap(b), s);
+  launch_tile_lanes_f32(b->d_cg32, b->d_items, b->n_items, b->max_tile_nodes, b->max_mat, b->d_st, i,
+                        batch_grid_cap(b), s);
   if (prof) prof_end(cx, ev);
   ev = prof ? prof_begin(cx, SW_PROF_UPDATE_F32) : -1;
   launch_lanes_cg(true, false, n, b->max_nodes, b->d_lanes, b->d_st, i, s, dev_index);
@@ -2411,8 +2421,8 @@ int batch_step_once(sw_batch* b) {
   if (rc) return rc;
   // right-hand side, its norm, tolerance, initial guess
   launch_lanes(LANE_BEGIN_STEP, n, b->max_nodes, b->d_lanes, nullptr, nullptr, s);
-  launch_tile_lanes_f64(b->d_rhs1, b->d_work, b->n_work, b->max_tile_nodes, nullptr, -1, s);
-  launch_tile_lanes_f64(b->d_rhs2, b->d_work, b->n_work, b->max_tile_nodes, nullptr, -1, s);
+  launch_tile_lanes_f64(b->d_rhs1, b->d_work, b->n_work, b->max_tile_nodes, b->max_mat, true, nullptr, s);
+  launch_tile_lanes_f64(b->d_rhs2, b->d_work, b->n_work, b->max_tile_nodes, b->max_mat, true, nullptr, s);
   launch_lanes(LANE_NORM2_B, n, b->max_nodes, b->d_lanes, nullptr, nullptr, s);
   launch_lanes(LANE_PREPARE64, n, b->max_nodes, b->d_lanes, nullptr, nullptr, s);
   launch_lanes(LANE_GUESS, n, b->max_nodes, b->d_lanes, nullptr, nullptr, s);
@@ -2445,7 +2455,7 @@ int batch_step_once(sw_batch* b) {
     }
     if ((rc = batch_upload(b, b->d_st, b->st.data(), n * sizeof(LaneState)))) return rc;
     launch_lanes(LANE_RRTRUE_RESET, n, b->max_nodes, b->d_lanes, b->d_st, nullptr, s);
-    launch_tile_lanes_f64(b->d_true, b->d_work, b->n_work, b->max_tile_nodes, b->d_st, -1, s);
+    launch_tile_lanes_f64(b->d_true, b->d_work, b->n_work, b->max_tile_nodes, b->max_mat, false, b->d_st, s);
     launch_lanes(LANE_TRUE_RES, n, b->max_nodes, b->d_lanes, b->d_st, nullptr, s);
     LAUNCHED();
     if ((rc = batch_gather(b))) return rc;
@@ -2631,6 +2641,7 @@ extern "C" int sw_batch_create(sw_ctx* ctx, sw_case* const* cases, int32_t n, vo
     sw_case* c = cases[l];
     b->max_nodes = std::max(b->max_nodes, c->mesh->n_nodes);
     b->max_tile_nodes = std::max(b->max_tile_nodes, c->mesh->dev.max_tile_nodes);
+    b->max_mat = std::max(b->max_mat, c->n_mat);
     LaneDev& L = b->lanes[l];
     L = LaneDev{};
     L.n_nodes = c->mesh->n_nodes;
@@ -2736,7 +2747,7 @@ extern "C" int sw_batch_apply_f32(sw_batch* b, const float* const* x, float* con
   LAUNCHED();
   int rc = batch_upload(b, b->d_st, b->st.data(), b->n * sizeof(LaneState));
   if (rc) return rc;
-  launch_tile_lanes_pipe_f32(b->d_cg32, b->d_items, b->n_items, b->max_tile_nodes, b->d_st, 1, batch_grid_cap(b),
+  launch_tile_lanes_f32(b->d_cg32, b->d_items, b->n_items, b->max_tile_nodes, b->max_mat, b->d_st, 1, batch_grid_cap(b),
                              s);
   for (int l = 0; l < b->n; ++l) {
     sw_case* c = b->cases[l];
@@ -2811,7 +2822,8 @@ extern "C" int sw_case_autotune(sw_case* c, int32_t reps, int32_t* choice, doubl
     if (ms[k] < ms[best]) best = k;
   }
   LAUNCHED();
-  c->grid_cap = caps[best];
+  // two-kernel iterations have one workgroup per tile
+  c->grid_cap = two_kernel_cg(c->mesh->dev, 0, true) ? 0 : caps[best];
   if (choice) *choice = best;
   if (ms_out)
     for (int k = 0; k < 3; ++k) ms_out[k] = ms[k];
@@ -2845,7 +2857,7 @@ extern "C" int sw_batch_autotune(sw_batch* b, int32_t reps, int32_t* choice, dou
     for (int g = 0; g < 2; ++g) {
       const int k = 2 * sch + g;
       rc = time_launches(s, reps, [&] {
-        launch_tile_lanes_pipe_f32(b->d_cg32, b->d_items, b->n_items, b->max_tile_nodes, b->d_st, 1, caps[g], s);
+        launch_tile_lanes_f32(b->d_cg32, b->d_items, b->n_items, b->max_tile_nodes, b->max_mat, b->d_st, 1, caps[g], s);
       }, &ms[k]);
       if (rc) return rc;
       if (ms[k] < ms[best]) best = k;

@@ -95,6 +95,14 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double* sh) {
   }
 }
 
+// A pointer read from a table in memory, known to point to global memory: its
+// loads and stores are global ones (without this they are flat ones, which
+// also occupy the LDS counters and wait with the LDS accesses).
+template <typename U>
+__device__ __forceinline__ U* as_global(U* p) {
+  return (U*)(__attribute__((address_space(1))) U*)(uintptr_t)p;
+}
+
 __device__ __forceinline__ void atomic_add(double* p, double v) { unsafeAtomicAdd(p, v); }
 __device__ __forceinline__ void atomic_add(float* p, float v) { unsafeAtomicAdd(p, v); }
 

@@ -46,7 +46,11 @@ struct MeshDev {
   int64_t n_interior;            // nodes [0, n_interior) belong to one tile each
   int32_t n_tiles, max_tile_nodes;
   int64_t tet_stride, face_stride;
-  const uint16_t* conn_loc;      // [10][tet_stride], 3 x tile-local node index
+  // per element, in vector loads: byte offsets of its nodes' first values in a
+  // tile's FP32 node array (12 x the tile-local node index), nodes 0..7 as eight
+  // 16-bit halves and nodes 8, 9 as two
+  const uint4* conn8;            // [tet_stride]
+  const uint32_t* conn2;         // [tet_stride]
   const int32_t* tile_elem_off;  // [n_tiles + 1]
   const int32_t* tile_node_off;  // [n_tiles + 1]
   const int32_t* tile_nodes;
@@ -55,8 +59,10 @@ struct MeshDev {
   const int32_t* tile_own_base;  // shared nodes from this id on are first touched by the tile (or a later one)
   const int32_t* tile_face_off;  // [n_tiles + 1]
   const double* xyz;             // [n_nodes][3]
-  const float* geo32;            // [10][tet_stride]: FP32 grad L1..L3 (9) and volume
-  const double* geo64;           // [10][tet_stride]: the same in FP64
+  // grad L1..L3 (9 values) and volume per element: FP32 as two arrays of four
+  // values and one of two, FP64 as five arrays of two
+  const float* geo32;            // float4 [2][tet_stride], float2 [tet_stride]
+  const double* geo64;           // double2 [5][tet_stride]
   const int32_t* fconn;          // [6][face_stride]
   const uint16_t* fconn_loc;     // [6][face_stride]
   const int32_t* face_elem;      // [n_faces]
@@ -72,6 +78,14 @@ struct MeshDev {
   const int32_t* finc_off;       // [n_nodes + 1]
   const int32_t* finc;
 };
+
+#if defined(__HIP__)
+// tile-local index of node k of internal element e
+__device__ __forceinline__ int conn_node(const MeshDev& m, int k, int64_t e) {
+  const uint32_t w = k < 8 ? reinterpret_cast<const uint32_t*>(m.conn8 + e)[k >> 1] : m.conn2[e];
+  return (int)((k & 1 ? w >> 16 : w & 0xffffu) / 12u);
+}
+#endif
 
 // One tiled operator pass:
 //   y (=|+=) sM M xe + sK K xe + sC C_abs xf + F(vin)
@@ -90,7 +104,7 @@ struct TileArgs {
   const double* vin;   // 3 values or nullptr
   T* y;
   int accumulate;      // interior nodes: 0 overwrite, 1 add
-  int n_mat;           // materials in the table (0: not given)
+  int n_mat;           // materials in the table
   // deterministic FP64 passes: each element's 10 x 3 results and each
   // face's 6 x 3 go here (slot-major), then every node sums its slots in
   // increasing order (null: LDS and global atomics, arrival order)
@@ -150,13 +164,14 @@ struct LaneInfo {
   int32_t done64, iters64, done32, iters32;
 };
 
-void launch_tile_lanes_f64(const TileLane<double>* lanes, const int2* work, int n_work, int max_tile_nodes,
-                           const LaneState* st, int iter, hipStream_t s);
-// FP32 CG-iteration pass of every lane, persistent and pipelined over items
-// (lane, tile) listed tile-major with a tile's lanes adjacent; tiles of at
-// most 1280 nodes.
-void launch_tile_lanes_pipe_f32(const TileLane<float>* lanes, const int2* items, int n_items, int max_tile_nodes,
-                                const LaneState* st, int iter, int grid_cap, hipStream_t s);
+// max_mat: the largest material table of the lanes; two: the passes take two
+// inputs (a1 x1 + a2 x2)
+void launch_tile_lanes_f64(const TileLane<double>* lanes, const int2* work, int n_work, int max_tile_nodes, int max_mat,
+                           bool two, const LaneState* st, hipStream_t s);
+// FP32 CG-iteration pass of every lane over items (lane, tile) listed
+// tile-major with a tile's lanes adjacent.
+void launch_tile_lanes_f32(const TileLane<float>* lanes, const int2* items, int n_items, int max_tile_nodes,
+                           int max_mat, const LaneState* st, int iter, int grid_cap, hipStream_t s);
 
 // Lane kernels (sw_kernels.hip): one launch covers every lane, grid
 // (blocks per lane, lanes); st == nullptr means every lane.
@@ -188,14 +203,14 @@ void launch_lanes_cg(bool f32, bool dir, int n_lanes, int64_t max_nodes, const L
 // fixed-order dot product; the mesh needs its incidence lists).
 void launch_tile_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                      CgCtl* ctl, int iter, hipStream_t s);
-// grid_cap > 0 limits the workgroups of the persistent FP32 pass (a multiple
-// of 8); 0 keeps three per compute unit.
+// grid_cap > 0 limits the workgroups of the pass (a multiple of 8, each then
+// walking several tiles); 0: one per tile.
 void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
                      CgCtl* ctl, int iter, int grid_cap, hipStream_t s);
 // Two-kernel CG iterations: whether a solve's iterations run so, the operator
 // pass (a.x1 = z; forms and stores p = z + beta p_old, a.y = A p) and the
 // vector kernel after it (x += alpha p, r -= alpha q, z = P r).
-bool two_kernel_cg(const MeshDev& m, int n_mat, int grid_cap, bool f32);
+bool two_kernel_cg(const MeshDev& m, int grid_cap, bool f32);
 void launch_tile_dir_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                          const double* p_old, double* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s);
 void launch_tile_dir_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
@@ -206,6 +221,8 @@ void launch_cg_step_f32(int64_t n_nodes, int64_t n_interior, int par, const __ha
                         float* q, const float* p, float* x, CgCtl* ctl, hipStream_t s);
 // FP32 element geometry for the FP32 operator (once per mesh).
 void launch_geom(const MeshDev& m, float* geo32, double* geo64, hipStream_t s);
+// conn8 and conn2 from conn_loc ([10][tet_stride], 3 x tile-local node index)
+void launch_pack_conn(const MeshDev& m, const uint16_t* conn_loc, uint4* conn8, uint32_t* conn2, hipStream_t s);
 // Diagonal 3x3 blocks (6 values per node) of cM M + cK K + cC C_abs.
 // eout / fout set: the deterministic form (two passes of three values per
 // node through the slot buffers, as launch_tile_f64).

@@ -766,12 +766,41 @@ void launch_permute_f32(int64_t n, int w, const float* src, const int32_t* map, 
 // lane's blocks run the same body as the single-case kernel on that lane's
 // vectors; lanes marked inactive return at once.
 
+// A lane's vectors as pointers to global memory (as_global).
+__device__ __forceinline__ LaneDev lane_of(const LaneDev* lanes, int l) {
+  LaneDev L = lanes[l];
+  L.u = as_global(L.u);
+  L.v = as_global(L.v);
+  L.a = as_global(L.a);
+  L.b = as_global(L.b);
+  L.x = as_global(L.x);
+  L.r = as_global(L.r);
+  L.z = as_global(L.z);
+  L.p = as_global(L.p);
+  L.q = as_global(L.q);
+  L.hist = as_global(L.hist);
+  L.pinv64 = as_global(L.pinv64);
+  L.pinv16 = as_global(L.pinv16);
+  L.r32 = as_global(L.r32);
+  L.d32 = as_global(L.d32);
+  L.z32 = as_global(L.z32);
+  L.p32 = as_global(L.p32);
+  L.q32 = as_global(L.q32);
+  L.ctl64 = as_global(L.ctl64);
+  L.ctl32 = as_global(L.ctl32);
+  L.rec = as_global(L.rec);
+  L.wave = as_global(L.wave);
+  L.log_it = as_global(L.log_it);
+  L.log_rel = as_global(L.log_rel);
+  return L;
+}
+
 template <int OP>
 __global__ __launch_bounds__(TPB) void k_lane_op(const LaneDev* __restrict__ lanes, const LaneState* __restrict__ st,
                                                  LaneInfo* __restrict__ info) {
   const int l = blockIdx.y;
   if (st != nullptr && !st[l].active) return;
-  const LaneDev& L = lanes[l];
+  const LaneDev L = lane_of(lanes, l);
   const int64_t nn = L.n_nodes, nd = 3 * nn;
   const int64_t i0 = (int64_t)blockIdx.x * TPB + threadIdx.x, stride = (int64_t)gridDim.x * TPB;
   const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
@@ -869,7 +898,7 @@ __global__ __launch_bounds__(TPB) void k_lane_cg(const LaneDev* __restrict__ lan
                                                  int iter, int dev_index) {
   const int l = blockIdx.y;
   if (!st[l].active) return;
-  const LaneDev& L = lanes[l];
+  const LaneDev L = lane_of(lanes, l);
   const int par = iter & 1;
   const int iabs = dev_index ? -1 : st[l].iter_base + iter;
   if constexpr (sizeof(T) == 4) {

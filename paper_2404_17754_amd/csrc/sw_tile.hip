@@ -17,10 +17,6 @@
 
 #include <algorithm>
 
-#ifndef SW_PIPE_PF
-#define SW_PIPE_PF false
-#endif
-
 namespace sw {
 
 // Load through the constant address space: with a uniform index this is a
@@ -32,47 +28,77 @@ __device__ __forceinline__ U ldc(const U* p, int64_t i) {
   return ((const __attribute__((address_space(4))) U*)p)[i];
 }
 
-// Input value i of a pass (x1): in the 16-bit passes of the SW_MIXED_FP16
-// inner CG it comes from the bfloat16 input x1h (x1 null).
+// A tile's LDS, all of it dynamic (so that it starts at address 0): the input
+// values in T first (an element's stored byte offsets address them as they
+// are), FP64 accumulators (LDS FP64 atomics are much faster than FP32 ones on
+// this target: 25 cycles against 192 at a tile's addresses), room for the
+// sums over the workgroup, the ids of the shared nodes, the material table.
 template <typename T>
-__device__ __forceinline__ T x1_at(const TileArgs<T>& A, int64_t i) {
-  return A.x1[i];
+__host__ __device__ constexpr size_t tile_lds_acc(int nmax) {
+  return (3 * (size_t)nmax * sizeof(T) + 7) / 8 * 8;
 }
-template <>
-__device__ __forceinline__ float x1_at<float>(const TileArgs<float>& A, int64_t i) {
-  return A.x1h ? bf16_value(A.x1h[i]) : A.x1[i];
+constexpr int TILE_SUMS = 8;  // wavefronts of the largest workgroup
+template <typename T>
+struct TileLds {
+  T* xs;
+  double *ys, *sh;
+  int32_t* gid;
+  T* matl;
+  __device__ __forceinline__ TileLds(unsigned char* smem, int nmax)
+      : xs(reinterpret_cast<T*>(smem)),
+        ys(reinterpret_cast<double*>(smem + tile_lds_acc<T>(nmax))),
+        sh(ys + 3 * nmax),
+        gid(reinterpret_cast<int32_t*>(sh + TILE_SUMS)),
+        matl(reinterpret_cast<T*>(gid + (nmax + (nmax & 1)))) {}
+};
+template <typename T>
+static size_t tile_lds(int nmax, int n_mat) {
+  return tile_lds_acc<T>(nmax) + (3 * (size_t)nmax + TILE_SUMS) * sizeof(double) +
+         (nmax + (nmax & 1)) * sizeof(int32_t) + 3 * (size_t)n_mat * sizeof(T);
 }
-// Per-element inputs fetched from global memory: tile-local connectivity
-// (stored as 3 x the local index: the offset of the node's first value in
-// the tile's 3-value-per-node LDS arrays, which saves the address
-// arithmetic), material id, and the precomputed barycentric gradients and
-// volume in the pass's precision (coalesced streams, no dependent gather).
+
+// Per-element inputs fetched from global memory in vector loads (5 in FP32,
+// 8 in FP64, and the material id): the nodes' offsets, and the precomputed
+// barycentric gradients and volume in the pass's precision (coalesced
+// streams, no dependent gather).
 template <typename T>
 struct ElemIn {
-  int ln[10];
+  uint4 c8;
+  uint32_t c2;
   T geo[10];
   int mid;
+  // offset in bytes of node k's first value in an FP32 node array
+  __device__ __forceinline__ uint32_t off(int k) const {
+    const uint32_t w = k < 2 ? c8.x : k < 4 ? c8.y : k < 6 ? c8.z : k < 8 ? c8.w : c2;
+    return k & 1 ? w >> 16 : w & 0xffffu;
+  }
 };
 
+// element i (0-based) of the tile whose elements start at eb: uniform base
+// pointers with one 32-bit offset per array
 template <typename T>
-__device__ __forceinline__ const T* geo_of(const MeshDev& m);
-template <>
-__device__ __forceinline__ const float* geo_of<float>(const MeshDev& m) {
-  return m.geo32;
-}
-template <>
-__device__ __forceinline__ const double* geo_of<double>(const MeshDev& m) {
-  return m.geo64;
-}
-
-template <typename T>
-__device__ __forceinline__ void load_elem(const MeshDev& m, const uint8_t* __restrict__ emat, int e, ElemIn<T>& o) {
-  const T* __restrict__ geo = geo_of<T>(m);
+__device__ __forceinline__ void load_elem(const MeshDev& m, const uint8_t* __restrict__ emat, int eb, uint32_t i,
+                                          ElemIn<T>& o) {
+  o.c8 = (m.conn8 + eb)[i];
+  o.c2 = (m.conn2 + eb)[i];
+  if constexpr (sizeof(T) == 4) {
+    const float4* g4 = reinterpret_cast<const float4*>(m.geo32) + eb;
+    const float2* g2 = reinterpret_cast<const float2*>(m.geo32 + 8 * m.tet_stride) + eb;
+    const float4 a = g4[i], b = (g4 + m.tet_stride)[i];
+    const float2 c = g2[i];
+    o.geo[0] = a.x, o.geo[1] = a.y, o.geo[2] = a.z, o.geo[3] = a.w;
+    o.geo[4] = b.x, o.geo[5] = b.y, o.geo[6] = b.z, o.geo[7] = b.w;
+    o.geo[8] = c.x, o.geo[9] = c.y;
+  } else {
+    const double2* g2 = reinterpret_cast<const double2*>(m.geo64) + eb;
 #pragma unroll
-  for (int k = 0; k < 10; ++k) o.ln[k] = m.conn_loc[k * m.tet_stride + e];
-#pragma unroll
-  for (int k = 0; k < 10; ++k) o.geo[k] = geo[k * m.tet_stride + e];
-  o.mid = emat[e];
+    for (int k = 0; k < 5; ++k) {
+      const double2 v = (g2 + k * m.tet_stride)[i];
+      o.geo[2 * k] = v.x;
+      o.geo[2 * k + 1] = v.y;
+    }
+  }
+  o.mid = (emat + eb)[i];
 }
 
 // g_0 = -(g_1 + g_2 + g_3), summed in the order tet_geometry uses, so the
@@ -89,71 +115,57 @@ __device__ __forceinline__ void elem_geometry(const ElemIn<T>& in, Geo<T>& G) {
   G.vol = in.geo[9];
 }
 
-// Element work of tile t on the values gathered in LDS (xs, node ids gid),
-// accumulated into ys (x.A x, which CG passes need, is taken afterwards from
-// the tile's node values: tile_scatter).  Work-item i takes the tile's
-// element i, i + NT, ...: the layout has grouped the elements of each
-// half-wavefront and numbered the tile's interior nodes so that the nodes one
-// LDS instruction reaches rarely share a bank (and rarely coincide), while
-// the element loads stay coalesced.  PF: software
-// pipeline, the next element's connectivity, geometry and material are
-// loaded before the current one is computed (FP32; in FP64 the registers
-// would halve the occupancy).  STIFF / MASS / DYN: which operator terms are
-// on, and whether each element checks its coefficients (element_apply).
-// hook() runs once, right after the first element's loads are issued (the
-// pipelined pass issues its next tile's gather there, behind them).  MATL:
-// the material constants come from an LDS copy (matl: lam, mu, rho per
-// material) rather than from global memory, a load that would wait on the
-// element's material id.  DET: each element's ten nodal results go to its
+// Element work of tile t on the values gathered in LDS, accumulated into ys
+// (x.A x, which CG passes need, is taken afterwards from the tile's node
+// values: tile_scatter).  Work-item i takes the tile's element i, i + NT,
+// ...: the layout has grouped the elements of each half-wavefront and
+// numbered the tile's interior nodes so that the nodes one LDS instruction
+// reaches rarely share a bank (and rarely coincide), while the element loads
+// stay coalesced.  PF: the next element's data are loaded before the current
+// one is computed (FP32; in FP64 the registers would halve the occupancy).
+// STIFF / MASS / DYN: which operator terms are on, and whether each element
+// checks its coefficients (element_apply).  hook() runs once, right after the
+// first element's loads are issued: the gather of the tile's values, with the
+// barrier that ends it.  DET: each element's ten nodal results go to its
 // slots of A.eout instead of the LDS accumulator.
-template <typename T, int NT, bool PF, bool STIFF, bool MASS, bool DYN, bool MATL, bool DET, typename Hook>
+template <typename T, int NT, bool PF, bool STIFF, bool MASS, bool DYN, bool DET, typename Hook>
 __device__ __forceinline__ void tile_element_loop(const MeshDev& m, const uint8_t* __restrict__ emat,
-                                                  const MatDev* __restrict__ mats, const T* matl,
-                                                  const TileArgs<T>& A, int t, const int32_t* gid, const T* xs,
-                                                  double* ys, Hook&& hook) {
+                                                  const TileArgs<T>& A, int t, const TileLds<T>& lds, Hook&& hook) {
+  const T* xs = lds.xs;
+  double* ys = lds.ys;
+  const T* matl = lds.matl;
   const int eb = ldc(m.tile_elem_off, t);
   const int n_e = ldc(m.tile_elem_off, t + 1) - eb;
-  auto elem_of = [&](int i) { return eb + i; };
   ElemIn<T> nx;
   int i = threadIdx.x;
-  if (i < n_e) load_elem<T>(m, emat, elem_of(i), nx);
+  if (i < n_e) load_elem<T>(m, emat, eb, i, nx);
   hook();
-  constexpr bool kPrefetch = PF;
   for (; i < n_e; i += NT) {
-    if (!kPrefetch && i != (int)threadIdx.x) load_elem<T>(m, emat, elem_of(i), nx);
+    if (!PF && i != (int)threadIdx.x) load_elem<T>(m, emat, eb, i, nx);
     const ElemIn<T> cur = nx;
-    if (kPrefetch && i + NT < n_e) load_elem<T>(m, emat, elem_of(i + NT), nx);
-    const int* ln = cur.ln;
+    if (PF && i + NT < n_e) load_elem<T>(m, emat, eb, i + NT, nx);
     Geo<T> G;
     elem_geometry(cur, G);
-    T lam, mu, rho;
-    if constexpr (MATL) {
-      lam = matl[3 * cur.mid];
-      mu = matl[3 * cur.mid + 1];
-      rho = matl[3 * cur.mid + 2];
-    } else {
-      const MatDev& mt = mats[cur.mid];
-      lam = (T)mt.lam;
-      mu = (T)mt.mu;
-      rho = (T)mt.rho;
-    }
+    const T lam = matl[3 * cur.mid], mu = matl[3 * cur.mid + 1], rho = matl[3 * cur.mid + 2];
     T w[10][3];
 #pragma unroll
     for (int k = 0; k < 10; ++k) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) w[k][c] = xs[ln[k] + c];
+      for (int c = 0; c < 3; ++c)
+        w[k][c] = reinterpret_cast<const T*>(reinterpret_cast<const char*>(xs) + cur.off(k) * (sizeof(T) / 4))[c];
     }
     // each node's force goes to the LDS accumulator as soon as it is
     // complete (no 30-value force array held in registers)
     element_apply<T, STIFF, MASS, DYN>(G, lam, mu, A.sK, A.sM * rho * G.vol, w,
                                   [&](int k, T f0, T f1, T f2) {
                                     if constexpr (DET) {
-                                      double* eo = A.eout + (size_t)elem_of(i) * 30 + 3 * k;
+                                      double* eo = A.eout + (size_t)(eb + i) * 30 + 3 * k;
                                       eo[0] = (double)f0;
                                       eo[1] = (double)f1;
                                       eo[2] = (double)f2;
                                     } else {
-                                      double* yk = &ys[ln[k]];
+                                      double* yk = reinterpret_cast<double*>(reinterpret_cast<char*>(ys) +
+                                                                             2 * cur.off(k));
                                       atomicAdd(yk, (double)f0);
                                       atomicAdd(yk + 1, (double)f1);
                                       atomicAdd(yk + 2, (double)f2);
@@ -162,35 +174,14 @@ __device__ __forceinline__ void tile_element_loop(const MeshDev& m, const uint8_
   }
 }
 
-// Element and face work of tile t (see tile_element_loop), plus the
-// boundary faces owned by the tile's elements (DET: their results to the
-// face slots of A.fout).
-template <typename T, int NT, bool PF, bool MATL, bool DET, typename Hook>
-__device__ __forceinline__ void tile_elements(const MeshDev& m, const uint8_t* __restrict__ emat,
-                                              const MatDev* __restrict__ mats, const T* matl,
-                                              const TileArgs<T>& A, int t, const int32_t* gid, const T* xs,
-                                              double* ys, Hook&& hook) {
-  if constexpr (sizeof(T) == 8) {
-    // FP64: per-element checks (the branch-free form needs more registers
-    // than the FP64 passes can spare; measured slower)
-    if (A.sK != (T)0 || A.sM != (T)0)
-      tile_element_loop<T, NT, PF, true, true, true, MATL, DET>(m, emat, mats, matl, A, t, gid, xs, ys,
-                                                                        hook);
-    else
-      hook();
-  } else {
-    if (A.sK != (T)0 && A.sM != (T)0)
-      tile_element_loop<T, NT, PF, true, true, false, MATL, false>(m, emat, mats, matl, A, t, gid, xs, ys,
-                                                                           hook);
-    else if (A.sK != (T)0)
-      tile_element_loop<T, NT, PF, true, false, false, MATL, false>(m, emat, mats, matl, A, t, gid, xs, ys,
-                                                                            hook);
-    else if (A.sM != (T)0)
-      tile_element_loop<T, NT, PF, false, true, false, MATL, false>(m, emat, mats, matl, A, t, gid, xs, ys,
-                                                                            hook);
-    else
-      hook();
-  }
+// The boundary faces owned by the elements of tile t (DET: their results to
+// the face slots of A.fout).
+template <typename T, int NT, bool DET>
+__device__ __forceinline__ void tile_faces(const MeshDev& m, const uint8_t* __restrict__ emat,
+                                           const MatDev* __restrict__ mats, const TileArgs<T>& A, int t,
+                                           const TileLds<T>& lds) {
+  const T* xs = lds.xs;
+  double* ys = lds.ys;
   if (A.sC != (T)0 || A.vin != nullptr) {
     const int f1 = ldc(m.tile_face_off, t + 1);
     for (int f = ldc(m.tile_face_off, t) + threadIdx.x; f < f1; f += NT) {
@@ -214,10 +205,18 @@ __device__ __forceinline__ void tile_elements(const MeshDev& m, const uint8_t* _
       for (int k = 0; k < 6; ++k) out[k][0] = out[k][1] = out[k][2] = (T)0;
       if (A.sC != (T)0) {
         T w[6][3];
+        if (A.xf != nullptr) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
+          for (int k = 0; k < 6; ++k)
 #pragma unroll
-          for (int c = 0; c < 3; ++c) w[k][c] = A.xf ? A.xf[3 * gn[k] + c] : xs[3 * ln[k] + c];
+            for (int c = 0; c < 3; ++c) w[k][c] = A.xf[3 * gn[k] + c];
+        } else {
+          // as LDS accesses (merged with the branch above they become flat ones)
+          const auto* xl = (const __attribute__((address_space(3))) T*)xs;
+#pragma unroll
+          for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) w[k][c] = xl[3 * ln[k] + c];
         }
         const T n[3] = {(T)g.n[0], (T)g.n[1], (T)g.n[2]};
         face_dashpot_apply<T>(n, (T)g.area, (T)mt.zp, (T)mt.zs, A.sC, w, out);
@@ -252,11 +251,24 @@ __device__ __forceinline__ void tile_elements(const MeshDev& m, const uint8_t* _
   }
 }
 
-template <typename T, int NT, bool PF>
+// Which terms a pass has, fixed at compile time where that pays: TERMS_A the
+// stiffness and the mass (CG passes, FP32: no per-node branches), TERMS_ANY
+// checked per element (FP64, where the branch-free form needs more registers
+// than the passes can spare).
+enum { TERMS_ANY = 0, TERMS_A = 1 };
+
+// Element and face work of tile t.
+template <typename T, int NT, bool PF, int TERMS, bool DET, typename Hook>
 __device__ __forceinline__ void tile_elements(const MeshDev& m, const uint8_t* __restrict__ emat,
                                               const MatDev* __restrict__ mats, const TileArgs<T>& A, int t,
-                                              const int32_t* gid, const T* xs, double* ys) {
-  tile_elements<T, NT, PF, false, false>(m, emat, mats, nullptr, A, t, gid, xs, ys, [] {});
+                                              const TileLds<T>& lds, Hook&& hook) {
+  if constexpr (TERMS == TERMS_A)
+    tile_element_loop<T, NT, PF, true, true, false, DET>(m, emat, A, t, lds, hook);
+  else if (A.sK != (T)0 || A.sM != (T)0)
+    tile_element_loop<T, NT, PF, true, true, true, DET>(m, emat, A, t, lds, hook);
+  else
+    hook();
+  tile_faces<T, NT, DET>(m, emat, mats, A, t, lds);
 }
 
 // Results of tile t: interior nodes (one contiguous range) with plain
@@ -266,8 +278,10 @@ __device__ __forceinline__ void tile_elements(const MeshDev& m, const uint8_t* _
 // is x.A x (a node's full value is the sum of its tiles' partials), with one
 // product per node value instead of one per element entry.
 template <typename T, int NT>
-__device__ __forceinline__ double tile_scatter(const MeshDev& m, const TileArgs<T>& A, int t, const int32_t* gid,
-                                               const T* xs, const double* ys) {
+__device__ __forceinline__ double tile_scatter(const MeshDev& m, const TileArgs<T>& A, int t,
+                                               const TileLds<T>& lds) {
+  const T* xs = lds.xs;
+  const double* ys = lds.ys;
   const int nt = ldc(m.tile_node_off, t + 1) - ldc(m.tile_node_off, t);
   const int nint = ldc(m.tile_nint, t);
   const int64_t ib3 = 3 * (int64_t)ldc(m.tile_int_base, t);
@@ -286,87 +300,162 @@ __device__ __forceinline__ double tile_scatter(const MeshDev& m, const TileArgs<
     const int j = k / 3;
     const double v = ys[k];
     energy += (double)xs[k] * v;
-    atomic_add(&y[3 * (int64_t)gid[j] + (k - 3 * j)], (T)v);
+    atomic_add(&y[3 * (int64_t)lds.gid[j] + (k - 3 * j)], (T)v);
   }
   return energy;
 }
 
-// One workgroup's share of an operator pass: tile t of mesh m.  smem_raw is
-// the dynamic LDS (sized for m.max_tile_nodes), sh NT/64 doubles.  DET: the
-// element and face results go to their slots (no scatter, no energy; the
-// node pass and a fixed-order dot product follow).
-template <typename T, int NT, bool DET = false>
-__device__ __forceinline__ void tile_body(const MeshDev& m, const uint8_t* __restrict__ emat,
-                                          const MatDev* __restrict__ mats, const TileArgs<T>& A, CgCtl* ctl,
-                                          int iter, int t, unsigned char* smem_raw, double* sh) {
-  // LDS: FP64 accumulators (LDS FP64 atomics are much faster than FP32 ones
-  // on this target), then the tile's input values in T
-  double* ys = reinterpret_cast<double*>(smem_raw);
-  int32_t* gid = reinterpret_cast<int32_t*>(ys + 3 * m.max_tile_nodes);
-  T* xs = reinterpret_cast<T*>(gid + m.max_tile_nodes + (m.max_tile_nodes & 1));
-  // CG-iteration protocol: exit when the solve is done; on the first
-  // iteration end a solve whose initial residual meets the tolerance; the
-  // workgroup of tile 0 clears the scalar slots the next update kernel
-  // accumulates into.
+// A tile's nodes, NPT per work-item: the interior ones are one contiguous
+// range of ids, the shared ones come from the tile's node list.  A work-item
+// past the last node holds node 0 (a valid address, loaded and unused).
+template <int NT, int NPT>
+struct TileNodes {
+  int nt, nint;
+  int32_t g[NPT];
+  __device__ __forceinline__ void load(const MeshDev& m, int t) {
+    const int n0 = ldc(m.tile_node_off, t);
+    nt = ldc(m.tile_node_off, t + 1) - n0;
+    nint = ldc(m.tile_nint, t);
+    const int ib = ldc(m.tile_int_base, t);
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int j = threadIdx.x + q * NT;
+      g[q] = j < nint ? ib + j : 0;
+      if (j >= nint && j < nt) g[q] = m.tile_nodes[n0 + j];
+    }
+  }
+};
+// Work-items 256 take five nodes each, 512 three: the largest tile.
+template <int NT>
+constexpr int tile_npt() {
+  return (TILE_MAX_NODES + NT - 1) / NT;
+}
+
+// The material table (lam, mu, rho per material), rounded to T, into LDS: a
+// load from global memory would wait on the element's material id.
+// The first NT values are loaded (mat_load) well before they are stored.
+__device__ __forceinline__ double mat_load(const MatDev* __restrict__ mats, int n_mat, int i) {
+  return i < 3 * n_mat ? (&mats[i / 3].lam)[i % 3] : 0.0;
+}
+template <typename T, int NT>
+__device__ __forceinline__ void mat_store(const MatDev* __restrict__ mats, int n_mat, double first, T* matl) {
+  if ((int)threadIdx.x < 3 * n_mat) matl[threadIdx.x] = (T)first;
+  for (int i = threadIdx.x + NT; i < 3 * n_mat; i += NT) matl[i] = (T)mat_load(mats, n_mat, i);
+}
+
+// Input of a pass: x1; a1 x1 + a2 x2; x1 in bfloat16 (x1h).
+enum { IN_ONE = 0, IN_TWO = 1, IN_BF16 = 2 };
+
+template <typename T, int NT, int IN, int NPT>
+__device__ __forceinline__ void tile_gather(const TileArgs<T>& A, const TileNodes<NT, NPT>& N,
+                                            const TileLds<T>& lds) {
+  // every load before the first is waited for: one memory latency a tile
+  T v[NPT][3], u[IN == IN_TWO ? NPT : 1][3];
+#pragma unroll
+  for (int q = 0; q < NPT; ++q) {
+    const int64_t g3 = 3 * (int64_t)N.g[q];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if constexpr (IN == IN_BF16)
+        v[q][c] = bf16_value(A.x1h[g3 + c]);
+      else
+        v[q][c] = A.x1[g3 + c];
+      if constexpr (IN == IN_TWO) u[q][c] = A.x2[g3 + c];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NPT; ++q) {
+    const int j = threadIdx.x + q * NT;
+    if (j < N.nt) {
+      lds.gid[j] = N.g[q];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if constexpr (IN == IN_TWO) v[q][c] = A.a1 * v[q][c] + A.a2 * u[q][c];
+        lds.xs[3 * j + c] = v[q][c];
+        lds.ys[3 * j + c] = 0.0;
+      }
+    }
+  }
+}
+
+// One tile of an operator pass; returns the work-item's share of x.A x.
+// DET: the element and face results go to their slots (no scatter, no energy;
+// the node pass and a fixed-order dot product follow).
+template <typename T, int NT, int IN, int TERMS, bool DET>
+__device__ __forceinline__ double tile_body(const MeshDev& m, const uint8_t* __restrict__ emat,
+                                            const MatDev* __restrict__ mats, const TileArgs<T>& A, int t,
+                                            const TileLds<T>& lds) {
+  TileNodes<NT, tile_npt<NT>()> N;
+  N.load(m, t);
+  const double mat = mat_load(mats, A.n_mat, threadIdx.x);
+  tile_elements<T, NT, sizeof(T) == 4, TERMS, DET>(m, emat, mats, A, t, lds, [&] {
+    mat_store<T, NT>(mats, A.n_mat, mat, lds.matl);
+    tile_gather<T, NT, IN>(A, N, lds);
+    __syncthreads();
+  });
+  if constexpr (DET) return 0.0;
+  __syncthreads();
+  return tile_scatter<T, NT>(m, A, t, lds);
+}
+
+// Share of n tiles (or work items) of workgroup b: XCD x = b mod 8
+// (workgroups are dealt to the 8 XCDs round-robin) takes the contiguous
+// eighth [lo, hi), so that neighbouring tiles, which share nodes, meet in one
+// L2; this workgroup the items lo + first, + step, ...
+struct XcdShare {
+  int at, hi, step;
+  __device__ __forceinline__ explicit XcdShare(int n) {
+    const int xcd = blockIdx.x & 7;
+    at = (int)(((int64_t)n * xcd) >> 3) + (int)(blockIdx.x >> 3);
+    hi = (int)(((int64_t)n * (xcd + 1)) >> 3);
+    step = gridDim.x >> 3;
+  }
+};
+
+// Operator pass of one case.  iter >= 0: as part of CG iteration `iter` (x.A x
+// into ctl->pAp[0]; nothing when the solve is done; the first iteration ends
+// a solve whose residual meets the tolerance; the first workgroup clears the
+// scalar slots the next update kernel accumulates into).
+// FP32, 9.6 M tets: 326 us (1.2 GB moved: 3.7 TB/s).  The vector units issue
+// 65 % of the time, the LDS is busy 58 % (three quarters of that the FP64
+// atomics), so what is left is latency that three wavefronts per SIMD (LDS: 46
+// KB a tile) do not cover.  With the element data in single words and the
+// next tile's values loaded behind the elements of the one before it took
+// 347 us; that pipeline costs 40 registers, which now hold the next
+// element's data.  FP64: 867 us a pass with the values gathered one after the
+// other, 620 with every load issued before the first is waited for.
+// LOOP: a workgroup walks several tiles (a capped grid), else it has one.
+template <typename T, int NT, int IN, int TERMS, bool DET, bool LOOP>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2))) void k_tile(
+    MeshDev m, const uint8_t* __restrict__ emat, const MatDev* __restrict__ mats, TileArgs<T> A, CgCtl* ctl,
+    int iter) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const TileLds<T> lds(smem_raw, m.max_tile_nodes);
   if (iter >= 0) {
     const int par = iter & 1;
     if (ctl->done) return;
     if (iter == 0 && slot_sum<NSLOT>(ctl->rr[0]) <= ctl->tol2) {
-      if (t == 0 && threadIdx.x == 0) ctl->done = 1;
+      if (blockIdx.x == 0 && threadIdx.x == 0) ctl->done = 1;
       return;
     }
-    if (t == 0 && threadIdx.x < NSLOT) {
+    if (blockIdx.x == 0 && threadIdx.x < NSLOT) {
       ctl->rz[par ^ 1][threadIdx.x] = 0.0;
       ctl->rr[par ^ 1][threadIdx.x] = 0.0;
     }
   }
-  const int n0 = ldc(m.tile_node_off, t);
-  const int nt = ldc(m.tile_node_off, t + 1) - n0;
-  const int nint = ldc(m.tile_nint, t);
-  const int64_t ib3 = 3 * (int64_t)ldc(m.tile_int_base, t);
-
-  // gather xe = a1 x1 + a2 x2 for the tile's nodes and clear the
-  // accumulator, issued behind the first element's loads (the hook of
-  // tile_elements): the interior nodes are one contiguous range; the shared
-  // ones take their ids from the tile's node list (kept in LDS for the
-  // scatter)
-  auto gather = [&] {
-    for (int k = threadIdx.x; k < 3 * nint; k += NT) {
-      T v = A.a1 * x1_at(A, ib3 + k);
-      if (A.x2 != nullptr) v += A.a2 * A.x2[ib3 + k];
-      xs[k] = v;
-      ys[k] = 0.0;
+  const XcdShare share(m.n_tiles);
+  if (share.at >= share.hi) return;
+  double energy = tile_body<T, NT, IN, TERMS, DET>(m, emat, mats, A, share.at, lds);
+  if constexpr (LOOP) {
+    for (int t = share.at + share.step; t < share.hi; t += share.step) {
+      __syncthreads();
+      energy += tile_body<T, NT, IN, TERMS, DET>(m, emat, mats, A, t, lds);
     }
-    for (int j = nint + threadIdx.x; j < nt; j += NT) {
-      const int32_t g = m.tile_nodes[n0 + j];
-      gid[j] = g;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const int64_t gi = 3 * (int64_t)g + c;
-        T v = A.a1 * x1_at(A, gi);
-        if (A.x2 != nullptr) v += A.a2 * A.x2[gi];
-        xs[3 * j + c] = v;
-        ys[3 * j + c] = 0.0;
-      }
-    }
-    __syncthreads();
-  };
-  tile_elements<T, NT, sizeof(T) == 4, false, DET>(m, emat, mats, nullptr, A, t, gid, xs, ys, gather);
-  if constexpr (DET) return;
-  __syncthreads();
-  const double energy = tile_scatter<T, NT>(m, A, t, gid, xs, ys);
-  if (iter >= 0) {
-    const double s = block_sum_n<NT>(energy, sh);
-    if (threadIdx.x == 0) atomic_add(&ctl->pAp[0][t % NSLOT], s);
   }
-}
-
-template <typename T, int NT, bool DET = false>
-__global__ __launch_bounds__(NT) void k_tile(MeshDev m, const uint8_t* __restrict__ emat,
-                                              const MatDev* __restrict__ mats, TileArgs<T> A, CgCtl* ctl, int iter) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double sh[NT / 64];
-  tile_body<T, NT, DET>(m, emat, mats, A, ctl, iter, blockIdx.x, smem_raw, sh);
+  if (!DET && iter >= 0) {
+    const double s = block_sum_n<NT>(energy, lds.sh);
+    if (threadIdx.x == 0) atomic_add(&ctl->pAp[0][blockIdx.x % NSLOT], s);
+  }
 }
 
 // Deterministic node pass: y[ystride * i + yoff + c] (= or +=) the sum over
@@ -413,24 +502,92 @@ __global__ __launch_bounds__(TPB) void k_dot_slots(int64_t n, const double* __re
   if (threadIdx.x == 0) slots[blockIdx.x] = acc;
 }
 
+// A lane's tables and vectors as pointers to global memory (as_global).
+template <typename T>
+__device__ __forceinline__ TileLane<T> lane_of(const TileLane<T>* lanes, int l) {
+  TileLane<T> L = lanes[l];
+  L.m.conn8 = as_global(L.m.conn8);
+  L.m.conn2 = as_global(L.m.conn2);
+  L.m.tile_elem_off = as_global(L.m.tile_elem_off);
+  L.m.tile_node_off = as_global(L.m.tile_node_off);
+  L.m.tile_nodes = as_global(L.m.tile_nodes);
+  L.m.tile_int_base = as_global(L.m.tile_int_base);
+  L.m.tile_nint = as_global(L.m.tile_nint);
+  L.m.tile_face_off = as_global(L.m.tile_face_off);
+  L.m.xyz = as_global(L.m.xyz);
+  L.m.geo32 = as_global(L.m.geo32);
+  L.m.geo64 = as_global(L.m.geo64);
+  L.m.fconn = as_global(L.m.fconn);
+  L.m.fconn_loc = as_global(L.m.fconn_loc);
+  L.m.face_elem = as_global(L.m.face_elem);
+  L.m.face_role = as_global(L.m.face_role);
+  L.emat = as_global(L.emat);
+  L.mats = as_global(L.mats);
+  L.A.x1 = as_global(L.A.x1);
+  L.A.x2 = as_global(L.A.x2);
+  L.A.xf = as_global(L.A.xf);
+  L.A.vin = as_global(L.A.vin);
+  L.A.y = as_global(L.A.y);
+  L.ctl = as_global(L.ctl);
+  return L;
+}
+
 // The same pass for several cases (lanes) in one launch: work item b is
 // (lane, tile) = work[b] (lane < 0: padding), lanes whose state is inactive
 // return at once.
-template <typename T, int NT>
+template <typename T, int NT, int IN>
 __global__ __launch_bounds__(NT) void k_tile_lanes(const TileLane<T>* __restrict__ lanes,
                                                     const int2* __restrict__ work,
-                                                    const LaneState* __restrict__ st, int iter) {
+                                                    const LaneState* __restrict__ st) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double sh[NT / 64];
   const int2 w = work[blockIdx.x];
   if (w.x < 0) return;
   if (st != nullptr && !st[w.x].active) return;
-  const TileLane<T>& L = lanes[w.x];
-  tile_body<T, NT>(L.m, L.emat, L.mats, L.A, L.ctl, iter, w.y, smem_raw, sh);
+  const TileLane<T> L = lane_of(lanes, w.x);
+  const TileLds<T> lds(smem_raw, L.m.max_tile_nodes);
+  tile_body<T, NT, IN, TERMS_ANY, false>(L.m, L.emat, L.mats, L.A, w.y, lds);
 }
 
-// Largest material table the CG passes copy into LDS.
-constexpr int PIPE_MATS = 32;
+// FP32 operator pass of a CG iteration over the (lane, tile) items of several
+// cases: items[k] = (lane, tile), tile-major with the lanes of a tile
+// adjacent (they share the tile's mesh data through L2).  An item is skipped
+// when its lane is inactive or its solve is done (or, on the first iteration,
+// already converged): every workgroup evaluates the same condition, so a
+// skipped lane's output is left untouched; the workgroup of the tile-0 item
+// marks an already converged lane done, and else clears the slots the lane's
+// next update kernel accumulates into.  nmax: the largest tile over the lanes
+// (LDS layout).
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_tile_lanes_cg(
+    const TileLane<float>* __restrict__ lanes, const int2* __restrict__ items, int n_items, int nmax,
+    const LaneState* __restrict__ st, int iter) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const TileLds<float> lds(smem_raw, nmax);
+  const int par = iter & 1;
+  XcdShare share(n_items);
+  for (int k = share.at; k < share.hi; k += share.step) {
+    // the same in every lane of the workgroup: readfirstlane tells the
+    // compiler so, which keeps the lane's pointers in scalar registers
+    const int2 item = items[k];
+    const int l = __builtin_amdgcn_readfirstlane(item.x), t = __builtin_amdgcn_readfirstlane(item.y);
+    if (st != nullptr && !st[l].active) continue;
+    const TileLane<float> L = lane_of(lanes, l);
+    CgCtl* c = L.ctl;
+    if (c->done) continue;
+    if (iter == 0 && slot_sum<NSLOT>(c->rr[0]) <= c->tol2) {
+      if (t == 0 && threadIdx.x == 0) c->done = 1;
+      continue;
+    }
+    if (t == 0 && threadIdx.x < NSLOT) {
+      c->rz[par ^ 1][threadIdx.x] = 0.0;
+      c->rr[par ^ 1][threadIdx.x] = 0.0;
+    }
+    const double energy = tile_body<float, NT, IN_ONE, TERMS_A, false>(L.m, L.emat, L.mats, L.A, t, lds);
+    const double e = block_sum_n<NT>(energy, lds.sh);
+    if (threadIdx.x == 0) atomic_add(&c->pAp[0][t % NSLOT], e);
+    __syncthreads();
+  }
+}
 
 // Operator pass of a two-kernel CG iteration (k_cg_step follows it), bound by
 // latency: its chain is launch, control block and node ids (1.4 us), the
@@ -442,37 +599,23 @@ constexpr int PIPE_MATS = 32;
 // neighbouring tiles still read p_old; a tile stores its interior nodes and
 // the shared nodes no earlier tile touches (tile_own_base).
 // par: the iteration's parity; first: the solve's first iteration (p = z).
-template <typename T, int NT, int NPT, int WPE>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void k_tile_dir(MeshDev m, const uint8_t* __restrict__ emat,
-                                                 const MatDev* __restrict__ mats, TileArgs<T> A,
-                                                 const T* __restrict__ p_old, T* __restrict__ p, CgCtl* ctl, int par,
-                                                 int first, int max_iter) {
+template <typename T, int NT, int WPE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void k_tile_dir(
+    MeshDev m, const uint8_t* __restrict__ emat, const MatDev* __restrict__ mats, TileArgs<T> A,
+    const T* __restrict__ p_old, T* __restrict__ p, CgCtl* ctl, int par, int first, int max_iter) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double sh[NT / 64];
-  __shared__ T matl[3 * PIPE_MATS];
-  double* ys = reinterpret_cast<double*>(smem_raw);
-  int32_t* gid = reinterpret_cast<int32_t*>(ys + 3 * m.max_tile_nodes);
-  T* xs = reinterpret_cast<T*>(gid + m.max_tile_nodes + (m.max_tile_nodes & 1));
-  // workgroup b runs on XCD b mod 8: each XCD takes a contiguous eighth of
-  // the tiles, so neighbours, which share nodes, meet in one L2
-  const int xcd = blockIdx.x & 7;
-  const int hi = (int)(((int64_t)m.n_tiles * (xcd + 1)) >> 3);
-  const int t = (int)(((int64_t)m.n_tiles * xcd) >> 3) + (int)(blockIdx.x >> 3);
-  const bool lead = blockIdx.x == 0;
-  // every load of the gather goes out before the first is waited for
-  const int n0 = t < hi ? ldc(m.tile_node_off, t) : 0;
-  const int nt = t < hi ? ldc(m.tile_node_off, t + 1) - n0 : 0;
-  const int nint = t < hi ? ldc(m.tile_nint, t) : 0;
-  const int own = t < hi ? ldc(m.tile_own_base, t) : 0;
-  int32_t g[NPT];
-#pragma unroll
-  for (int q = 0; q < NPT; ++q) {
-    const int j = threadIdx.x + q * NT;
-    g[q] = j < nt ? m.tile_nodes[n0 + j] : 0;
+  const TileLds<T> lds(smem_raw, m.max_tile_nodes);
+  constexpr int NPT = tile_npt<NT>();
+  const XcdShare share(m.n_tiles);
+  const int t = share.at;
+  const bool lead = blockIdx.x == 0, has_tile = t < share.hi;
+  TileNodes<NT, NPT> N;
+  int own = 0;
+  if (has_tile) {
+    N.load(m, t);
+    own = ldc(m.tile_own_base, t);
   }
-  // material constants (lam, mu, rho) of one entry per work-item, for the LDS copy
-  const bool has_mat = (int)threadIdx.x < 3 * A.n_mat;
-  const double mat = has_mat ? (&mats[threadIdx.x / 3].lam)[threadIdx.x % 3] : 0.0;
+  const double mat = mat_load(mats, A.n_mat, threadIdx.x);
   // the previous iteration's residual decides whether this one runs: the
   // same test in every workgroup, on values no workgroup of this launch writes
   const double tol2 = ctl->tol2, rz_prev = ctl->rz_prev;
@@ -490,21 +633,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     ctl->rz[par ^ 1][threadIdx.x] = 0.0;
     ctl->rr[par ^ 1][threadIdx.x] = 0.0;
   }
-  if (t >= hi) return;
+  if (!has_tile) return;
   const T* __restrict__ z = A.x1;
   auto gather = [&] {
+    mat_store<T, NT>(mats, A.n_mat, mat, lds.matl);
     T zv[NPT][3], pv[NPT][3];
-    if (has_mat) matl[threadIdx.x] = (T)mat;
 #pragma unroll
     for (int q = 0; q < NPT; ++q) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) zv[q][c] = z[3 * (int64_t)g[q] + c];
+      for (int c = 0; c < 3; ++c) zv[q][c] = z[3 * (int64_t)N.g[q] + c];
     }
     if (!first) {
 #pragma unroll
       for (int q = 0; q < NPT; ++q) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) pv[q][c] = p_old[3 * (int64_t)g[q] + c];
+        for (int c = 0; c < 3; ++c) pv[q][c] = p_old[3 * (int64_t)N.g[q] + c];
       }
     } else {
 #pragma unroll
@@ -513,327 +656,49 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
 #pragma unroll
     for (int q = 0; q < NPT; ++q) {
       const int j = threadIdx.x + q * NT;
-      if (j < nt) {
-        gid[j] = g[q];
+      if (j < N.nt) {
+        lds.gid[j] = N.g[q];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           const T v = zv[q][c] + beta * pv[q][c];
-          xs[3 * j + c] = v;
-          ys[3 * j + c] = 0.0;
-          if (j < nint || g[q] >= own) p[3 * (int64_t)g[q] + c] = v;
+          lds.xs[3 * j + c] = v;
+          lds.ys[3 * j + c] = 0.0;
+          if (j < N.nint || N.g[q] >= own) p[3 * (int64_t)N.g[q] + c] = v;
         }
       }
     }
     __syncthreads();
   };
-  tile_elements<T, NT, false, true, false>(m, emat, mats, matl, A, t, gid, xs, ys, gather);
+  tile_elements<T, NT, sizeof(T) == 4 && NT == 256, sizeof(T) == 4 ? TERMS_A : TERMS_ANY, false>(m, emat, mats, A, t,
+                                                                                                lds, gather);
   __syncthreads();
-  const double energy = tile_scatter<T, NT>(m, A, t, gid, xs, ys);
-  const double e = block_sum_n<NT>(energy, sh);
+  const double energy = tile_scatter<T, NT>(m, A, t, lds);
+  const double e = block_sum_n<NT>(energy, lds.sh);
   if (threadIdx.x == 0) atomic_add(&ctl->pAp[par][t % NSLOT], e);
 }
 
-// FP32 operator pass of a CG iteration (input scaled by 1, no second input),
-// persistent and software-pipelined.  Each workgroup walks a run of tiles;
-// while it computes tile t it already loads the input values of its next
-// tile into registers (node by node, 12 contiguous bytes per node), so a
-// tile's gather latency hides behind the element work of the one before.
-// Order of the loads, since a wait for a vector load also waits for every
-// older one: the node ids of tile t+1 are loaded at the end of tile t-1;
-// tile t's first element data goes out before the values of tile t+1, so
-// the element work waits only for its own data; per-tile offsets and counts
-// are scalar loads; the material constants come from an LDS copy.
-// XCD-aware: workgroup b runs on XCD b mod 8 (workgroups are dealt to the 8
-// XCDs round-robin) and takes its tiles from that XCD's contiguous eighth of
-// the tile list, so neighbouring tiles, which share nodes, meet in the same
-// L2.  NPT * NT must cover the largest tile; at most PIPE_MATS materials.
-template <int NT, int NPT, bool PF, bool H16 = false>
-__global__ __launch_bounds__(NT) void k_tile_pipe(MeshDev m, const uint8_t* __restrict__ emat,
-                                                   const MatDev* __restrict__ mats, TileArgs<float> A, CgCtl* ctl,
-                                                   int iter) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double sh[NT / 64];
-  double* ys = reinterpret_cast<double*>(smem_raw);
-  int32_t* gid = reinterpret_cast<int32_t*>(ys + 3 * m.max_tile_nodes);
-  float* xs = reinterpret_cast<float*>(gid + m.max_tile_nodes + (m.max_tile_nodes & 1));
-  // CG-iteration protocol (as in tile_body; workgroup 0 leads)
-  const int par = iter & 1;
-  if (ctl->done) return;
-  if (iter == 0 && slot_sum<NSLOT>(ctl->rr[0]) <= ctl->tol2) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->done = 1;
-    return;
-  }
-  if (blockIdx.x == 0 && threadIdx.x < NSLOT) {
-    ctl->rz[par ^ 1][threadIdx.x] = 0.0;
-    ctl->rr[par ^ 1][threadIdx.x] = 0.0;
-  }
-  const int xcd = blockIdx.x & 7, slots = gridDim.x >> 3, slot = blockIdx.x >> 3;
-  const int lo = (int)(((int64_t)m.n_tiles * xcd) >> 3);
-  const int hi = (int)(((int64_t)m.n_tiles * (xcd + 1)) >> 3);
-  int t = lo + slot;
-  if (t >= hi) return;
-  // the input: FP32, or bfloat16 (H16: the 16-bit passes)
-  const float* __restrict__ x = A.x1;
-  const uint16_t* __restrict__ xh = A.x1h;
-  auto in = [&](int64_t i) -> float {
-    if constexpr (H16)
-      return bf16_value(xh[i]);
-    else
-      return x[i];
-  };
-  // the material table, rounded to FP32, into LDS
-  __shared__ float matl[3 * PIPE_MATS];
-  for (int i = threadIdx.x; i < A.n_mat; i += NT) {
-    matl[3 * i] = (float)mats[i].lam;
-    matl[3 * i + 1] = (float)mats[i].mu;
-    matl[3 * i + 2] = (float)mats[i].rho;
-  }
-  {
-    // first tile: node ids and values straight into LDS
-    const int n0 = ldc(m.tile_node_off, t), nt = ldc(m.tile_node_off, t + 1) - n0;
-    for (int j = threadIdx.x; j < nt; j += NT) {
-      const int32_t g = m.tile_nodes[n0 + j];
-      gid[j] = g;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        xs[3 * j + c] = in(3 * (int64_t)g + c);
-        ys[3 * j + c] = 0.0;
-      }
-    }
-  }
-  // node ids of tile tn (0 past the tile: a valid index, loaded and unused)
-  int32_t pg[NPT];
-  auto load_ids = [&](int tn, int& ntn) {
-    ntn = 0;
-    int n0 = 0;
-    if (tn < hi) {
-      n0 = ldc(m.tile_node_off, tn);
-      ntn = ldc(m.tile_node_off, tn + 1) - n0;
-    }
-#pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-      const int j = threadIdx.x + q * NT;
-      pg[q] = j < ntn ? m.tile_nodes[n0 + j] : 0;
-    }
-  };
-  int ntn;
-  load_ids(t + slots, ntn);
-  __syncthreads();
-  double energy = 0.0;
-  for (;;) {
-    const int tn = t + slots;
-    const bool more = tn < hi;
-    // the next tile's values: loaded behind the first element's loads, so
-    // that the element work waits only for its own data
-    float px[NPT][3];
-    auto gather_next = [&] {
-#pragma unroll
-      for (int q = 0; q < NPT; ++q) {
-        const int64_t g3 = 3 * (int64_t)pg[q];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) px[q][c] = in(g3 + c);
-      }
-    };
-    tile_elements<float, NT, PF, true, false>(m, emat, mats, matl, A, t, gid, xs, ys, gather_next);
-    __syncthreads();
-    energy += tile_scatter<float, NT>(m, A, t, gid, xs, ys);
-    __syncthreads();
-    if (!more) break;
-#pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-      const int j = threadIdx.x + q * NT;
-      if (j < ntn) {
-        gid[j] = pg[q];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          xs[3 * j + c] = px[q][c];
-          ys[3 * j + c] = 0.0;
-        }
-      }
-    }
-    // ids of the tile after next: their latency overlaps the barrier and
-    // the next tile's first element loads
-    load_ids(tn + slots, ntn);
-    __syncthreads();
-    t = tn;
-  }
-  const double e = block_sum_n<NT>(energy, sh);
-  if (threadIdx.x == 0) atomic_add(&ctl->pAp[0][blockIdx.x % NSLOT], e);
-}
-
-// The same persistent pipeline over the (lane, tile) items of several cases:
-// items[k] = (lane, tile), tile-major with the lanes of a tile adjacent (they
-// share the tile's mesh data through L2); XCD x owns the contiguous eighth
-// [k_x, k_{x+1}) of the list.  An item is skipped when its lane is inactive or
-// its solve is done (or, on the first iteration, already converged): every
-// workgroup evaluates the same condition, so a skipped lane's output is left
-// untouched; on the first iteration the workgroup whose scan passes the
-// tile-0 item of an already converged lane marks that lane done (every item
-// is visited by exactly one workgroup's scan).  nmax: the largest tile over
-// the lanes (LDS layout).
-
-template <int NT, int NPT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_tile_lanes_pipe(
-    const TileLane<float>* __restrict__ lanes, const int2* __restrict__ items, int n_items, int nmax,
-    const LaneState* __restrict__ st, int iter) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double sh[NT / 64];
-  double* ys = reinterpret_cast<double*>(smem_raw);
-  int32_t* gid = reinterpret_cast<int32_t*>(ys + 3 * nmax);
-  float* xs = reinterpret_cast<float*>(gid + nmax + (nmax & 1));
-  const int par = iter & 1;
-  const int xcd = blockIdx.x & 7, slots = gridDim.x >> 3, slot = blockIdx.x >> 3;
-  const int lo = (int)(((int64_t)n_items * xcd) >> 3);
-  const int hi = (int)(((int64_t)n_items * (xcd + 1)) >> 3);
-  // work item k, the same in every lane of the workgroup: readfirstlane
-  // tells the compiler so, which keeps the item's lane and tile indices and
-  // the lane's pointers in scalar registers (without it the kernel spilled
-  // 29 vector registers)
-  auto item = [&](int k) {
-    int2 w = items[k];
-    w.x = __builtin_amdgcn_readfirstlane(w.x);
-    w.y = __builtin_amdgcn_readfirstlane(w.y);
-    return w;
-  };
-  // next item at or after k (in steps of slots) that is not skipped (hi if none)
-  auto next_live = [&](int k) {
-    for (; k < hi; k += slots) {
-      const int2 w = item(k);
-      if (st != nullptr && !st[w.x].active) continue;
-      CgCtl* c = lanes[w.x].ctl;
-      if (c->done) continue;
-      if (iter == 0 && slot_sum<NSLOT>(c->rr[0]) <= c->tol2) {
-        if (w.y == 0 && threadIdx.x == 0) c->done = 1;
-        continue;
-      }
-      break;
-    }
-    return k;
-  };
-  int k = __builtin_amdgcn_readfirstlane(next_live(lo + slot));
-  if (k >= hi) return;
-  int2 w = item(k);
-  {
-    const TileLane<float>& L = lanes[w.x];
-    const int n0 = L.m.tile_node_off[w.y], nt = L.m.tile_node_off[w.y + 1] - n0;
-    const float* __restrict__ x = L.A.x1;
-    for (int j = threadIdx.x; j < nt; j += NT) {
-      const int32_t g = L.m.tile_nodes[n0 + j];
-      gid[j] = g;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        xs[3 * j + c] = x[3 * (int64_t)g + c];
-        ys[3 * j + c] = 0.0;
-      }
-    }
-    __syncthreads();
-  }
-  for (;;) {
-    const TileLane<float>& L = lanes[w.x];
-    const int t = w.y;
-    // lane duties of the tile-0 item: clear the slots the next update kernel
-    // accumulates into
-    if (t == 0 && threadIdx.x < NSLOT) {
-      L.ctl->rz[par ^ 1][threadIdx.x] = 0.0;
-      L.ctl->rr[par ^ 1][threadIdx.x] = 0.0;
-    }
-    const int kn = __builtin_amdgcn_readfirstlane(next_live(k + slots));
-    const bool more = kn < hi;
-    int2 wn = make_int2(0, 0);
-    int32_t pg[NPT];
-    float px[NPT][3];
-    int ntn = 0;
-    if (more) {
-      wn = item(kn);
-      const TileLane<float>& Ln = lanes[wn.x];
-      const int n0 = Ln.m.tile_node_off[wn.y];
-      ntn = Ln.m.tile_node_off[wn.y + 1] - n0;
-      const float* __restrict__ xn = Ln.A.x1;
-#pragma unroll
-      for (int q = 0; q < NPT; ++q) {
-        const int j = threadIdx.x + q * NT;
-        pg[q] = j < ntn ? Ln.m.tile_nodes[n0 + j] : 0;
-      }
-#pragma unroll
-      for (int q = 0; q < NPT; ++q) {
-        const int64_t g3 = 3 * (int64_t)pg[q];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) px[q][c] = (threadIdx.x + q * NT < ntn) ? xn[g3 + c] : 0.0f;
-      }
-    }
-    tile_elements<float, NT, false>(L.m, L.emat, L.mats, L.A, t, gid, xs, ys);
-    __syncthreads();
-    const double energy = tile_scatter<float, NT>(L.m, L.A, t, gid, xs, ys);
-    const double e = block_sum_n<NT>(energy, sh);
-    if (threadIdx.x == 0) atomic_add(&L.ctl->pAp[0][t % NSLOT], e);
-    __syncthreads();
-    if (!more) break;
-#pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-      const int j = threadIdx.x + q * NT;
-      if (j < ntn) {
-        gid[j] = pg[q];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          xs[3 * j + c] = px[q][c];
-          ys[3 * j + c] = 0.0;
-        }
-      }
-    }
-    __syncthreads();
-    k = kn;
-    w = wn;
-  }
-}
-
-// Workgroups of the persistent pass: three per compute unit (the LDS and
-// register budget of the FP32 tile pass), a multiple of 8 (one run per XCD),
-// at most `cap` when cap > 0 (fewer workgroups, each walking more tiles).
-static unsigned pipe_grid(int n_tiles, int cap) {
-  static int n_cu = 0;
-  if (n_cu == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) ==
-                                                 hipSuccess && v > 0)
-      n_cu = v;
-    else
-      n_cu = 256;
-  }
-  int per_xcd = std::max(1, std::min((n_tiles + 7) / 8, 3 * n_cu / 8));
+// Workgroups of a pass over n tiles (or items): one each, a multiple of 8 (an
+// eighth per XCD); at most `cap` when cap > 0, each then walking several.
+static unsigned pass_grid(int n, int cap) {
+  int per_xcd = std::max(1, (n + 7) / 8);
   if (cap > 0) per_xcd = std::max(1, std::min(per_xcd, cap / 8));
   return (unsigned)(8 * per_xcd);
 }
 
-template <typename T>
-static size_t tile_lds(int max_tile_nodes) {
-  const size_t nmax = max_tile_nodes;
-  return 3 * nmax * sizeof(double) + (nmax + (nmax & 1)) * sizeof(int32_t) + 3 * nmax * sizeof(T);
-}
-
-constexpr int PIPE_NT = 256, PIPE_NPT = 5;
-static_assert(PIPE_NT * PIPE_NPT >= TILE_MAX_NODES, "the pipelined pass must cover a whole tile");
-static_assert(512 * 3 >= TILE_MAX_NODES && 256 * 5 >= TILE_MAX_NODES, "k_tile_dir must cover a whole tile");
-static_assert(3 * PIPE_MATS <= 256, "one work-item per entry of the material table");
-
-template <typename T>
-static void launch_tile(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<T>& a, CgCtl* ctl,
-                        int iter, hipStream_t s, int grid_cap = 0) {
-  const size_t lds = tile_lds<T>(m.max_tile_nodes);
+template <typename T, int IN, int TERMS, bool DET>
+static void launch_pass(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<T>& a, CgCtl* ctl,
+                        int iter, int grid_cap, hipStream_t s) {
+  constexpr int NT = 256;
+  const unsigned g = pass_grid(m.n_tiles, 0), gc = pass_grid(m.n_tiles, grid_cap);
+  const size_t lds = tile_lds<T>(m.max_tile_nodes, a.n_mat);
   if constexpr (sizeof(T) == 4) {
-    if (iter >= 0 && a.x2 == nullptr && a.a1 == 1.0f && a.accumulate == 0 && a.vin == nullptr &&
-        m.max_tile_nodes <= PIPE_NT * PIPE_NPT && a.n_mat >= 1 && a.n_mat <= PIPE_MATS) {
-      if (a.x1h)
-        hipLaunchKernelGGL((k_tile_pipe<PIPE_NT, PIPE_NPT, SW_PIPE_PF, true>), dim3(pipe_grid(m.n_tiles, grid_cap)),
-                           dim3(PIPE_NT), lds, s, m, emat, mats, a, ctl, iter);
-      else
-        hipLaunchKernelGGL((k_tile_pipe<PIPE_NT, PIPE_NPT, SW_PIPE_PF>), dim3(pipe_grid(m.n_tiles, grid_cap)),
-                           dim3(PIPE_NT), lds, s, m, emat, mats, a, ctl, iter);
+    if (gc < g) {
+      hipLaunchKernelGGL((k_tile<T, NT, IN, TERMS, DET, true>), dim3(gc), dim3(NT), lds, s, m, emat, mats, a, ctl,
+                         iter);
       return;
     }
   }
-  // 4 waves per workgroup (6 measured slower for FP32)
-  constexpr int NT = 256;
-  hipLaunchKernelGGL((k_tile<T, NT>), dim3(m.n_tiles), dim3(NT), lds, s, m, emat, mats, a, ctl, iter);
+  hipLaunchKernelGGL((k_tile<T, NT, IN, TERMS, DET, false>), dim3(g), dim3(NT), lds, s, m, emat, mats, a, ctl, iter);
 }
 
 // Whether a solve's iterations run as two kernels (k_tile_dir, k_cg_step)
@@ -841,13 +706,12 @@ static void launch_tile(const MeshDev& m, const uint8_t* emat, const MatDev* mat
 // step's other work included) against 1597 on 9.6 M tets, 17 against 26 on
 // 3000.  In FP32 up to 4000 tiles: 67 us against 86 at 1500 tiles, 128
 // against 141 at 3000, but 270 against 255 at 6750, where the vectors no
-// longer stay in the caches and the pipelined pass and the non-temporal
-// accesses of the three kernels gain more.  A cap on the persistent pass's
-// workgroups that binds asks for that pass.
+// longer stay in the caches and the non-temporal accesses of the three
+// kernels gain more.  A cap on the pass's workgroups that binds asks for
+// workgroups that walk several tiles: three kernels.
 constexpr int TWO_KERNEL_TILES_F32 = 4000;
-bool two_kernel_cg(const MeshDev& m, int n_mat, int grid_cap, bool f32) {
-  return n_mat >= 1 && n_mat <= PIPE_MATS &&
-         (!f32 || (m.n_tiles <= TWO_KERNEL_TILES_F32 && (grid_cap == 0 || grid_cap >= m.n_tiles)));
+bool two_kernel_cg(const MeshDev& m, int grid_cap, bool f32) {
+  return !f32 || (m.n_tiles <= TWO_KERNEL_TILES_F32 && (grid_cap == 0 || grid_cap >= m.n_tiles));
 }
 
 // FP32: 512 work-items, one element each in a full tile, two workgroups per
@@ -859,14 +723,14 @@ bool two_kernel_cg(const MeshDev& m, int n_mat, int grid_cap, bool f32) {
 template <typename T>
 static void launch_tile_dir(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<T>& a,
                             const T* p_old, T* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
-  const size_t lds = tile_lds<T>(m.max_tile_nodes);
-  const dim3 grid(8 * ((m.n_tiles + 7) / 8));
+  const size_t lds = tile_lds<T>(m.max_tile_nodes, a.n_mat);
+  const dim3 grid(pass_grid(m.n_tiles, 0));
   constexpr bool f32 = sizeof(T) == 4;
   if (f32 || m.n_tiles <= 256)
-    hipLaunchKernelGGL((k_tile_dir<T, 512, 3, f32 ? 4 : 2>), grid, dim3(512), lds, s, m, emat, mats, a, p_old, p, ctl,
+    hipLaunchKernelGGL((k_tile_dir<T, 512, f32 ? 4 : 2>), grid, dim3(512), lds, s, m, emat, mats, a, p_old, p, ctl,
                        iter & 1, iter == 0, max_iter);
   else if constexpr (!f32)
-    hipLaunchKernelGGL((k_tile_dir<T, 256, 5, 2>), grid, dim3(256), lds, s, m, emat, mats, a, p_old, p, ctl, iter & 1,
+    hipLaunchKernelGGL((k_tile_dir<T, 256, 2>), grid, dim3(256), lds, s, m, emat, mats, a, p_old, p, ctl, iter & 1,
                        iter == 0, max_iter);
 }
 void launch_tile_dir_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
@@ -886,14 +750,18 @@ static unsigned node_grid(int64_t n_nodes) {
 void launch_tile_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                      CgCtl* ctl, int iter, hipStream_t s) {
   if (!a.eout) {
-    launch_tile<double>(m, emat, mats, a, ctl, iter, s);
+    if (a.x2)
+      launch_pass<double, IN_TWO, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, 0, s);
+    else
+      launch_pass<double, IN_ONE, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, 0, s);
     return;
   }
   // deterministic: element and face slots, the node pass in slot order, and
-  // p.Ap as a fixed-order dot product (a CG pass has x1 = p, a1 = 1)
-  constexpr int NT = 256;
-  hipLaunchKernelGGL((k_tile<double, NT, true>), dim3(m.n_tiles), dim3(NT), tile_lds<double>(m.max_tile_nodes), s, m,
-                     emat, mats, a, ctl, iter);
+  // p.Ap as a fixed-order dot product (a CG pass has x1 = p)
+  if (a.x2)
+    launch_pass<double, IN_TWO, TERMS_ANY, true>(m, emat, mats, a, ctl, iter, 0, s);
+  else
+    launch_pass<double, IN_ONE, TERMS_ANY, true>(m, emat, mats, a, ctl, iter, 0, s);
   const int elems = a.sK != 0.0 || a.sM != 0.0, faces = a.sC != 0.0 || a.vin != nullptr;
   hipLaunchKernelGGL(k_node_gather, dim3(node_grid(m.n_nodes)), dim3(TPB), 0, s, m, a.eout, a.fout, a.y, 3, 0,
                      a.accumulate, elems, faces, ctl, iter);
@@ -902,25 +770,35 @@ void launch_tile_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, 
 }
 void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
                      CgCtl* ctl, int iter, int grid_cap, hipStream_t s) {
-  launch_tile<float>(m, emat, mats, a, ctl, iter, s, grid_cap);
+  if (a.sK != 0.0f && a.sM != 0.0f) {
+    if (a.x1h)
+      launch_pass<float, IN_BF16, TERMS_A, false>(m, emat, mats, a, ctl, iter, grid_cap, s);
+    else
+      launch_pass<float, IN_ONE, TERMS_A, false>(m, emat, mats, a, ctl, iter, grid_cap, s);
+  } else {
+    launch_pass<float, IN_ONE, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, grid_cap, s);
+  }
 }
 
-void launch_tile_lanes_f64(const TileLane<double>* lanes, const int2* work, int n_work, int max_tile_nodes,
-                           const LaneState* st, int iter, hipStream_t s) {
-  hipLaunchKernelGGL((k_tile_lanes<double, 256>), dim3(n_work), dim3(256), tile_lds<double>(max_tile_nodes), s, lanes,
-                     work, st, iter);
+void launch_tile_lanes_f64(const TileLane<double>* lanes, const int2* work, int n_work, int max_tile_nodes, int max_mat,
+                           bool two, const LaneState* st, hipStream_t s) {
+  const size_t lds = tile_lds<double>(max_tile_nodes, max_mat);
+  if (two)
+    hipLaunchKernelGGL((k_tile_lanes<double, 256, IN_TWO>), dim3(n_work), dim3(256), lds, s, lanes, work, st);
+  else
+    hipLaunchKernelGGL((k_tile_lanes<double, 256, IN_ONE>), dim3(n_work), dim3(256), lds, s, lanes, work, st);
 }
-void launch_tile_lanes_pipe_f32(const TileLane<float>* lanes, const int2* items, int n_items, int max_tile_nodes,
-                                const LaneState* st, int iter, int grid_cap, hipStream_t s) {
-  hipLaunchKernelGGL((k_tile_lanes_pipe<PIPE_NT, PIPE_NPT>), dim3(pipe_grid(n_items, grid_cap)), dim3(PIPE_NT),
-                     tile_lds<float>(max_tile_nodes), s, lanes, items, n_items, max_tile_nodes, st, iter);
+void launch_tile_lanes_f32(const TileLane<float>* lanes, const int2* items, int n_items, int max_tile_nodes,
+                           int max_mat, const LaneState* st, int iter, int grid_cap, hipStream_t s) {
+  hipLaunchKernelGGL((k_tile_lanes_cg<256>), dim3(pass_grid(n_items, grid_cap)), dim3(256),
+                     tile_lds<float>(max_tile_nodes, max_mat), s, lanes, items, n_items, max_tile_nodes, st, iter);
 }
 
 // ------------------------------------------------------------ geometry
 
 // Barycentric gradients (rows of the inverse Jacobian, L1..L3) and the volume
-// of every element from the FP64 coordinates, in FP64 (geo64[k][e], k < 10)
-// and rounded to FP32 (geo32).
+// of every element from the FP64 coordinates, in FP64 (geo64) and rounded to
+// FP32 (geo32).
 __global__ __launch_bounds__(TPB) void k_geom(MeshDev m, float* __restrict__ geo32, double* __restrict__ geo64) {
   __shared__ int32_t gid[TILE_MAX_NODES];
   const int t = blockIdx.x;
@@ -931,20 +809,38 @@ __global__ __launch_bounds__(TPB) void k_geom(MeshDev m, float* __restrict__ geo
   for (int e = m.tile_elem_off[t] + threadIdx.x; e < m.tile_elem_off[t + 1]; e += TPB) {
     double X[4][3];
     for (int k = 0; k < 4; ++k) {
-      const int64_t g = gid[m.conn_loc[k * m.tet_stride + e] / 3];
+      const int64_t g = gid[conn_node(m, k, e)];
       for (int d = 0; d < 3; ++d) X[k][d] = m.xyz[3 * g + d];
     }
     Geo<double> G;
     tet_geometry<double>(X, G);
-    for (int j = 0; j < 3; ++j) {
-      for (int d = 0; d < 3; ++d) {
-        geo64[(3 * j + d) * m.tet_stride + e] = G.g[1 + j][d];
-        geo32[(3 * j + d) * m.tet_stride + e] = (float)G.g[1 + j][d];
-      }
-    }
-    geo64[9 * m.tet_stride + e] = G.vol;
-    geo32[9 * m.tet_stride + e] = (float)G.vol;
+    const double v[10] = {G.g[1][0], G.g[1][1], G.g[1][2], G.g[2][0], G.g[2][1],
+                          G.g[2][2], G.g[3][0], G.g[3][1], G.g[3][2], G.vol};
+    double2* g64 = reinterpret_cast<double2*>(geo64);
+    float4* g32 = reinterpret_cast<float4*>(geo32);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) g64[k * m.tet_stride + e] = make_double2(v[2 * k], v[2 * k + 1]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      g32[k * m.tet_stride + e] =
+          make_float4((float)v[4 * k], (float)v[4 * k + 1], (float)v[4 * k + 2], (float)v[4 * k + 3]);
+    reinterpret_cast<float2*>(geo32 + 8 * m.tet_stride)[e] = make_float2((float)v[8], (float)v[9]);
   }
+}
+
+__global__ __launch_bounds__(TPB) void k_pack_conn(int64_t stride, const uint16_t* __restrict__ c,
+                                                   uint4* __restrict__ conn8, uint32_t* __restrict__ conn2) {
+  const int64_t e = (int64_t)blockIdx.x * TPB + threadIdx.x;
+  if (e >= stride) return;
+  uint32_t w[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k)
+    w[k] = 4u * c[(2 * k) * stride + e] | (4u * c[(2 * k + 1) * stride + e]) << 16;
+  conn8[e] = make_uint4(w[0], w[1], w[2], w[3]);
+  conn2[e] = w[4];
+}
+void launch_pack_conn(const MeshDev& m, const uint16_t* conn_loc, uint4* conn8, uint32_t* conn2, hipStream_t s) {
+  hipLaunchKernelGGL(k_pack_conn, dim3(nblocks(m.tet_stride)), dim3(TPB), 0, s, m.tet_stride, conn_loc, conn8, conn2);
 }
 
 void launch_geom(const MeshDev& m, float* geo32, double* geo64, hipStream_t s) {
@@ -974,7 +870,7 @@ __global__ __launch_bounds__(TPB) void k_tile_diag(MeshDev m, const uint8_t* __r
   const int e1 = m.tile_elem_off[t + 1];
   for (int e = m.tile_elem_off[t] + threadIdx.x; e < e1; e += TPB) {
     int ln[10];
-    for (int k = 0; k < 10; ++k) ln[k] = m.conn_loc[k * m.tet_stride + e] / 3;
+    for (int k = 0; k < 10; ++k) ln[k] = conn_node(m, k, e);
     double X[4][3];
     for (int k = 0; k < 4; ++k)
       for (int d = 0; d < 3; ++d) X[k][d] = m.xyz[3 * (int64_t)gid[ln[k]] + d];
