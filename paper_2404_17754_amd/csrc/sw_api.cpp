@@ -260,8 +260,7 @@ struct sw_batch {
   LaneDev* d_lanes = nullptr;
   LaneState* d_st = nullptr;
   LaneInfo* d_info = nullptr;
-  TileLane<double>* d_rhs1 = nullptr;
-  TileLane<double>* d_rhs2 = nullptr;
+  TileLane<double>* d_rhs = nullptr;
   TileLane<double>* d_true = nullptr;
   TileLane<float>* d_cg32 = nullptr;
   int2* d_work = nullptr;
@@ -271,7 +270,7 @@ struct sw_batch {
   std::vector<LaneDev> lanes;
   std::vector<LaneState> st;
   std::vector<LaneInfo> info;
-  std::vector<TileLane<double>> rhs1;
+  std::vector<TileLane<double>> rhs;
 };
 
 inline int batch_grid_cap(const sw_batch* b) { return b->grid_cap >= 0 ? b->grid_cap : b->ctx->grid_cap; }
@@ -913,40 +912,48 @@ int apply_f32_h(sw_case* c, const uint16_t* x, float* y, CgCtl* ctl, int iter, h
 }
 
 // Right-hand side of step c->step -> c->step + 1 (internal order) into y:
-// y = M (a + (4/dt + alpha) v) + C_abs v + F  then  y += -K (u - beta v).
-int build_rhs(sw_case* c, double* y) {
-  hipStream_t s = c->ctx->stream;
-  const int64_t nd = 3 * c->mesh->n_nodes;
-  // the first pass stores the interior nodes and adds into the shared ones
-  const int64_t ni3 = 3 * c->mesh->dev.n_interior;
-  launch_fill_f64(nd - ni3, y + ni3, 0.0, s);
+// y = M (a + (4/dt + alpha) v) + C_abs v + F - K (u - beta v).
+TileArgs<double> args_rhs(const sw_case* c, double* y) {
   TileArgs<double> A{};
   A.sM = 1.0;
-  A.sK = 0.0;
+  A.sK = -1.0;
   A.sC = 1.0;
   A.x1 = c->a;
   A.a1 = 1.0;
   A.x2 = c->v;
   A.a2 = 4.0 / c->dt + c->alpha;
   A.xf = c->v;
-  A.vin = c->vin + 3 * (c->step + 1);
+  A.k1 = c->u;
+  A.k2 = -c->beta;
   A.y = y;
-  A.accumulate = 0;
   A.n_mat = c->n_mat;
+  return A;
+}
+int build_rhs(sw_case* c, double* y) {
+  hipStream_t s = c->ctx->stream;
+  const int64_t nd = 3 * c->mesh->n_nodes;
+  // the pass stores the interior nodes and adds into the shared ones
+  const int64_t ni3 = 3 * c->mesh->dev.n_interior;
+  launch_fill_f64(nd - ni3, y + ni3, 0.0, s);
+  TileArgs<double> A = args_rhs(c, y);
+  A.vin = c->vin + 3 * (c->step + 1);
+  if (!c->det) {
+    launch_tile_rhs(c->mesh->dev, c->emat, c->mats, A, s);
+    LAUNCHED();
+    return SW_OK;
+  }
+  // deterministic: the mass, the dashpots and the force, then the stiffness
+  // added, each through the element and face slots
+  A.sK = 0.0;
   A.eout = c->det_e;
   A.fout = c->det_f;
   launch_tile_f64(c->mesh->dev, c->emat, c->mats, A, nullptr, -1, s);
-  TileArgs<double> B{};
+  TileArgs<double> B = args_rhs(c, y);
   B.sM = 0.0;
-  B.sK = -1.0;
   B.sC = 0.0;
-  B.x1 = c->u;
-  B.a1 = 1.0;
-  B.x2 = c->v;
-  B.a2 = -c->beta;
-  B.y = y;
+  B.x1 = B.k1;
+  B.a2 = B.k2;
   B.accumulate = 1;
-  B.n_mat = c->n_mat;
   B.eout = c->det_e;
   B.fout = c->det_f;
   launch_tile_f64(c->mesh->dev, c->emat, c->mats, B, nullptr, -1, s);
@@ -1755,12 +1762,13 @@ extern "C" int sw_case_apply(sw_case* c, int32_t op, const double* x, double* y)
   HIPC(hipSetDevice(c->ctx->device));
   const int64_t nn = c->mesh->n_nodes;
   hipStream_t s = c->ctx->stream;
+  const int64_t ni3 = 3 * c->mesh->dev.n_interior;  // the pass stores the interior nodes, adds into the rest
   launch_permute_f64(nn, 3, x, c->mesh->dev.node_i2u, c->p, s);
-  launch_fill_f64(3 * nn, c->q, 0.0, s);
+  launch_fill_f64(3 * nn - ni3, c->q + ni3, 0.0, s);
   int rc = apply_f64(c, op, c->p, c->q, nullptr, -1);
   if (rc) return rc;
   launch_permute_f64(nn, 3, c->q, c->mesh->dev.node_u2i, y, s);
-  launch_fill_f64(3 * nn, c->q, 0.0, s);
+  launch_fill_f64(3 * nn - ni3, c->q + ni3, 0.0, s);
   LAUNCHED();
   HIPC(hipStreamSynchronize(s));
   return SW_OK;
@@ -1774,8 +1782,9 @@ extern "C" int sw_case_apply_f32(sw_case* c, int32_t op, const float* x, float* 
   hipStream_t s = c->ctx->stream;
   float* xi = (float*)c->r;  // FP64 vectors hold twice the floats needed
   float* yi = (float*)c->z;
-  launch_permute_f32(nn, 3, x, c->mesh->dev.node_i2u, xi, s);
-  launch_fill_f32(3 * nn, yi, 0.0f, s);
+  launch_permute_f32(nn, x, c->mesh->dev.node_i2u, xi, s);
+  const int64_t ni3 = 3 * c->mesh->dev.n_interior;
+  launch_fill_f32(3 * nn - ni3, yi + ni3, 0.0f, s);
   int rc;
   if (op == SW_OP_A) {
     // as in an inner CG iteration (past the first): a fresh control block,
@@ -1787,7 +1796,7 @@ extern "C" int sw_case_apply_f32(sw_case* c, int32_t op, const float* x, float* 
     rc = apply_f32(c, op, xi, yi, nullptr, -1);
   }
   if (rc) return rc;
-  launch_permute_f32(nn, 3, yi, c->mesh->dev.node_u2i, y, s);
+  launch_permute_f32(nn, yi, c->mesh->dev.node_u2i, y, s);
   LAUNCHED();
   HIPC(hipStreamSynchronize(s));
   return SW_OK;
@@ -2303,8 +2312,7 @@ size_t batch_layout(int n, int n_work, int n_items, Carver& cv, sw_batch* b) {
   b->d_lanes = cv.take<LaneDev>(n);
   b->d_st = cv.take<LaneState>(n);
   b->d_info = cv.take<LaneInfo>(n);
-  b->d_rhs1 = cv.take<TileLane<double>>(n);
-  b->d_rhs2 = cv.take<TileLane<double>>(n);
+  b->d_rhs = cv.take<TileLane<double>>(n);
   b->d_true = cv.take<TileLane<double>>(n);
   b->d_cg32 = cv.take<TileLane<float>>(n);
   b->d_work = cv.take<int2>(n_work);
@@ -2413,16 +2421,15 @@ int batch_step_once(sw_batch* b) {
     L.guess_order = (g[l] == GUESS_NET || projected(g[l]))
                         ? -2
                         : (g[l] == GUESS_EXTRAP ? std::min(c->poly_order, c->hist_count - 1) : -1);
-    b->rhs1[l].A.vin = c->vin + 3 * (c->step + 1);
+    b->rhs[l].A.vin = c->vin + 3 * (c->step + 1);
     est[l] = std::max(1, c->last_iters / 2);
   }
   int rc = batch_upload(b, b->d_lanes, b->lanes.data(), n * sizeof(LaneDev));
-  if (!rc) rc = batch_upload(b, b->d_rhs1, b->rhs1.data(), n * sizeof(TileLane<double>));
+  if (!rc) rc = batch_upload(b, b->d_rhs, b->rhs.data(), n * sizeof(TileLane<double>));
   if (rc) return rc;
   // right-hand side, its norm, tolerance, initial guess
   launch_lanes(LANE_BEGIN_STEP, n, b->max_nodes, b->d_lanes, nullptr, nullptr, s);
-  launch_tile_lanes_f64(b->d_rhs1, b->d_work, b->n_work, b->max_tile_nodes, b->max_mat, true, nullptr, s);
-  launch_tile_lanes_f64(b->d_rhs2, b->d_work, b->n_work, b->max_tile_nodes, b->max_mat, true, nullptr, s);
+  launch_tile_lanes_f64(b->d_rhs, b->d_work, b->n_work, b->max_tile_nodes, b->max_mat, true, nullptr, s);
   launch_lanes(LANE_NORM2_B, n, b->max_nodes, b->d_lanes, nullptr, nullptr, s);
   launch_lanes(LANE_PREPARE64, n, b->max_nodes, b->d_lanes, nullptr, nullptr, s);
   launch_lanes(LANE_GUESS, n, b->max_nodes, b->d_lanes, nullptr, nullptr, s);
@@ -2634,8 +2641,8 @@ extern "C" int sw_batch_create(sw_ctx* ctx, sw_case* const* cases, int32_t n, vo
   b->lanes.resize(n);
   b->st.assign(n, LaneState{});
   b->info.resize(n);
-  b->rhs1.resize(n);
-  std::vector<TileLane<double>> rhs2(n), tru(n);
+  b->rhs.resize(n);
+  std::vector<TileLane<double>> tru(n);
   std::vector<TileLane<float>> cg32(n);
   for (int l = 0; l < n; ++l) {
     sw_case* c = cases[l];
@@ -2673,26 +2680,9 @@ extern "C" int sw_batch_create(sw_ctx* ctx, sw_case* const* cases, int32_t n, vo
     L.rtol = c->rtol;
     L.n_rec = c->n_rec;
     L.max_iter = c->max_iter;
-    // right-hand side: M (a + (4/dt + alpha) v) + C_abs v + F, then -K (u - beta v)
-    TileLane<double>& r1 = b->rhs1[l];
+    TileLane<double>& r1 = b->rhs[l];
     r1 = tile_lane<double>(c);
-    r1.A.sM = 1.0;
-    r1.A.sC = 1.0;
-    r1.A.x1 = c->a;
-    r1.A.a1 = 1.0;
-    r1.A.x2 = c->v;
-    r1.A.a2 = 4.0 / c->dt + c->alpha;
-    r1.A.xf = c->v;
-    r1.A.y = c->b;
-    TileLane<double>& r2 = rhs2[l];
-    r2 = tile_lane<double>(c);
-    r2.A.sK = -1.0;
-    r2.A.x1 = c->u;
-    r2.A.a1 = 1.0;
-    r2.A.x2 = c->v;
-    r2.A.a2 = -c->beta;
-    r2.A.y = c->b;
-    r2.A.accumulate = 1;
+    r1.A = args_rhs(c, c->b);
     // q = A x (FP64) and q32 = A p32 (FP32 CG iterations)
     TileLane<double>& t = tru[l];
     t = tile_lane<double>(c);
@@ -2712,8 +2702,7 @@ extern "C" int sw_batch_create(sw_ctx* ctx, sw_case* const* cases, int32_t n, vo
     f.A.y = c->q32;
     f.ctl = c->ctl32;
   }
-  rc = batch_upload(b, b->d_rhs2, rhs2.data(), n * sizeof(TileLane<double>));
-  if (!rc) rc = batch_upload(b, b->d_true, tru.data(), n * sizeof(TileLane<double>));
+  rc = batch_upload(b, b->d_true, tru.data(), n * sizeof(TileLane<double>));
   if (!rc) rc = batch_upload(b, b->d_cg32, cg32.data(), n * sizeof(TileLane<float>));
   if (!rc) rc = batch_upload(b, b->d_work, work.data(), work.size() * sizeof(int2));
   if (!rc) rc = batch_upload(b, b->d_items, items.data(), items.size() * sizeof(int2));
@@ -2739,7 +2728,7 @@ extern "C" int sw_batch_apply_f32(sw_batch* b, const float* const* x, float* con
   for (int l = 0; l < b->n; ++l) {
     sw_case* c = b->cases[l];
     const int64_t nn = c->mesh->n_nodes;
-    launch_permute_f32(nn, 3, x[l], c->mesh->dev.node_i2u, c->p32, s);
+    launch_permute_f32(nn, x[l], c->mesh->dev.node_i2u, c->p32, s);
     launch_fill_f32(3 * nn, c->q32, 0.0f, s);
     launch_fill_f64(sizeof(CgCtl) / 8, (double*)c->ctl32, 0.0, s);
     b->st[l].active = 1;
@@ -2751,7 +2740,7 @@ extern "C" int sw_batch_apply_f32(sw_batch* b, const float* const* x, float* con
                              s);
   for (int l = 0; l < b->n; ++l) {
     sw_case* c = b->cases[l];
-    launch_permute_f32(c->mesh->n_nodes, 3, c->q32, c->mesh->dev.node_u2i, y[l], s);
+    launch_permute_f32(c->mesh->n_nodes, c->q32, c->mesh->dev.node_u2i, y[l], s);
   }
   LAUNCHED();
   HIPC(hipStreamSynchronize(s));

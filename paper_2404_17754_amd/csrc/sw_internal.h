@@ -101,6 +101,8 @@ struct TileArgs {
   const T* x2;
   T a1, a2;
   const T* xf;         // nullptr: the pass's input xe
+  const T* k1;         // the right-hand side pass: the stiffness acts on k1 + k2 x2
+  T k2;
   const double* vin;   // 3 values or nullptr
   T* y;
   int accumulate;      // interior nodes: 0 overwrite, 1 add
@@ -164,10 +166,10 @@ struct LaneInfo {
   int32_t done64, iters64, done32, iters32;
 };
 
-// max_mat: the largest material table of the lanes; two: the passes take two
-// inputs (a1 x1 + a2 x2)
+// max_mat: the largest material table of the lanes; rhs: the right-hand side
+// pass (else A applied to x1)
 void launch_tile_lanes_f64(const TileLane<double>* lanes, const int2* work, int n_work, int max_tile_nodes, int max_mat,
-                           bool two, const LaneState* st, hipStream_t s);
+                           bool rhs, const LaneState* st, hipStream_t s);
 // FP32 CG-iteration pass of every lane over items (lane, tile) listed
 // tile-major with a tile's lanes adjacent.
 void launch_tile_lanes_f32(const TileLane<float>* lanes, const int2* items, int n_items, int max_tile_nodes,
@@ -203,6 +205,10 @@ void launch_lanes_cg(bool f32, bool dir, int n_lanes, int64_t max_nodes, const L
 // fixed-order dot product; the mesh needs its incidence lists).
 void launch_tile_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                      CgCtl* ctl, int iter, hipStream_t s);
+// The right-hand side in one pass: y = sM M (a1 x1 + a2 x2) + sC C_abs xf +
+// F(vin) + sK K (k1 + k2 x2), shared nodes of y cleared beforehand.
+void launch_tile_rhs(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
+                     hipStream_t s);
 // grid_cap > 0 limits the workgroups of the pass (a multiple of 8, each then
 // walking several tiles); 0: one per tile.
 void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
@@ -295,9 +301,9 @@ void launch_log_step(int32_t* it_dst, int32_t iters, double* rel_dst, double rel
 void launch_misfit(int n_rec, int64_t n_steps, const double* U, const double* obs, double* pair_buf,
                    double* out2, hipStream_t s);
 
-// dst[i*w + k] = src[map[i]*w + k], i < n, k < w (w <= 6)
+// dst[i*w + k] = src[map[i]*w + k], i < n, k < w (w = 3 or 6; 3 in FP32)
 void launch_permute_f64(int64_t n, int w, const double* src, const int32_t* map, double* dst, hipStream_t s);
-void launch_permute_f32(int64_t n, int w, const float* src, const int32_t* map, float* dst, hipStream_t s);
+void launch_permute_f32(int64_t n, const float* src, const int32_t* map, float* dst, hipStream_t s);
 
 // ---- learned initial guess (sw_mlp.hip) ---------------------------------
 

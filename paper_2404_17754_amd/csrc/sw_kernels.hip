@@ -261,6 +261,8 @@ __global__ __launch_bounds__(TPB) void k_cg_dir_h(int64_t n, int par, int iter_a
   }
 }
 
+constexpr int64_t STEP_XCD_NODES = 1500000;
+
 // Vector kernel of a two-kernel iteration (after k_tile_dir, which formed
 // p and q = A p): alpha = rz[par] / pAp[par]; x += alpha p; r -= alpha q;
 // z = P r; q = 0 (shared nodes); rz[par^1] += r.z, rr[par^1] += r.r.  r.z of
@@ -284,7 +286,25 @@ __global__ __launch_bounds__(NT) void k_cg_step(int64_t n, int64_t n_int, int pa
     }
     if (threadIdx.x < NSLOT) ctl->pAp[par ^ 1][threadIdx.x] = 0.0;
   }
-  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
+  // Each XCD's nodes (workgroup b runs on XCD b mod 8): an eighth of the
+  // interior nodes and an eighth of the shared ones, about those of the tiles
+  // the operator pass gives it, so that z, p and q stay in its L2: 26.0 us an
+  // iteration against 27.0 at 0.27 M nodes, 46.3 against 48.4 at 0.6 M.  Past
+  // STEP_XCD_NODES, where the caches no longer hold them, one stream over all
+  // nodes (FP64 at 2.1 M nodes: 215 us against 222).
+  int64_t i0 = 0, ci = n_int, s0 = n_int, cs = n - n_int;
+  int64_t l = (int64_t)blockIdx.x * NT + threadIdx.x, stride = (int64_t)gridDim.x * NT;
+  if (n <= STEP_XCD_NODES) {
+    const int xcd = blockIdx.x & 7;
+    i0 = n_int * xcd / 8;
+    ci = n_int * (xcd + 1) / 8 - i0;
+    s0 = n_int + (n - n_int) * xcd / 8;
+    cs = n_int + (n - n_int) * (xcd + 1) / 8 - s0;
+    l = (int64_t)(blockIdx.x >> 3) * NT + threadIdx.x;
+    stride /= 8;
+  }
+  for (; l < ci + cs; l += stride) {
+    const int64_t i = l < ci ? i0 + l : s0 + (l - ci);
     T rv[3], qv[3], pv[3], xv[3], zv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -355,8 +375,8 @@ void launch_cg_update_f32(int64_t n, int64_t n_int, int par, const __half* P, fl
 }
 constexpr int STEP_NT = 512;
 static inline unsigned step_grid(int64_t n) {
-  const int64_t g = (n + STEP_NT - 1) / STEP_NT;
-  return (unsigned)(g > 1024 ? 1024 : (g == 0 ? 1 : g));
+  const int64_t g = (n + 8 * STEP_NT - 1) / (8 * STEP_NT) * 8;
+  return (unsigned)(g > 1024 ? 1024 : (g == 0 ? 8 : g));
 }
 void launch_cg_step_f64(int64_t n, int64_t n_int, int par, const double* P, double* r, double* z, double* q,
                         const double* p, double* x, CgCtl* ctl, hipStream_t s) {
@@ -402,39 +422,45 @@ void launch_ctl_prepare(CgCtl* ctl, double rtol, int iters, hipStream_t s) {
   hipLaunchKernelGGL(k_ctl_prepare, dim3(1), dim3(64), 0, s, ctl, rtol, iters);
 }
 
-__global__ __launch_bounds__(TPB) void k_norm2(int64_t n, const double* __restrict__ x, double* out) {
-  __shared__ double sh[2 * TPB / 64];
+// Norms of whole vectors: one FP64 atomic per workgroup into one address,
+// 12 ns each, so few large workgroups (256 work-items and up to 8192 groups
+// took 41 us for the residual of 0.8 M values, this grid 10).  det: one
+// workgroup, a fixed-order sum.
+constexpr int NORM_NT = 1024;
+static unsigned norm_grid(int64_t n, bool det) {
+  const int64_t g = (n + NORM_NT - 1) / NORM_NT;
+  return det || g < 1 ? 1u : (unsigned)(g > 512 ? 512 : g);
+}
+
+__global__ __launch_bounds__(NORM_NT) void k_norm2(int64_t n, const double* __restrict__ x, double* out) {
+  __shared__ double sh[NORM_NT / 64];
   double acc = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) acc += x[i] * x[i];
-  acc = block_sum(acc, sh);
+  for (int64_t i = (int64_t)blockIdx.x * NORM_NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NORM_NT)
+    acc += x[i] * x[i];
+  acc = block_sum_n<NORM_NT>(acc, sh);
   if (threadIdx.x == 0) atomic_add(out, acc);
 }
 void launch_norm2(int64_t n, const double* x, double* out, hipStream_t s, bool det) {
-  unsigned g = nblocks(n);
-  if (g > 4096) g = 4096;
-  if (det || g == 0) g = 1;
-  hipLaunchKernelGGL(k_norm2, dim3(g), dim3(TPB), 0, s, n, x, out);
+  hipLaunchKernelGGL(k_norm2, dim3(norm_grid(n, det)), dim3(NORM_NT), 0, s, n, x, out);
 }
 
 // r = b - q (n doubles), rr_true += r.r (ctl->rr_true cleared by the caller)
-__global__ __launch_bounds__(TPB) void k_true_res(int64_t n, const double* __restrict__ b,
-                                                  const double* __restrict__ q, double* __restrict__ r, CgCtl* ctl) {
-  __shared__ double sh[2 * TPB / 64];
+__global__ __launch_bounds__(NORM_NT) void k_true_res(int64_t n, const double* __restrict__ b,
+                                                      const double* __restrict__ q, double* __restrict__ r,
+                                                      CgCtl* ctl) {
+  __shared__ double sh[NORM_NT / 64];
   double acc = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
+  for (int64_t i = (int64_t)blockIdx.x * NORM_NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NORM_NT) {
     const double t = b[i] - q[i];
     r[i] = t;
     acc += t * t;
   }
-  acc = block_sum(acc, sh);
+  acc = block_sum_n<NORM_NT>(acc, sh);
   if (threadIdx.x == 0) atomic_add(&ctl->rr_true, acc);
 }
 void launch_true_residual(int64_t n, const double* b, const double* q, double* r, CgCtl* ctl, hipStream_t s,
                           bool det) {
-  unsigned g = nblocks(n);
-  if (g > 8192) g = 8192;
-  if (det || g == 0) g = 1;
-  hipLaunchKernelGGL(k_true_res, dim3(g), dim3(TPB), 0, s, n, b, q, r, ctl);
+  hipLaunchKernelGGL(k_true_res, dim3(norm_grid(n, det)), dim3(NORM_NT), 0, s, n, b, q, r, ctl);
 }
 
 // Start of a refinement round in one pass: the FP32 inner system's
@@ -741,23 +767,35 @@ void launch_fill_f32(int64_t n, float* x, float val, hipStream_t s) {
 
 // ---------------------------------------------------------- permutation
 
-template <typename T>
-__global__ __launch_bounds__(TPB) void k_permute(int64_t n, int w, const T* __restrict__ src,
+// one node per work-item: the W values of a node in one or two loads (a value
+// per work-item divided its index by W and loaded the map W times: 13 M nodes
+// of three floats in 190 us, this one in 130; 174 without the XCDs' eighths)
+template <typename T, int W>
+__global__ __launch_bounds__(TPB) void k_permute(int64_t n, const T* __restrict__ src,
                                                  const int32_t* __restrict__ map, T* __restrict__ dst) {
-  for (int64_t k = (int64_t)blockIdx.x * TPB + threadIdx.x; k < n * w; k += (int64_t)gridDim.x * TPB) {
-    const int64_t i = k / w;
-    dst[k] = src[(int64_t)map[i] * w + (k - i * w)];
-  }
+  // a contiguous eighth of the nodes per XCD (workgroup b runs on XCD b mod 8):
+  // nodes next to each other share cache lines of the other order
+  const int64_t blk = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int64_t i = blk * TPB + threadIdx.x;
+  if (i >= n) return;
+  const int64_t j = map[i];
+  T v[W];
+#pragma unroll
+  for (int c = 0; c < W; ++c) v[c] = src[W * j + c];
+#pragma unroll
+  for (int c = 0; c < W; ++c) dst[W * i + c] = v[c];
 }
 void launch_permute_f64(int64_t n, int w, const double* src, const int32_t* map, double* dst, hipStream_t s) {
-  unsigned g = nblocks(n * w);
-  if (g > 16384) g = 16384;
-  hipLaunchKernelGGL(k_permute<double>, dim3(g), dim3(TPB), 0, s, n, w, src, map, dst);
+  if (n <= 0) return;
+  const unsigned g = (nblocks(n) + 7) / 8 * 8;
+  if (w == 3)
+    hipLaunchKernelGGL((k_permute<double, 3>), dim3(g), dim3(TPB), 0, s, n, src, map, dst);
+  else
+    hipLaunchKernelGGL((k_permute<double, 6>), dim3(g), dim3(TPB), 0, s, n, src, map, dst);
 }
-void launch_permute_f32(int64_t n, int w, const float* src, const int32_t* map, float* dst, hipStream_t s) {
-  unsigned g = nblocks(n * w);
-  if (g > 16384) g = 16384;
-  hipLaunchKernelGGL(k_permute<float>, dim3(g), dim3(TPB), 0, s, n, w, src, map, dst);
+void launch_permute_f32(int64_t n, const float* src, const int32_t* map, float* dst, hipStream_t s) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL((k_permute<float, 3>), dim3((nblocks(n) + 7) / 8 * 8), dim3(TPB), 0, s, n, src, map, dst);
 }
 
 // ---------------------------------------------------------------- lanes
@@ -929,17 +967,18 @@ void launch_lanes(LaneOp op, int n_lanes, int64_t max_nodes, const LaneDev* lane
   if (n_lanes <= 0) return;
   const unsigned bn = lane_blocks(n_lanes, max_nodes, 2048);       // node loops (dot products into slots)
   const unsigned bd = lane_blocks(n_lanes, 3 * max_nodes, 8192);   // DOF loops
+  const unsigned bs = lane_blocks(n_lanes, 3 * max_nodes, 2048);   // DOF loops with a norm (into one address)
   switch (op) {
 #define SW_LANE_CASE(OP, BX)                                                                          \
   case OP:                                                                                            \
     hipLaunchKernelGGL(k_lane_op<OP>, dim3(BX, n_lanes), dim3(TPB), 0, s, lanes, st, info);           \
     break;
     SW_LANE_CASE(LANE_BEGIN_STEP, bd)
-    SW_LANE_CASE(LANE_NORM2_B, bd)
+    SW_LANE_CASE(LANE_NORM2_B, bs)
     SW_LANE_CASE(LANE_PREPARE64, 1)
     SW_LANE_CASE(LANE_GUESS, bd)
     SW_LANE_CASE(LANE_RRTRUE_RESET, 1)
-    SW_LANE_CASE(LANE_TRUE_RES, bd)
+    SW_LANE_CASE(LANE_TRUE_RES, bs)
     SW_LANE_CASE(LANE_TO_F32, bd)
     SW_LANE_CASE(LANE_CG_INIT32, bn)
     SW_LANE_CASE(LANE_CG_INIT64, bn)

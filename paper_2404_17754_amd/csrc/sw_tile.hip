@@ -398,6 +398,67 @@ __device__ __forceinline__ double tile_body(const MeshDev& m, const uint8_t* __r
   return tile_scatter<T, NT>(m, A, t, lds);
 }
 
+// One tile of the right-hand side pass,
+//   y = sM M (a1 x1 + a2 x2) + sC C_abs xf + F(vin) + sK K (k1 + k2 x2):
+// the mass on its input, then the stiffness on the other, which waits in
+// registers (30 of the mass loop's spare ones) for its turn in the LDS.  Two
+// passes gather v and add every shared node to global memory twice: with the
+// permutation of the result 1.55 ms on 9.6 M tets, this pass 1.15.
+template <int NT>
+__device__ __forceinline__ void tile_rhs(const MeshDev& m, const uint8_t* __restrict__ emat,
+                                         const MatDev* __restrict__ mats, const TileArgs<double>& A, int t,
+                                         const TileLds<double>& lds) {
+  constexpr int NPT = tile_npt<NT>();
+  TileNodes<NT, NPT> N;
+  N.load(m, t);
+  const double mat = mat_load(mats, A.n_mat, threadIdx.x);
+  double kv[NPT][3];
+  tile_element_loop<double, NT, false, false, true, false, false>(m, emat, A, t, lds, [&] {
+    mat_store<double, NT>(mats, A.n_mat, mat, lds.matl);
+    double v1[NPT][3], v2[NPT][3];
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int64_t g3 = 3 * (int64_t)N.g[q];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        v1[q][c] = A.x1[g3 + c];
+        v2[q][c] = A.x2[g3 + c];
+        kv[q][c] = A.k1[g3 + c];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int j = threadIdx.x + q * NT;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) kv[q][c] += A.k2 * v2[q][c];
+      if (j < N.nt) {
+        lds.gid[j] = N.g[q];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          lds.xs[3 * j + c] = A.a1 * v1[q][c] + A.a2 * v2[q][c];
+          lds.ys[3 * j + c] = 0.0;
+        }
+      }
+    }
+    __syncthreads();
+  });
+  tile_faces<double, NT, false>(m, emat, mats, A, t, lds);
+  tile_element_loop<double, NT, false, true, false, false, false>(m, emat, A, t, lds, [&] {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int j = threadIdx.x + q * NT;
+      if (j < N.nt) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) lds.xs[3 * j + c] = kv[q][c];
+      }
+    }
+    __syncthreads();
+  });
+  __syncthreads();
+  tile_scatter<double, NT>(m, A, t, lds);
+}
+
 // Share of n tiles (or work items) of workgroup b: XCD x = b mod 8
 // (workgroups are dealt to the 8 XCDs round-robin) takes the contiguous
 // eighth [lo, hi), so that neighbouring tiles, which share nodes, meet in one
@@ -502,6 +563,15 @@ __global__ __launch_bounds__(TPB) void k_dot_slots(int64_t n, const double* __re
   if (threadIdx.x == 0) slots[blockIdx.x] = acc;
 }
 
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_tile_rhs(
+    MeshDev m, const uint8_t* __restrict__ emat, const MatDev* __restrict__ mats, TileArgs<double> A) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const TileLds<double> lds(smem_raw, m.max_tile_nodes);
+  const XcdShare share(m.n_tiles);
+  if (share.at < share.hi) tile_rhs<NT>(m, emat, mats, A, share.at, lds);
+}
+
 // A lane's tables and vectors as pointers to global memory (as_global).
 template <typename T>
 __device__ __forceinline__ TileLane<T> lane_of(const TileLane<T>* lanes, int l) {
@@ -525,6 +595,7 @@ __device__ __forceinline__ TileLane<T> lane_of(const TileLane<T>* lanes, int l) 
   L.mats = as_global(L.mats);
   L.A.x1 = as_global(L.A.x1);
   L.A.x2 = as_global(L.A.x2);
+  L.A.k1 = as_global(L.A.k1);
   L.A.xf = as_global(L.A.xf);
   L.A.vin = as_global(L.A.vin);
   L.A.y = as_global(L.A.y);
@@ -534,8 +605,8 @@ __device__ __forceinline__ TileLane<T> lane_of(const TileLane<T>* lanes, int l) 
 
 // The same pass for several cases (lanes) in one launch: work item b is
 // (lane, tile) = work[b] (lane < 0: padding), lanes whose state is inactive
-// return at once.
-template <typename T, int NT, int IN>
+// return at once.  RHS: the right-hand side pass, else A applied to x1.
+template <typename T, int NT, bool RHS>
 __global__ __launch_bounds__(NT) void k_tile_lanes(const TileLane<T>* __restrict__ lanes,
                                                     const int2* __restrict__ work,
                                                     const LaneState* __restrict__ st) {
@@ -545,7 +616,10 @@ __global__ __launch_bounds__(NT) void k_tile_lanes(const TileLane<T>* __restrict
   if (st != nullptr && !st[w.x].active) return;
   const TileLane<T> L = lane_of(lanes, w.x);
   const TileLds<T> lds(smem_raw, L.m.max_tile_nodes);
-  tile_body<T, NT, IN, TERMS_ANY, false>(L.m, L.emat, L.mats, L.A, w.y, lds);
+  if constexpr (RHS)
+    tile_rhs<NT>(L.m, L.emat, L.mats, L.A, w.y, lds);
+  else
+    tile_body<T, NT, IN_ONE, TERMS_ANY, false>(L.m, L.emat, L.mats, L.A, w.y, lds);
 }
 
 // FP32 operator pass of a CG iteration over the (lane, tile) items of several
@@ -750,10 +824,7 @@ static unsigned node_grid(int64_t n_nodes) {
 void launch_tile_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                      CgCtl* ctl, int iter, hipStream_t s) {
   if (!a.eout) {
-    if (a.x2)
-      launch_pass<double, IN_TWO, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, 0, s);
-    else
-      launch_pass<double, IN_ONE, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, 0, s);
+    launch_pass<double, IN_ONE, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, 0, s);
     return;
   }
   // deterministic: element and face slots, the node pass in slot order, and
@@ -780,13 +851,19 @@ void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, 
   }
 }
 
+void launch_tile_rhs(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
+                     hipStream_t s) {
+  hipLaunchKernelGGL(k_tile_rhs<256>, dim3(pass_grid(m.n_tiles, 0)), dim3(256),
+                     tile_lds<double>(m.max_tile_nodes, a.n_mat), s, m, emat, mats, a);
+}
+
 void launch_tile_lanes_f64(const TileLane<double>* lanes, const int2* work, int n_work, int max_tile_nodes, int max_mat,
-                           bool two, const LaneState* st, hipStream_t s) {
+                           bool rhs, const LaneState* st, hipStream_t s) {
   const size_t lds = tile_lds<double>(max_tile_nodes, max_mat);
-  if (two)
-    hipLaunchKernelGGL((k_tile_lanes<double, 256, IN_TWO>), dim3(n_work), dim3(256), lds, s, lanes, work, st);
+  if (rhs)
+    hipLaunchKernelGGL((k_tile_lanes<double, 256, true>), dim3(n_work), dim3(256), lds, s, lanes, work, st);
   else
-    hipLaunchKernelGGL((k_tile_lanes<double, 256, IN_ONE>), dim3(n_work), dim3(256), lds, s, lanes, work, st);
+    hipLaunchKernelGGL((k_tile_lanes<double, 256, false>), dim3(n_work), dim3(256), lds, s, lanes, work, st);
 }
 void launch_tile_lanes_f32(const TileLane<float>* lanes, const int2* items, int n_items, int max_tile_nodes,
                            int max_mat, const LaneState* st, int iter, int grid_cap, hipStream_t s) {

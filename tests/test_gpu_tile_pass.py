@@ -41,8 +41,13 @@ def test_long_material_tables(sw, n_mat):
     for op in ("A", "M", "K", "M+K+Cabs"):
         assert _rel(many["fp64"].apply(op, x), two["fp64"].apply(op, x)) < 1e-14
         assert _rel(many["mixed"].apply_f32(op, x), two["mixed"].apply_f32(op, x)) < 1e-6
+    u, v, a = (rng.standard_normal(3 * mesh.n_nodes) for _ in range(3))
+    for c in (two["fp64"], many["fp64"]):
+        c.set_state(u, v, a)
+    assert _rel(many["fp64"].rhs(), two["fp64"].rhs()) < 1e-14
     for p in ("fp64", "mixed"):
         for c in (two[p], many[p]):
+            c.set_state(u * 1e-3, v * 1e-3, a * 1e-3)
             c.step(3)
         assert np.linalg.norm(many[p].waveforms() - two[p].waveforms()) <= 1e-6 * np.linalg.norm(two[p].waveforms())
 
@@ -64,6 +69,11 @@ def test_tile_sizes_and_capped_grids(sw, nodes, elems, cap):
     assert _rel(gc.apply("A", xd), ref) < 1e-13
     ref32 = torch.from_numpy(A @ x.astype(np.float32).astype(np.float64)).cuda()
     assert _rel(gc.apply_f32("A", xd), ref32) < 1e-6
+    # right-hand side b = F + M (4/dt v + a) + C v - K u
+    u, v, a = (np.random.default_rng(k).standard_normal(3 * mesh.n_nodes) for k in (2, 3, 4))
+    gc.set_state(u, v, a)
+    rhs = case.v_in[1] @ s.Fb + s.M @ (4.0 / case.dt * v + a) + s.C @ v - s.K @ u
+    assert _rel(gc.rhs(), torch.from_numpy(rhs).cuda()) < 1e-13
     b = sw.Batch(ctx, [gc, sw.Case(ctx, gm, case, precision="mixed")])
     for y in b.apply_f32([xd, xd]):
         assert _rel(y, ref32) < 1e-6
