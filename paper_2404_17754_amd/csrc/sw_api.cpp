@@ -237,7 +237,7 @@ struct sw_mlp {
   sw_ctx* ctx;
   float *theta, *m, *v;  // FP32 master weights, Adam moments
   double* grad;          // un-normalised gradient accumulator
-  double* loss2;         // sum w e^2, sum w
+  double* loss2;         // sum w e^2, sum w: one pair per training step of a round of LOSS_RING
   int64_t adam_step = 0;
 };
 
@@ -2090,12 +2090,15 @@ static int fit_one(sw_ctx* ctx, int32_t n_rec, int64_t n_steps, const double* co
   return SW_OK;
 }
 
+// Training steps whose losses stay on the device before the host reads them.
+constexpr int LOSS_RING = 1024;
+
 static size_t mlp_layout(Carver& cv, sw_mlp* o) {
   auto th = cv.take<float>(MLP_NP);
   auto m = cv.take<float>(MLP_NP);
   auto v = cv.take<float>(MLP_NP);
   auto g = cv.take<double>(MLP_NP);
-  auto l2 = cv.take<double>(4);
+  auto l2 = cv.take<double>(2 * LOSS_RING);
   if (o) {
     o->theta = th;
     o->m = m;
@@ -2151,7 +2154,7 @@ extern "C" int sw_mlp_create(sw_ctx* ctx, const float* params, void* ws, size_t 
   launch_fill_f32(MLP_NP, o->m, 0.0f, s);
   launch_fill_f32(MLP_NP, o->v, 0.0f, s);
   launch_fill_f64(MLP_NP, o->grad, 0.0, s);
-  launch_fill_f64(4, o->loss2, 0.0, s);
+  launch_fill_f64(2 * LOSS_RING, o->loss2, 0.0, s);
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
     delete o;
@@ -2188,7 +2191,7 @@ extern "C" int sw_mlp_gradient(sw_mlp* o, const float* S, int64_t n, double* gra
   HIPC(hipSetDevice(o->ctx->device));
   hipStream_t s = o->ctx->stream;
   launch_fill_f64(MLP_NP, o->grad, 0.0, s);
-  launch_fill_f64(4, o->loss2, 0.0, s);
+  launch_fill_f64(2, o->loss2, 0.0, s);
   launch_mlp_grad(S, n, 0, 0, 0, o->theta, o->grad, o->loss2, s);
   LAUNCHED();
   double l2[2];
@@ -2207,17 +2210,20 @@ extern "C" int sw_mlp_train(sw_mlp* o, const float* S, int64_t n, int32_t steps,
   if (!o || !S || n <= 0 || steps < 0 || batch <= 0 || !(lr > 0.0f)) return fail(SW_EINVAL, "bad arguments");
   HIPC(hipSetDevice(o->ctx->device));
   hipStream_t s = o->ctx->stream;
-  for (int k = 0; k < steps; ++k) {
-    launch_fill_f64(4, o->loss2, 0.0, s);
-    launch_mlp_grad(S, n, batch, seed, o->adam_step, o->theta, o->grad, o->loss2, s);
-    o->adam_step += 1;
-    launch_mlp_adam(o->theta, o->m, o->v, o->grad, o->loss2, o->adam_step, lr, s);
+  std::vector<double> l2(loss ? 2 * (size_t)std::min(steps, LOSS_RING) : 0);
+  for (int k0 = 0; k0 < steps; k0 += LOSS_RING) {
+    const int m = std::min(LOSS_RING, steps - k0);
+    launch_fill_f64(2 * m, o->loss2, 0.0, s);
+    for (int k = 0; k < m; ++k) {
+      launch_mlp_grad(S, n, batch, seed, o->adam_step, o->theta, o->grad, o->loss2 + 2 * k, s);
+      o->adam_step += 1;
+      launch_mlp_adam(o->theta, o->m, o->v, o->grad, o->loss2 + 2 * k, o->adam_step, lr, s);
+    }
     LAUNCHED();
     if (loss) {
-      double l2[2];
-      HIPC(hipMemcpyAsync(l2, o->loss2, 16, hipMemcpyDeviceToHost, s));
+      HIPC(hipMemcpyAsync(l2.data(), o->loss2, 16 * (size_t)m, hipMemcpyDeviceToHost, s));
       HIPC(hipStreamSynchronize(s));
-      loss[k] = l2[1] > 0.0 ? (float)(l2[0] / l2[1]) : 0.0f;
+      for (int k = 0; k < m; ++k) loss[k0 + k] = l2[2 * k + 1] > 0.0 ? (float)(l2[2 * k] / l2[2 * k + 1]) : 0.0f;
     }
   }
   HIPC(hipStreamSynchronize(s));

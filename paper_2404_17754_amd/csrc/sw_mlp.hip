@@ -18,64 +18,80 @@
 namespace sw {
 
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+// vector loads from a caller's rows, which need be aligned to single values only
+typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // ---------------------------------------------------------------- network
 
 // Network weights held in registers by every lane of a wave, laid out for
-// the 16x16x16 MFMA in transposed form (rows = hidden units, columns = the
-// 16 DOFs of one pass): lane l (q = l / 16, r = l % 16) holds
+// the 16x16x16 and 16x16x32 MFMA in transposed form (rows = hidden units,
+// columns = the 16 DOFs of one pass): lane l (q = l / 16, r = l % 16) holds
 //   w1[b]    = W1[16b + r][4q .. 4q+3]          (A operand, layer 1)
 //   b1[b]    = b1[16b + 4q .. 16b + 4q + 3]      (accumulator init)
-//   w2[c][b] = W2[16c + r][16b + 4q .. +3]       (A operand, layer 2)
+//   w2[c][p] = W2[16c + r][32p + 4q .. +3] and [32p + 16 + 4q .. +3]
+//              (A operand, layer 2: the sum over the units of both halves in
+//              the order in which layer 1 leaves them in the lanes)
 //   b2[c], w3[c] likewise for units 16c + 4q .. +3
 struct MlpRegs {
   half4 w1[4];
   floatx4 b1[4];
-  half4 w2[4][4];
+  half8 w2[4][2];
   floatx4 b2[4];
   floatx4 w3[4];
   float b3;
 };
 
+__device__ __forceinline__ floatx4 load4(const float* __restrict__ p) {
+  const float4 v = *reinterpret_cast<const float4*>(p);
+  return floatx4{v.x, v.y, v.z, v.w};
+}
+
 __device__ __forceinline__ void mlp_load(const float* __restrict__ th, MlpRegs& R) {
   const int l = threadIdx.x & 63, q = l >> 4, r = l & 15;
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int f = 4 * q + j;
-      R.w1[b][j] = (_Float16)(f < MLP_IN ? th[MLP_OFF_W1 + (16 * b + r) * MLP_IN + f] : 0.0f);
-      R.b1[b][j] = th[MLP_OFF_B1 + 16 * b + 4 * q + j];
-      R.b2[b][j] = th[MLP_OFF_B2 + 16 * b + 4 * q + j];
-      R.w3[b][j] = th[MLP_OFF_W3 + 16 * b + 4 * q + j];
-    }
+    // features 4q .. 4q+3 of ten (8-byte aligned rows)
+    const float2* w = reinterpret_cast<const float2*>(th + MLP_OFF_W1 + (16 * b + r) * MLP_IN + 4 * q);
+    const float2 lo = q < 3 ? w[0] : make_float2(0.0f, 0.0f), hi = q < 2 ? w[1] : make_float2(0.0f, 0.0f);
+    R.w1[b] = half4{(_Float16)lo.x, (_Float16)lo.y, (_Float16)hi.x, (_Float16)hi.y};
+    R.b1[b] = load4(th + MLP_OFF_B1 + 16 * b + 4 * q);
+    R.b2[b] = load4(th + MLP_OFF_B2 + 16 * b + 4 * q);
+    R.w3[b] = load4(th + MLP_OFF_W3 + 16 * b + 4 * q);
   }
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int p = 0; p < 2; ++p) {
+      const float* w = th + MLP_OFF_W2 + (16 * c + r) * MLP_H + 32 * p + 4 * q;
+      const floatx4 lo = load4(w), hi = load4(w + 16);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) R.w2[c][b][j] = (_Float16)th[MLP_OFF_W2 + (16 * c + r) * MLP_H + 16 * b + 4 * q + j];
+      for (int j = 0; j < 4; ++j) {
+        R.w2[c][p][j] = (_Float16)lo[j];
+        R.w2[c][p][4 + j] = (_Float16)hi[j];
+      }
+    }
   R.b3 = th[MLP_OFF_B3];
 }
 
 // Network output for the 16 inputs of one pass.  xin: lane (q, r) holds
 // features 4q .. 4q+3 of input r.  Returns y of input r in every lane.
 __device__ __forceinline__ float mlp_eval16(const half4 xin, const MlpRegs& R) {
-  half4 h1[4];
+  half8 h1[2];
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
-    floatx4 d = __builtin_amdgcn_mfma_f32_16x16x16f16(R.w1[b], xin, R.b1[b], 0, 0, 0);
+    const floatx4 d = __builtin_amdgcn_mfma_f32_16x16x16f16(R.w1[b], xin, R.b1[b], 0, 0, 0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) h1[b][j] = (_Float16)fmaxf(d[j], 0.0f);
+    for (int j = 0; j < 4; ++j) h1[b >> 1][4 * (b & 1) + j] = (_Float16)fmaxf(d[j], 0.0f);
   }
   float part = 0.0f;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     floatx4 acc = R.b2[c];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc = __builtin_amdgcn_mfma_f32_16x16x16f16(R.w2[c][b], h1[b], acc, 0, 0, 0);
+    for (int p = 0; p < 2; ++p) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(R.w2[c][p], h1[p], acc, 0, 0, 0);
 #pragma unroll
     for (int j = 0; j < 4; ++j) part += R.w3[c][j] * fmaxf(acc[j], 0.0f);
   }
@@ -84,23 +100,36 @@ __device__ __forceinline__ float mlp_eval16(const half4 xin, const MlpRegs& R) {
   return part + R.b3;
 }
 
-// y[i] = net(X[i, 0..9]) for i < n (matrix-core path, as in the guess)
+// y[i] = net(X[i, 0..9]) for i < n (matrix-core path, as in the guess).  A
+// wavefront keeps the weights for all its passes (so few wavefronts: 20 KB of
+// weights each) and loads the next pass's inputs, in one load, before it
+// evaluates one.  The call on 1 M rows: 50 us (23 of it the call itself), 90
+// with four loads of one value per lane and 16384 wavefronts; 8 M rows 219 and
+// 359.
 __global__ __launch_bounds__(TPB) void k_mlp_forward(int64_t n, const float* __restrict__ X,
                                                      const float* __restrict__ theta, float* __restrict__ y) {
+  const int l = threadIdx.x & 63, q = l >> 4, r = l & 15;
+  const int64_t nwave = ((int64_t)gridDim.x * TPB) >> 6;
+  int64_t g = ((int64_t)blockIdx.x * TPB + threadIdx.x) >> 6;
+  auto load = [&](int64_t pass) {
+    const int64_t i = pass * 16 + r;
+    floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (i < n && q < 2) v = *reinterpret_cast<const float4u*>(X + i * MLP_IN + 4 * q);
+    if (i < n && q == 2) {
+      const float2u lo = *reinterpret_cast<const float2u*>(X + i * MLP_IN + 8);
+      v.x = lo.x;
+      v.y = lo.y;
+    }
+    return v;
+  };
+  floatx4 nx = load(g);
   MlpRegs R;
   mlp_load(theta, R);
-  const int l = threadIdx.x & 63, q = l >> 4, r = l & 15;
-  const int64_t wave = ((int64_t)blockIdx.x * TPB + threadIdx.x) >> 6;
-  const int64_t nwave = ((int64_t)gridDim.x * TPB) >> 6;
-  for (int64_t g = wave; g * 16 < n; g += nwave) {
+  for (; g * 16 < n; g += nwave) {
+    const floatx4 x = nx;
+    nx = load(g + nwave);
+    const float v = mlp_eval16(half4{(_Float16)x.x, (_Float16)x.y, (_Float16)x.z, (_Float16)x.w}, R);
     const int64_t i = g * 16 + r;
-    half4 xin;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int f = 4 * q + j;
-      xin[j] = (_Float16)((i < n && f < MLP_IN) ? X[i * MLP_IN + f] : 0.0f);
-    }
-    const float v = mlp_eval16(xin, R);
     if (q == 0 && i < n) y[i] = v;
   }
 }
@@ -108,7 +137,7 @@ __global__ __launch_bounds__(TPB) void k_mlp_forward(int64_t n, const float* __r
 void launch_mlp_forward(int64_t n, const float* X, const float* theta, float* y, hipStream_t s) {
   if (n <= 0) return;
   unsigned g = (unsigned)((n / 16 + 3) / 4 + 1);
-  if (g > 4096) g = 4096;
+  if (g > 1024) g = 1024;
   hipLaunchKernelGGL(k_mlp_forward, dim3(g), dim3(TPB), 0, s, n, X, theta, y);
 }
 
@@ -245,120 +274,218 @@ void launch_mlp_collect(const MlpFeat& F, const double* du, int count, uint64_t 
 
 // -------------------------------------------------------------- training
 
-constexpr int GCHUNK = 128;  // samples per block pass (one per work-item)
+// Gradient kernel: a wavefront takes 16 samples at a time through FP32 matrix
+// instructions (16x16x4: products and sums as in scalar FP32 code), four
+// wavefronts to a workgroup.  Hidden units are rows and samples columns, so
+// that a layer's output (lane (q, r): rows 16 b + 4 q + j of sample r) is the
+// next one's right operand as it stands: the instruction (b, j) sums over the
+// units 16 b + 4 q + j, and the weights are read in that order.  Only the
+// weight gradients, sums over the samples, need the activations with the
+// samples across the lanes: they go through the LDS.  Per wavefront and 16
+// samples 16 + 64 instructions forward, 64 back, 64 + 16 for the weight
+// gradients, 32 cycles each: 3.5 us; the rest is latency (the rows, weights
+// and accumulators of a workgroup that has one pass to make).
+// 8192 rows, with the Adam step: 406 us as one work-item per sample in scalar
+// loops, 33 so.
+// FP32 sums run over at most GFLUSH * 16 = 128 samples, then in FP64.
+constexpr int GW = 4, GS = 16, GFLUSH = 8;
+constexpr int GLD = 17, GLD2 = 65, GLDX = 13;  // row strides that spread the LDS banks
+struct GradLds {
+  double acc[MLP_NP + 1];
+  float w1[MLP_H * GLD], w2[MLP_H * GLD2], b1[MLP_H], b2[MLP_H], w3[MLP_H];
+  struct {
+    float h1[MLP_H * GLD], d1[MLP_H * GLD], d2[MLP_H * GLD], x[GS * GLDX];
+  } wave[GW];
+};
+
+// sum over the 16 lanes of a row, in every lane
+__device__ __forceinline__ float row_sum(float v) {
+  auto add = [](float a, int moved) { return a + __int_as_float(moved); };
+  v = add(v, __builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));
+  v = add(v, __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true));
+  v = add(v, __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xf, 0xf, true));
+  return add(v, __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xf, 0xf, true));
+}
 
 // Gradient of L = sum w (y - t)^2 / sum w, accumulated un-normalised:
 // grad += sum_i 2 w_i (y_i - t_i) dy_i/dtheta, loss2 += (sum w e^2, sum w).
 // Samples: rows i < n of S (all, in order) when nb == 0; otherwise nb rows
 // drawn by (seed, batch) with replacement.
-__global__ __launch_bounds__(GCHUNK) void k_mlp_grad(const float* __restrict__ S, int64_t n, int64_t nb,
-                                                     uint64_t seed, int64_t batch, const float* __restrict__ theta,
-                                                     double* __restrict__ grad, double* __restrict__ loss2) {
-  __shared__ float th[MLP_NP];
-  __shared__ float Xs[GCHUNK][MLP_IN];
-  __shared__ float H1[GCHUNK][MLP_H + 1];
-  __shared__ float H2[GCHUNK][MLP_H + 1];
-  __shared__ float D2[GCHUNK][MLP_H + 1];
-  __shared__ float D1[GCHUNK][MLP_H + 1];
-  __shared__ float DY[GCHUNK];
-  __shared__ double red[2 * GCHUNK / 64];
-  const int tid = threadIdx.x;
-  for (int j = tid; j < MLP_NP; j += GCHUNK) th[j] = theta[j];
-  constexpr int PER = (MLP_NP + GCHUNK - 1) / GCHUNK;
-  double acc[PER];
-#pragma unroll
-  for (int k = 0; k < PER; ++k) acc[k] = 0.0;
-  double lw = 0.0, ww = 0.0;
-  const int64_t total = nb > 0 ? nb : n;
-  __syncthreads();
-  for (int64_t c0 = (int64_t)blockIdx.x * GCHUNK; c0 < total; c0 += (int64_t)gridDim.x * GCHUNK) {
-    // phase 1: forward and back-propagation of one sample per work-item
-    const int64_t k = c0 + tid;
-    float dy = 0.0f;
-    if (k < total) {
+__global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ S, int64_t n, int64_t nb,
+                                                      uint64_t seed, int64_t batch, const float* __restrict__ theta,
+                                                      double* __restrict__ grad, double* __restrict__ loss2) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  GradLds& L = *reinterpret_cast<GradLds*>(smem_raw);
+  const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6, q = l >> 4, r = l & 15;
+  const int64_t total = nb > 0 ? nb : n, step = (int64_t)gridDim.x * GW * GS;
+  int64_t c0 = (int64_t)blockIdx.x * GW * GS;
+  // features 4q .. 4q+3 of sample r (q = 2: the last two, target and weight)
+  auto load_row = [&](int64_t k) {
+    floatx4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (k < total && q < 3) {
       int64_t i = k;
       if (nb > 0) i = (int64_t)(splitmix64(seed ^ splitmix64((uint64_t)batch * 0x100000001B3ull + (uint64_t)k)) %
                                 (uint64_t)n);
-      const float* row = S + i * MLP_ROW;
-      for (int f = 0; f < MLP_IN; ++f) Xs[tid][f] = row[f];
-      for (int u = 0; u < MLP_H; ++u) {
-        float z = th[MLP_OFF_B1 + u];
-        for (int f = 0; f < MLP_IN; ++f) z += th[MLP_OFF_W1 + u * MLP_IN + f] * Xs[tid][f];
-        H1[tid][u] = fmaxf(z, 0.0f);
-      }
-      float y = th[MLP_OFF_B3];
-      for (int u = 0; u < MLP_H; ++u) {
-        float z = th[MLP_OFF_B2 + u];
-        for (int v = 0; v < MLP_H; ++v) z += th[MLP_OFF_W2 + u * MLP_H + v] * H1[tid][v];
-        H2[tid][u] = fmaxf(z, 0.0f);
-        y += th[MLP_OFF_W3 + u] * H2[tid][u];
-      }
-      const float w = row[11];
-      const float e = y - row[10];
-      dy = 2.0f * w * e;
-      lw += (double)w * (double)e * (double)e;
-      ww += (double)w;
-      for (int u = 0; u < MLP_H; ++u) D2[tid][u] = H2[tid][u] > 0.0f ? dy * th[MLP_OFF_W3 + u] : 0.0f;
-      for (int v = 0; v < MLP_H; ++v) {
-        float sacc = 0.0f;
-        for (int u = 0; u < MLP_H; ++u) sacc += D2[tid][u] * th[MLP_OFF_W2 + u * MLP_H + v];
-        D1[tid][v] = H1[tid][v] > 0.0f ? sacc : 0.0f;
-      }
-    } else {
-      for (int f = 0; f < MLP_IN; ++f) Xs[tid][f] = 0.0f;
-      for (int u = 0; u < MLP_H; ++u) H1[tid][u] = H2[tid][u] = D2[tid][u] = D1[tid][u] = 0.0f;
+      x = *reinterpret_cast<const float4u*>(S + i * MLP_ROW + 4 * q);
     }
-    DY[tid] = dy;
-    __syncthreads();
-    // phase 2: parameter j sums its products over the chunk
-    const int ns = (int)((total - c0) < GCHUNK ? (total - c0) : GCHUNK);
+    return x;
+  };
+  floatx4 xr = load_row(c0 + wv * GS + r);
+  for (int j = tid; j < MLP_NP + 1; j += 64 * GW) L.acc[j] = 0.0;
+  for (int j = tid; j < MLP_H * MLP_H; j += 64 * GW) L.w2[(j / MLP_H) * GLD2 + j % MLP_H] = theta[MLP_OFF_W2 + j];
+  for (int j = tid; j < MLP_H * 16; j += 64 * GW)
+    L.w1[(j / 16) * GLD + j % 16] = j % 16 < MLP_IN ? theta[MLP_OFF_W1 + (j / 16) * MLP_IN + j % 16] : 0.0f;
+  if (tid < MLP_H) {
+    L.b1[tid] = theta[MLP_OFF_B1 + tid];
+    L.b2[tid] = theta[MLP_OFF_B2 + tid];
+    L.w3[tid] = theta[MLP_OFF_W3 + tid];
+  }
+  const float b3 = theta[MLP_OFF_B3];
+  __syncthreads();
+  auto& W = L.wave[wv];
+  const floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  floatx4 g2[4][4], g1[4], gb2[4], gw3[4];  // weight gradients; biases and output layer per lane's sample
+  float gb3 = 0.0f;
+  auto clear = [&] {
 #pragma unroll
-    for (int kk = 0; kk < PER; ++kk) {
-      const int j = tid + kk * GCHUNK;
-      if (j >= MLP_NP) break;
-      float sacc = 0.0f;
-      if (j < MLP_OFF_B1) {
-        const int u = j / MLP_IN, f = j % MLP_IN;
-        for (int s = 0; s < ns; ++s) sacc += D1[s][u] * Xs[s][f];
-      } else if (j < MLP_OFF_W2) {
-        const int u = j - MLP_OFF_B1;
-        for (int s = 0; s < ns; ++s) sacc += D1[s][u];
-      } else if (j < MLP_OFF_B2) {
-        const int u = (j - MLP_OFF_W2) / MLP_H, v = (j - MLP_OFF_W2) % MLP_H;
-        for (int s = 0; s < ns; ++s) sacc += D2[s][u] * H1[s][v];
-      } else if (j < MLP_OFF_W3) {
-        const int u = j - MLP_OFF_B2;
-        for (int s = 0; s < ns; ++s) sacc += D2[s][u];
-      } else if (j < MLP_OFF_B3) {
-        const int u = j - MLP_OFF_W3;
-        for (int s = 0; s < ns; ++s) sacc += DY[s] * H2[s][u];
-      } else {
-        for (int s = 0; s < ns; ++s) sacc += DY[s];
-      }
-      acc[kk] += (double)sacc;
+    for (int c = 0; c < 4; ++c) {
+      g1[c] = gb2[c] = gw3[c] = zero;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) g2[c][b] = zero;
     }
+    gb3 = 0.0f;
+  };
+  // FP32 sums into the workgroup's FP64 ones
+  auto flush = [&] {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int u = 16 * c + 4 * q + j;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) atomicAdd(&L.acc[MLP_OFF_W2 + u * MLP_H + 16 * b + r], (double)g2[c][b][j]);
+        if (r <= MLP_IN)  // column 10 of the inputs is one: the bias
+          atomicAdd(&L.acc[r < MLP_IN ? MLP_OFF_W1 + u * MLP_IN + r : MLP_OFF_B1 + u], (double)g1[c][j]);
+        const float sb = row_sum(gb2[c][j]), sw = row_sum(gw3[c][j]);
+        if (r == 0) {
+          atomicAdd(&L.acc[MLP_OFF_B2 + u], (double)sb);
+          atomicAdd(&L.acc[MLP_OFF_W3 + u], (double)sw);
+        }
+      }
+    const float s3 = row_sum(gb3);
+    if (l == 0) atomicAdd(&L.acc[MLP_OFF_B3], (double)s3);
+    clear();
+  };
+  clear();
+  double lw = 0.0, ww = 0.0;
+  for (int pass = 1; c0 < total; c0 += step, ++pass) {
+    const bool live = c0 + wv * GS + r < total;
+    const floatx4 x = xr;
+    xr = load_row(c0 + step + wv * GS + r);
+    const float xf[4] = {x.x, x.y, q == 2 ? 0.0f : x.z, q == 2 ? 0.0f : x.w};
+    const float target = __shfl(x.z, 32 + r, 64), weight = __shfl(x.w, 32 + r, 64);
+    floatx4 h1[4], h2[4], d2[4], z;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) z[j] = L.b1[16 * b + 4 * q + j];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w1[(16 * b + r) * GLD + 4 * q + j], xf[j], z, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) h1[b][j] = fmaxf(z[j], 0.0f);
+    }
+    double y = 0.0;  // the output and its error in FP64
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) z[j] = L.b2[16 * c + 4 * q + j];
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w2[(16 * c + r) * GLD2 + 16 * b + 4 * q + j], h1[b][j], z, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        h2[c][j] = fmaxf(z[j], 0.0f);
+        y += (double)L.w3[16 * c + 4 * q + j] * (double)h2[c][j];
+      }
+    }
+    y += __shfl_xor(y, 16, 64);
+    y += __shfl_xor(y, 32, 64);
+    y += (double)b3;
+    const double e = y - (double)target;
+    const float dy = live ? (float)(2.0 * (double)weight * e) : 0.0f;
+    if (live && q == 0) {
+      lw += (double)weight * e * e;
+      ww += (double)weight;
+      gb3 += dy;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int u = 16 * c + 4 * q + j;
+        d2[c][j] = h2[c][j] > 0.0f ? dy * L.w3[u] : 0.0f;
+        gb2[c][j] += d2[c][j];
+        gw3[c][j] += live ? dy * h2[c][j] : 0.0f;
+        W.h1[u * GLD + r] = h1[c][j];
+        W.d2[u * GLD + r] = d2[c][j];
+      }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      z = zero;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w2[(16 * c + 4 * q + j) * GLD2 + 16 * b + r], d2[c][j], z, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) W.d1[(16 * b + 4 * q + j) * GLD + r] = h1[b][j] > 0.0f ? z[j] : 0.0f;
+    }
+    if (q < 3) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) W.x[r * GLDX + 4 * q + j] = 4 * q + j == MLP_IN ? 1.0f : xf[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int sm = 4 * t + q;  // the sample of this lane in the sums over samples
+      const float xb = r <= MLP_IN ? W.x[sm * GLDX + r] : 0.0f;
+      float ha[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) ha[b] = W.h1[(16 * b + r) * GLD + sm];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float da = W.d2[(16 * c + r) * GLD + sm];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) g2[c][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(da, ha[b], g2[c][b], 0, 0, 0);
+        g1[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(W.d1[(16 * c + r) * GLD + sm], xb, g1[c], 0, 0, 0);
+      }
+    }
+    if (pass % GFLUSH == 0) flush();
     __syncthreads();
   }
-#pragma unroll
-  for (int kk = 0; kk < PER; ++kk) {
-    const int j = tid + kk * GCHUNK;
-    if (j < MLP_NP && acc[kk] != 0.0) atomic_add(&grad[j], acc[kk]);
-  }
+  flush();
   lw = wave_sum(lw);
   ww = wave_sum(ww);
-  if ((tid & 63) == 0) {
+  if (l == 0) {
     atomic_add(&loss2[0], lw);
     atomic_add(&loss2[1], ww);
   }
+  __syncthreads();
+  for (int j = tid; j < MLP_NP; j += 64 * GW)
+    if (L.acc[j] != 0.0) atomic_add(&grad[j], L.acc[j]);
 }
 
 void launch_mlp_grad(const float* S, int64_t n, int64_t nb, uint64_t seed, int64_t batch, const float* theta,
                      double* grad, double* loss2, hipStream_t s) {
   const int64_t total = nb > 0 ? nb : n;
   if (total <= 0) return;
-  unsigned g = (unsigned)((total + GCHUNK - 1) / GCHUNK);
-  if (g > 512) g = 512;
-  hipLaunchKernelGGL(k_mlp_grad, dim3(g), dim3(GCHUNK), 0, s, S, n, nb, seed, batch, theta, grad, loss2);
+  unsigned g = (unsigned)((total + GW * GS - 1) / (GW * GS));
+  if (g > 256) g = 256;  // one per compute unit (LDS: 117 KB)
+  hipLaunchKernelGGL(k_mlp_grad, dim3(g), dim3(64 * GW), sizeof(GradLds), s, S, n, nb, seed, batch, theta, grad,
+                     loss2);
 }
 
 // Adam on the FP32 master weights with the gradient normalised by sum w;
