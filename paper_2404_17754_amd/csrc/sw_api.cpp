@@ -2052,28 +2052,36 @@ static int fit_one(sw_ctx* ctx, int32_t n_rec, int64_t n_steps, const double* co
   fit_layout(n_rec, n_steps, stride, cv, &f);
   const int np = 3 * n_rec, nb = (int)(n_steps / stride), L = n_shift, ncol = 4 * nb;
   launch_fit_weights(np, n_steps, obs, f.o2, f.w, s);
-  launch_fit_gram(green, obs, np, stride, nb, f.w, f.C, s);
+  // the response's place is free until the coefficients are known
+  launch_fit_gram(green, obs, np, stride, nb, f.w, f.C, f.U, n_steps * np, s);
   LAUNCHED();
   std::vector<double> C((size_t)ncol * ncol);
   HIPC(hipMemcpyAsync(C.data(), f.C, C.size() * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPC(hipStreamSynchronize(s));
-  // normal equations from block inner products (shift l delays by l blocks)
+  // normal equations from block inner products (shift l delays by l blocks):
+  // A(j l, j2 l2) = sum over i <= nb - 1 - l of C(j i, j2 i + l - l2), running
+  // sums along the diagonals of each pair's block
   const int n = 3 * L;
-  std::vector<double> A((size_t)n * n, 0.0), bv(n, 0.0), V, w, cvec(n);
-  for (int j = 0; j < 3; ++j)
+  std::vector<double> A((size_t)n * n, 0.0), bv(n, 0.0), cvec(n);
+  for (int j = 0; j < 3; ++j) {
     for (int l = 0; l < L; ++l) {
       double acc = 0.0;
       for (int b = l; b < nb; ++b) acc += C[(size_t)(j * nb + b - l) * ncol + 3 * nb + b];
       bv[j * L + l] = acc;
-      for (int j2 = 0; j2 < 3; ++j2)
-        for (int l2 = 0; l2 < L; ++l2) {
-          double a = 0.0;
-          for (int b = std::max(l, l2); b < nb; ++b) a += C[(size_t)(j * nb + b - l) * ncol + j2 * nb + b - l2];
-          A[(size_t)(j * L + l) * n + j2 * L + l2] = a;
-        }
     }
-  sym_eig(n, A, V, w);
-  const int kept = truncated_solve(n, V, w, bv.data(), cvec.data(), rel_cut);
+    for (int j2 = 0; j2 < 3; ++j2)
+      for (int d = -(L - 1); d < L; ++d) {  // l - l2
+        double acc = 0.0;
+        const int i0 = std::max(0, -d);     // first block of j whose partner i + d exists
+        for (int i = i0; i < nb && i + d < nb; ++i) {
+          acc += C[(size_t)(j * nb + i) * ncol + j2 * nb + i + d];
+          // the last term of these shifts
+          const int l = nb - 1 - i, l2 = l - d;
+          if (l < L && l2 < L) A[(size_t)(j * L + l) * n + j2 * L + l2] = acc;
+        }
+      }
+  }
+  const int kept = sym_pinv_solve(n, A, bv.data(), cvec.data(), rel_cut);
   for (int i = 0; i < n; ++i) c_host[i] = cvec[i];
   if (rank) *rank = kept;
   // response to the fitted input and its misfit

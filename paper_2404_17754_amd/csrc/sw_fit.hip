@@ -17,18 +17,27 @@
 
 namespace sw {
 
-// o2[pair] = sum_t obs[t][pair]^2, one workgroup per (receiver, component)
-__global__ __launch_bounds__(TPB) void k_fit_pair_norms(int n_pairs, int64_t n_steps, const double* __restrict__ obs,
-                                                        double* __restrict__ o2) {
-  __shared__ double sh[TPB / 64];
-  const int pr = blockIdx.x;
+// o2[pair] = sum_t obs[t][pair]^2: 16 pairs by 64 times a workgroup, so that a
+// load of the records, which lie pair by pair within a time, is whole lines
+constexpr int NP = 16, NTIME = 64;
+__global__ __launch_bounds__(NP* NTIME) void k_fit_pair_norms(int n_pairs, int64_t n_steps,
+                                                              const double* __restrict__ obs,
+                                                              double* __restrict__ o2) {
+  __shared__ double sh[NTIME][NP + 1];
+  const int px = threadIdx.x % NP, ty = threadIdx.x / NP, pr = blockIdx.x * NP + px;
   double s = 0.0;
-  for (int64_t t = threadIdx.x; t < n_steps; t += TPB) {
-    const double o = obs[t * n_pairs + pr];
-    s += o * o;
+  if (pr < n_pairs)
+    for (int64_t t = ty; t < n_steps; t += NTIME) {
+      const double o = obs[t * n_pairs + pr];
+      s += o * o;
+    }
+  sh[ty][px] = s;
+  __syncthreads();
+  if (threadIdx.x < NP && pr < n_pairs) {
+    s = 0.0;
+    for (int k = 0; k < NTIME; ++k) s += sh[k][px];
+    o2[pr] = s;
   }
-  s = block_sum(s, sh);
-  if (threadIdx.x == 0) o2[pr] = s;
 }
 
 // w[pair] = 1 / o2[pair], zero for pairs whose norm is <= 1e-12 of the
@@ -56,7 +65,7 @@ __global__ __launch_bounds__(TPB) void k_fit_weights(int n_pairs, const double* 
   }
 }
 
-// Block column `col` (< 4 nb) at row (pair, r): Green's block (j, b) for
+// Block column `col` (< 4 nb) at row (r, pair): Green's block (j, b) for
 // col = j nb + b (j < 3), observed block b for col = 3 nb + b.
 struct FitSrc {
   const double* g[3];
@@ -64,84 +73,171 @@ struct FitSrc {
   int n_pairs, m, nb;
 };
 
-__device__ __forceinline__ double fit_x(const FitSrc& S, int col, int pair, int r) {
+__device__ __forceinline__ const double* fit_col(const FitSrc& S, int col) {
   const int j = col / S.nb, b = col - j * S.nb;
-  const double* src = j < 3 ? S.g[j] : S.obs;
-  return src[(int64_t)(b * S.m + r) * S.n_pairs + pair];
+  return (j < 3 ? S.g[j] : S.obs) + (int64_t)b * S.m * S.n_pairs;
 }
 
-// C = X^T diag(w) X for the 4 nb block columns, 16 x 16 output tiles, rows
-// (pair, r) streamed through LDS in chunks; tiles below the diagonal skip.
-constexpr int FT = 16, FK = 64;
-__global__ __launch_bounds__(FT* FT) void k_fit_gram(FitSrc S, const double* __restrict__ w, int ncol,
-                                                     double* __restrict__ C) {
-  const int ta = blockIdx.y, tb = blockIdx.x;
-  if (tb < ta) return;
-  __shared__ double xa[FK][FT], xb[FK][FT];
-  const int a = threadIdx.x / FT, bcol = threadIdx.x % FT;
-  const int ca = ta * FT + a, cb = tb * FT + bcol;
-  const int64_t n_rows = (int64_t)S.n_pairs * S.m;
-  double acc = 0.0;
-  for (int64_t k0 = 0; k0 < n_rows; k0 += FK) {
-    for (int e = threadIdx.x; e < FK * FT; e += FT * FT) {
-      const int kk = e / FT, cc = e % FT;
-      const int64_t row = k0 + kk;
-      double va = 0.0, vb = 0.0;
-      if (row < n_rows) {
-        const int pair = (int)(row / S.m), r = (int)(row - (int64_t)pair * S.m);
-        const double wr = w[pair];
-        if (ta * FT + cc < ncol) va = wr * fit_x(S, ta * FT + cc, pair, r);
-        if (tb * FT + cc < ncol) vb = fit_x(S, tb * FT + cc, pair, r);
-      }
-      xa[kk][cc] = va;
-      xb[kk][cc] = vb;
+// C = X^T diag(w) X for the 4 nb block columns, on the FP64 matrix
+// instructions (16x16x4), 64 x 64 output tiles (the upper ones), rows in
+// chunks of FK pairs at one time r, which are contiguous in the records.  A
+// workgroup takes a share (blockIdx.y) of the chunks, and the shares' results
+// are added in their order by k_fit_sum, since the few tiles of a fit (10 at
+// 200 columns) would leave most of the chip idle.  Four wavefronts of 32 x 32.
+// 200 columns of 24000 rows: 1354 us with one output per work-item and rows
+// read pair by pair (one value of a line), 134 so.
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int FT = 64, FK = 32, FLD = FK + 1;
+__global__ __launch_bounds__(256) void k_fit_gram(FitSrc S, const double* __restrict__ w, int ncol, int nt,
+                                                  double* __restrict__ part) {
+  __shared__ double xa[FT * FLD], xb[FT * FLD];
+  // tile pair (ta <= tb) of the upper triangle
+  int ta = 0, rest = blockIdx.x;
+  while (rest >= nt - ta) rest -= nt - ta++;
+  const int tb = ta + rest;
+  const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
+  const int pchunks = (S.n_pairs + FK - 1) / FK, chunks = S.m * pchunks;
+  const int c0 = (int)((int64_t)chunks * blockIdx.y / gridDim.y), c1 = (int)((int64_t)chunks * (blockIdx.y + 1) / gridDim.y);
+  // each work-item loads pair kk of columns row0, row0 + 8, ...
+  const int kk = tid % FK, row0 = tid / FK;
+  constexpr int PER = FT * FK / 256;
+  const double *pa[PER], *pb[PER];  // null past the last column
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int ca = ta * FT + row0 + q * (256 / FK), cb = tb * FT + row0 + q * (256 / FK);
+    pa[q] = ca < ncol ? fit_col(S, ca) : nullptr;
+    pb[q] = cb < ncol ? fit_col(S, cb) : nullptr;
+  }
+  double ra[PER], rb[PER];
+  auto load = [&](int c) {
+    const int r = c / pchunks, pair = (c - r * pchunks) * FK + kk;
+    const bool in = pair < S.n_pairs;
+    const double wp = in ? w[pair] : 0.0;
+    const int64_t at = (int64_t)r * S.n_pairs + pair;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      ra[q] = in && pa[q] ? wp * pa[q][at] : 0.0;
+      rb[q] = in && pb[q] ? pb[q][at] : 0.0;
+    }
+  };
+  doublex4 acc[2][2] = {};
+  const int a0 = (wv >> 1) * 32 + (l & 15), b0 = (wv & 1) * 32 + (l & 15), k0 = l >> 4;
+  if (c0 < c1) load(c0);
+  for (int c = c0; c < c1; ++c) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      xa[(row0 + q * (256 / FK)) * FLD + kk] = ra[q];
+      xb[(row0 + q * (256 / FK)) * FLD + kk] = rb[q];
     }
     __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < FK; ++kk) acc += xa[kk][a] * xb[kk][bcol];
-    __syncthreads();
+    if (c + 1 < c1) load(c + 1);
+#pragma unroll
+    for (int k = 0; k < FK; k += 4) {
+      double av[2], bv[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        av[i] = xa[(a0 + 16 * i) * FLD + k + k0];
+        bv[i] = xb[(b0 + 16 * i) * FLD + k + k0];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
+    }
   }
-  // each symmetric pair written by one thread (in a diagonal tile the
-  // (a, b) and (b, a) threads round differently), so C is deterministic
-  if (ca < ncol && cb < ncol && (tb > ta || bcol >= a)) {
-    C[(int64_t)ca * ncol + cb] = acc;
-    C[(int64_t)cb * ncol + ca] = acc;
-  }
+  // result rows 4 v + l / 16, column l % 16 of each 16 x 16 block
+  double* out = part + (size_t)blockIdx.y * ncol * ncol;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = ta * FT + (wv >> 1) * 32 + 16 * i + 4 * v + (l >> 4), col = tb * FT + b0 + 16 * j;
+        if (row < ncol && col < ncol && row <= col) out[(size_t)row * ncol + col] = acc[i][j][v];
+      }
 }
 
-// U[t][pair] = sum_j sum_{l <= t/m, l < n_shift} c[j][l] G_j[t - l m][pair]
-__global__ __launch_bounds__(TPB) void k_fit_response(FitSrc S, int n_shift, int64_t n_steps,
-                                                      const double* __restrict__ c, double* __restrict__ U) {
-  const int64_t n = n_steps * S.n_pairs;
-  for (int64_t e = (int64_t)blockIdx.x * TPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * TPB) {
-    const int64_t t = e / S.n_pairs;
-    const int pair = (int)(e - t * S.n_pairs);
-    const int lmax = (int)min((int64_t)n_shift - 1, t / S.m);
-    double s = 0.0;
-    for (int j = 0; j < 3; ++j)
-      for (int l = 0; l <= lmax; ++l) s += c[j * n_shift + l] * S.g[j][(t - (int64_t)l * S.m) * S.n_pairs + pair];
-    U[e] = s;
+// C's upper triangle = the sum of the shares in their order, mirrored (the
+// (a, b) and (b, a) products round differently: one of them serves both).
+// part may be C itself when there is one share.
+__global__ __launch_bounds__(TPB) void k_fit_sum(int ncol, int shares, const double* part, double* C) {
+  const int col = blockIdx.x * TPB + threadIdx.x, row = blockIdx.y;
+  if (col >= ncol || col < row) return;
+  const size_t at = (size_t)row * ncol + col;
+  double s = 0.0;
+  for (int k = 0; k < shares; ++k) s += part[(size_t)k * ncol * ncol + at];
+  C[at] = s;
+  C[(size_t)col * ncol + row] = s;
+}
+
+// U[t][pair] = sum_j sum_{l <= t/m, l < n_shift} c[j][l] G_j[t - l m][pair]:
+// at the same (r, pair) the times b m + r are a convolution over the blocks b;
+// a work-item makes OB consecutive blocks, so that a record value is loaded
+// once for OB results.  cp: the coefficients with zeros at both ends.  50
+// blocks and shifts, 1200 pairs: 108 us with a load per product, 24 so.
+constexpr int OB = 8;
+__global__ __launch_bounds__(TPB) void k_fit_response(FitSrc S, int n_shift, const double* __restrict__ c,
+                                                      double* __restrict__ U) {
+  extern __shared__ double cp[];
+  const int ld = n_shift + 2 * OB;
+  for (int i = threadIdx.x; i < 3 * ld; i += TPB) {
+    const int j = i / ld, k = i - j * ld - OB;
+    cp[i] = k >= 0 && k < n_shift ? c[j * n_shift + k] : 0.0;
   }
+  __syncthreads();
+  const int64_t stride = (int64_t)S.m * S.n_pairs, x = (int64_t)blockIdx.x * TPB + threadIdx.x;
+  if (x >= stride) return;
+  const int b0 = blockIdx.y * OB;
+  double acc[OB];
+#pragma unroll
+  for (int o = 0; o < OB; ++o) acc[o] = 0.0;
+  // source block i reaches result block b0 + o through shift b0 + o - i
+  const int i0 = max(0, b0 - n_shift + 1), i1 = min(S.nb, b0 + OB);
+  for (int j = 0; j < 3; ++j) {
+    const double* g = S.g[j] + x;
+    const double* cj = cp + j * ld + OB + b0;
+#pragma unroll 4
+    for (int i = i0; i < i1; ++i) {
+      const double v = g[i * stride];
+#pragma unroll
+      for (int o = 0; o < OB; ++o) acc[o] += cj[o - i] * v;
+    }
+  }
+#pragma unroll
+  for (int o = 0; o < OB; ++o)
+    if (b0 + o < S.nb) U[(b0 + o) * stride + x] = acc[o];
 }
 
 void launch_fit_weights(int n_pairs, int64_t n_steps, const double* obs, double* o2, double* w, hipStream_t s) {
-  hipLaunchKernelGGL(k_fit_pair_norms, dim3(n_pairs), dim3(TPB), 0, s, n_pairs, n_steps, obs, o2);
+  hipLaunchKernelGGL(k_fit_pair_norms, dim3((n_pairs + NP - 1) / NP), dim3(NP * NTIME), 0, s, n_pairs, n_steps, obs,
+                     o2);
   hipLaunchKernelGGL(k_fit_weights, dim3(1), dim3(TPB), 0, s, n_pairs, o2, w);
 }
 
 void launch_fit_gram(const double* const g[3], const double* obs, int n_pairs, int m, int nb, const double* w,
-                     double* C, hipStream_t s) {
+                     double* C, double* scratch, int64_t scratch_len, hipStream_t s) {
   FitSrc S{{g[0], g[1], g[2]}, obs, n_pairs, m, nb};
-  const int ncol = 4 * nb, nt = (ncol + FT - 1) / FT;
-  hipLaunchKernelGGL(k_fit_gram, dim3(nt, nt), dim3(FT * FT), 0, s, S, w, ncol, C);
+  const int ncol = 4 * nb, nt = (ncol + FT - 1) / FT, tiles = nt * (nt + 1) / 2;
+  // shares: two workgroups per compute unit, as far as there are chunks and
+  // room for the shares' results
+  const int64_t chunks = (int64_t)m * ((n_pairs + FK - 1) / FK), room = scratch_len / ((int64_t)ncol * ncol);
+  int64_t shares = (512 + tiles - 1) / tiles;
+  shares = shares < chunks ? shares : chunks;
+  shares = shares < room ? shares : room;
+  double* part = shares > 1 ? scratch : C;
+  if (shares < 1) shares = 1;
+  hipLaunchKernelGGL(k_fit_gram, dim3(tiles, (unsigned)shares), dim3(256), 0, s, S, w, ncol, nt, part);
+  hipLaunchKernelGGL(k_fit_sum, dim3((ncol + TPB - 1) / TPB, ncol), dim3(TPB), 0, s, ncol, (int)shares, part, C);
 }
 
 void launch_fit_response(const double* const g[3], int n_pairs, int m, int n_shift, int64_t n_steps,
                          const double* c, double* U, hipStream_t s) {
-  FitSrc S{{g[0], g[1], g[2]}, nullptr, n_pairs, m, 0};
-  unsigned gsz = nblocks(n_steps * n_pairs);
-  if (gsz > 4096) gsz = 4096;
-  hipLaunchKernelGGL(k_fit_response, dim3(gsz), dim3(TPB), 0, s, S, n_shift, n_steps, c, U);
+  FitSrc S{{g[0], g[1], g[2]}, nullptr, n_pairs, m, (int)(n_steps / m)};
+  const size_t lds = 3 * (size_t)(n_shift + 2 * OB) * sizeof(double);
+  hipLaunchKernelGGL(k_fit_response, dim3(nblocks((int64_t)m * n_pairs), (S.nb + OB - 1) / OB), dim3(TPB), lds, s, S,
+                     n_shift, c, U);
 }
 
 }  // namespace sw

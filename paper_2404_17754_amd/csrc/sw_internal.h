@@ -362,9 +362,10 @@ void launch_proj_store(int64_t n, const double* x, const double* b, const double
 // w[pair] = 1 / |obs_pair|^2 (zero for silent pairs); o2: n_pairs scratch
 void launch_fit_weights(int n_pairs, int64_t n_steps, const double* obs, double* o2, double* w, hipStream_t s);
 // C (4 nb x 4 nb) = weighted Gram matrix of the stride-m blocks of the three
-// Green's records and the observed record, records [t][pair]
+// Green's records and the observed record, records [t][pair]; scratch: room
+// for partial results (used as far as it reaches; may be none)
 void launch_fit_gram(const double* const g[3], const double* obs, int n_pairs, int m, int nb, const double* w,
-                     double* C, hipStream_t s);
+                     double* C, double* scratch, int64_t scratch_len, hipStream_t s);
 // U[t][pair] = sum_{j,l} c[j][l] g_j[t - l m][pair]
 void launch_fit_response(const double* const g[3], int n_pairs, int m, int n_shift, int64_t n_steps,
                          const double* c, double* U, hipStream_t s);
