@@ -6,8 +6,8 @@
 //      + C_abs v  (one EBE pass with two inputs + one face pass)
 //   2. ||b||^2, tolerance, initial guess
 //   3. preconditioned CG on A du = b in chunks of iterations that run with
-//      no host round trip (device-side convergence test), two or three kernels
-//      an iteration (see two_kernel_cg); FP64, or FP32 inner
+//      no host round trip (device-side convergence test), one to three kernels
+//      an iteration (see one_kernel_cg, two_kernel_cg); FP64, or FP32 inner
 //      solves inside FP64 iterative refinement
 //   4. FP64 true residual ||b - A du|| / ||b|| checked against rtol
 //   5. Newmark update of (u, v, a), increment history, receiver record.
@@ -20,6 +20,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <new>
 #include <stdexcept>
 #include <vector>
@@ -182,6 +183,10 @@ struct sw_case {
   // cases have one of their own, the FP32 one lies in p, free in an inner solve
   double* p_alt = nullptr;
   float* p32_alt = nullptr;
+  // further vectors of one-kernel iterations (s twice, w three times), in
+  // the precision of the CG; null where the mesh is too large for them
+  double* one64[5] = {};
+  float* one32[5] = {};
   uint16_t* p16;  // SW_MIXED_FP16: the inner CG's direction in bfloat16 (else null)
   // flexible outer CG (SW_MIXED_FP32_FLEX): directions and their images of
   // the current and the previous iteration (by parity), dot products
@@ -694,6 +699,14 @@ static size_t case_layout(const sw_mesh* m, const sw_case_desc* d, Carver& cv, s
   if (mixed)
     for (int i = 0; i < 5; ++i) f32[i] = cv.take<float>(nd);
   double* p_alt = mixed || d->deterministic ? nullptr : cv.take<double>(nd);
+  double* one64[4] = {nullptr, nullptr, nullptr, nullptr};
+  float* one32[3] = {nullptr, nullptr, nullptr};
+  if (!d->deterministic && d->precision != SW_MIXED_FP16 && one_kernel_cg(m->dev, 0, mixed)) {
+    if (mixed)
+      for (float*& v : one32) v = cv.take<float>(nd);
+    else
+      for (double*& v : one64) v = cv.take<double>(nd);
+  }
   uint16_t* p16 = d->precision == SW_MIXED_FP16 ? cv.take<uint16_t>(nd) : nullptr;
   double* fvec[4] = {nullptr, nullptr, nullptr, nullptr};
   double* fdots = nullptr;
@@ -755,6 +768,15 @@ static size_t case_layout(const sw_mesh* m, const sw_case_desc* d, Carver& cv, s
     c->q32 = f32[4];
     c->p_alt = p_alt;
     c->p32_alt = mixed ? reinterpret_cast<float*>(vec[7]) : nullptr;
+    if (one32[0]) {
+      c->one32[0] = reinterpret_cast<float*>(vec[7]);
+      c->one32[1] = c->one32[0] + nd;
+      for (int i = 0; i < 3; ++i) c->one32[2 + i] = one32[i];
+    }
+    if (one64[0]) {
+      c->one64[0] = p_alt;
+      for (int i = 0; i < 4; ++i) c->one64[1 + i] = one64[i];
+    }
     c->p16 = p16;
     c->fp[0] = fvec[0];
     c->fp[1] = fvec[1];
@@ -1143,13 +1165,46 @@ int read_ctl(sw_case* c, CgCtl* dev, CgCtl* host) {
   return c->ctx->prof.on ? prof_flush(c->ctx) : SW_OK;
 }
 
-// Whether the case's iterations run as two kernels now.  Three kernels serve
-// the deterministic and the 16-bit modes, and the profiler, which times the
-// operator, the update and the direction each for itself.
+// Whether the case's iterations run as two kernels now, if not as one.  Three
+// kernels serve the deterministic and the 16-bit modes, and the profiler,
+// which times the operator, the update and the direction each for itself.
 template <bool F32>
 bool two_kernel(const sw_case* c) {
   return !c->ctx->prof.on && !c->det && !(F32 && c->p16) &&
          two_kernel_cg(c->mesh->dev, F32 ? case_grid_cap(c) : 0, F32);
+}
+
+// Whether they run as one kernel.
+template <bool F32>
+bool one_kernel(const sw_case* c) {
+  return !c->ctx->prof.on && (F32 ? c->one32[0] != nullptr : c->one64[0] != nullptr) &&
+         one_kernel_cg(c->mesh->dev, F32 ? case_grid_cap(c) : 0, F32);
+}
+
+// Kernel `iter` of a solve in one-kernel iterations: r, z and the first two
+// further vectors are the buffers of r and s, the other three those of w.
+template <bool F32>
+void one_cg_iteration(sw_case* c, CgCtl* ctl, int iter, hipStream_t s) {
+  using T = std::conditional_t<F32, float, double>;
+  T *r[2], *p, *x, *const* o;
+  if constexpr (F32) {
+    r[0] = c->r32, r[1] = c->z32, p = c->p32, x = c->d32, o = c->one32;
+  } else {
+    r[0] = c->r, r[1] = c->z, p = c->p, x = c->x, o = c->one64;
+  }
+  const int par = iter & 1, old = iter == 0 ? 0 : par ^ 1;
+  OneCg<T> v;
+  v.r_old = r[old], v.r_new = r[par];
+  v.s_old = o[par ^ 1], v.s_new = o[par];
+  v.w_old = o[2 + (iter + 2) % 3], v.w_clear = o[2 + (iter + 1) % 3];
+  v.p = p, v.x = x;
+  T* w = o[2 + iter % 3];
+  if constexpr (F32)
+    launch_tile_cg_f32(c->mesh->dev, c->emat, c->mats, args_f32(c, SW_OP_A, c->r32, w), v, c->pinv16, ctl, iter,
+                       c->max_iter, s);
+  else
+    launch_tile_cg_f64(c->mesh->dev, c->emat, c->mats, args_f64(c, SW_OP_A, c->r, w), v, c->pinv64, ctl, iter,
+                       c->max_iter, s);
 }
 
 // One CG iteration of the single-case solve on stream s: the operator pass
@@ -1161,6 +1216,11 @@ int cg_iteration(sw_case* c, CgCtl* ctl, int iter, int iter_abs, hipStream_t s, 
   const int64_t nn = c->mesh->n_nodes;
   sw_ctx* cx = c->ctx;
   int rc;
+  if (one_kernel<F32>(c)) {
+    one_cg_iteration<F32>(c, ctl, iter, s);
+    LAUNCHED();
+    return SW_OK;
+  }
   if (two_kernel<F32>(c)) {
     const MeshDev& m = c->mesh->dev;
     const int par = iter & 1;
@@ -1220,6 +1280,8 @@ int capture_stream(sw_ctx* cx, hipStream_t* out) {
 // about as much for a whole graph, while an iteration of a small mesh takes
 // 14 us on the GPU and a skipped one 4 us.
 constexpr int GRAPH_ITERS = 8;
+// the same for one-kernel iterations, whose arguments repeat every six
+constexpr int GRAPH_ITERS_ONE = 6;
 
 // Instantiated graph of GRAPH_ITERS CG iterations of this case's solve (from
 // an even iteration past the first: the direction kernels take the iteration
@@ -1242,7 +1304,8 @@ int cg_graph(sw_case* c, CgCtl* ctl, hipGraphExec_t* out) {
   int rc = capture_stream(c->ctx, &cs);
   if (rc) return rc;
   HIPC(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-  for (int k = 0; k < GRAPH_ITERS && !rc; ++k) rc = cg_iteration<F32>(c, ctl, 2 + k, -1, cs, false);
+  const int n = one_kernel<F32>(c) ? GRAPH_ITERS_ONE : GRAPH_ITERS;
+  for (int k = 0; k < n && !rc; ++k) rc = cg_iteration<F32>(c, ctl, 2 + k, -1, cs, false);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(cs, &g);
   if (rc) return rc;
@@ -1266,19 +1329,29 @@ int cg_loop(sw_case* c, CgCtl* ctl, int iter_base, int expected, int* iters_out)
   hipStream_t s = c->ctx->stream;
   sw_ctx* cx = c->ctx;
   int it = 0;
+  const bool one = one_kernel<F32>(c), two = two_kernel<F32>(c);
+  const int graph_iters = one ? GRAPH_ITERS_ONE : GRAPH_ITERS;
+  if (one) {
+    // kernel k finds the residual of iteration k: one kernel more
+    ++expected;
+    const int64_t nd = 3 * c->mesh->n_nodes, ni3 = 3 * c->mesh->dev.n_interior;
+    if (F32)
+      launch_fill_f32(nd - ni3, c->one32[2] + ni3, 0.0f, s);
+    else
+      launch_fill_f64(nd - ni3, c->one64[2] + ni3, 0.0, s);
+  }
   int end = std::max(2, expected + (expected & 1));
   CgCtl h;
-  const bool two = two_kernel<F32>(c);
   for (;;) {
     while (it < end) {
       hipGraphExec_t g = nullptr;
-      if (it > 0 && end - it >= GRAPH_ITERS && cx->graphs && !cx->prof.on) {
+      if (it > 0 && end - it >= graph_iters && cx->graphs && !cx->prof.on) {
         int rc = cg_graph<F32>(c, ctl, &g);
         if (rc) return rc;
       }
       if (g) {
         HIPC(hipGraphLaunch(g, s));
-        it += GRAPH_ITERS;
+        it += graph_iters;
         continue;
       }
       for (int k = 0; k < 2; ++k, ++it) {
@@ -1289,8 +1362,15 @@ int cg_loop(sw_case* c, CgCtl* ctl, int iter_base, int expected, int* iters_out)
     LAUNCHED();
     int rc = read_ctl(c, ctl, &h);
     if (rc) return rc;
-    if (h.done) break;
-    if (two) {
+    if (one) {
+      h.iters = std::max(h.one_iters[0], h.one_iters[1]);
+      if (h.done) break;
+      double rr = 0.0;
+      for (int k = 0; k < NSLOT; ++k) rr += h.rr[(it - 1) % 3][k];
+      if (!(rr > h.tol2) || h.iters >= c->max_iter) break;
+    } else if (h.done) {
+      break;
+    } else if (two) {
       // the next operator pass would find the same and set the flag
       double rr = 0.0;
       for (int k = 0; k < NSLOT; ++k) rr += h.rr[it & 1][k];
@@ -2825,7 +2905,7 @@ extern "C" int sw_case_autotune(sw_case* c, int32_t reps, int32_t* choice, doubl
     if (ms[k] < ms[best]) best = k;
   }
   LAUNCHED();
-  // two-kernel iterations have one workgroup per tile
+  // one- and two-kernel iterations have one workgroup per tile
   c->grid_cap = two_kernel_cg(c->mesh->dev, 0, true) ? 0 : caps[best];
   if (choice) *choice = best;
   if (ms_out)

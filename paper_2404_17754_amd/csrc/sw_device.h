@@ -2,6 +2,7 @@
 // workgroup reductions, hardware floating-point atomics, grid sizing.
 #pragma once
 
+#include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -95,6 +96,31 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double* sh) {
   }
 }
 
+// Three sums at once over an NT-thread workgroup (sh holds 3 * NT / 64
+// doubles), valid on thread 0.
+template <int NT>
+__device__ __forceinline__ void block_sum3(double& a, double& b, double& c, double* sh) {
+  a = wave_sum(a);
+  b = wave_sum(b);
+  c = wave_sum(c);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (lane == 0) {
+    sh[wid] = a;
+    sh[NT / 64 + wid] = b;
+    sh[2 * NT / 64 + wid] = c;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a = b = c = 0.0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) {
+      a += sh[i];
+      b += sh[NT / 64 + i];
+      c += sh[2 * NT / 64 + i];
+    }
+  }
+}
+
 // A pointer read from a table in memory, known to point to global memory: its
 // loads and stores are global ones (without this they are flat ones, which
 // also occupy the LDS counters and wait with the LDS accesses).
@@ -131,6 +157,48 @@ __device__ __forceinline__ void slot_sum2(const double* a, const double* b, doub
   v = dpp_add<0x140>(v);  // the other eight of sixteen
   ta = read_lane(v, 0) + read_lane(v, 16);
   tb = read_lane(v, 32) + read_lane(v, 48);
+}
+
+// ---- 3x3 block-Jacobi preconditioner
+
+__device__ __forceinline__ float to_t(__half v, float) { return __half2float(v); }
+__device__ __forceinline__ float to_t(float v, float) { return v; }
+__device__ __forceinline__ double to_t(double v, double) { return v; }
+
+// the six values (xx yy zz yz xz xy) of node i's block
+template <typename T, typename PT>
+__device__ __forceinline__ void bj_load(const PT* __restrict__ P, int64_t i, T v[6]) {
+#pragma unroll
+  for (int k = 0; k < 6; ++k) v[k] = to_t(P[6 * i + k], T());
+}
+// FP16 blocks: three 32-bit loads of two values each (12-byte records are
+// 4-byte aligned)
+template <>
+__device__ __forceinline__ void bj_load<float, __half>(const __half* __restrict__ P, int64_t i, float v[6]) {
+  const __half2* P2 = reinterpret_cast<const __half2*>(P) + 3 * i;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float2 f = __half22float2(P2[k]);
+    v[2 * k] = f.x;
+    v[2 * k + 1] = f.y;
+  }
+}
+
+// z = B r for a symmetric 3x3 block (xx yy zz yz xz xy)
+template <typename T>
+__device__ __forceinline__ void bj_mul(const T v[6], const T r[3], T z[3]) {
+  const T a = v[0], b = v[1], c = v[2], yz = v[3], xz = v[4], xy = v[5];
+  z[0] = a * r[0] + xy * r[1] + xz * r[2];
+  z[1] = xy * r[0] + b * r[1] + yz * r[2];
+  z[2] = xz * r[0] + yz * r[1] + c * r[2];
+}
+
+// z = P r for the block of node i, stored in PT, applied in T
+template <typename T, typename PT>
+__device__ __forceinline__ void bj_apply(const PT* __restrict__ P, int64_t i, const T r[3], T z[3]) {
+  T v[6];
+  bj_load<T, PT>(P, i, v);
+  bj_mul(v, r, z);
 }
 
 }  // namespace sw

@@ -21,15 +21,20 @@ struct MatDev {
 // address; readers add the slots up.
 constexpr int NSLOT = 32;
 struct CgCtl {
-  double pAp[2][NSLOT];  // p . A p (ring by iteration parity in two-kernel iterations, else [0])
-  double rz[2][NSLOT];   // r . z, ring indexed by iteration parity
-  double rr[2][NSLOT];   // r . r, same ring
+  // rings indexed by the iteration: mod 3 in one-kernel iterations, else by its parity
+  double pAp[3][NSLOT];  // p . A p (one kernel: z . A z; three kernels: [0] only)
+  double rz[3][NSLOT];   // r . z
+  double rr[3][NSLOT];   // r . r
   double bb;       // ||b||^2 of the right-hand side
   double tol2;     // stop when rr <= tol2
   double rr_true;  // ||b - A x||^2 recomputed in FP64
   double scale;    // mixed precision: residual scaling of the inner system
   double alpha;    // step length of the last update kernel's iteration
   double rz_prev;  // r . z before the last step kernel (two-kernel iterations)
+  // one-kernel iterations: r . z, step length and iteration count as of the
+  // last kernel of each parity
+  double one_rz[2], one_alpha[2];
+  int32_t one_iters[2];
   int32_t done;    // 1 once converged or capped
   int32_t iters;   // iterations of the current solve
   int32_t live;    // 1 when the last update kernel ran its iteration (the
@@ -112,6 +117,14 @@ struct TileArgs {
   // increasing order (null: LDS and global atomics, arrival order)
   double* eout;
   double* fout;
+};
+
+// Vectors of one kernel of a one-kernel CG iteration.
+template <typename T>
+struct OneCg {
+  const T *r_old, *s_old, *w_old;
+  T *r_new, *s_new, *w_clear;
+  T *p, *x;
 };
 
 // ---- several cases marched together (lanes) ------------------------------
@@ -216,6 +229,11 @@ void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, 
 // Two-kernel CG iterations: whether a solve's iterations run so, the operator
 // pass (a.x1 = z; forms and stores p = z + beta p_old, a.y = A p) and the
 // vector kernel after it (x += alpha p, r -= alpha q, z = P r).
+bool one_kernel_cg(const MeshDev& m, int grid_cap, bool f32);
+void launch_tile_cg_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
+                        const OneCg<double>& v, const double* pinv, CgCtl* ctl, int iter, int max_iter, hipStream_t s);
+void launch_tile_cg_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
+                        const OneCg<float>& v, const __half* pinv, CgCtl* ctl, int iter, int max_iter, hipStream_t s);
 bool two_kernel_cg(const MeshDev& m, int grid_cap, bool f32);
 void launch_tile_dir_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                          const double* p_old, double* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s);

@@ -17,41 +17,6 @@ namespace sw {
 
 // --------------------------------------------------------- CG vector ops
 
-__device__ __forceinline__ float to_t(__half v, float) { return __half2float(v); }
-__device__ __forceinline__ float to_t(float v, float) { return v; }
-__device__ __forceinline__ double to_t(double v, double) { return v; }
-
-// the six values (xx yy zz yz xz xy) of node i's block
-template <typename T, typename PT>
-__device__ __forceinline__ void bj_load(const PT* __restrict__ P, int64_t i, T v[6]) {
-#pragma unroll
-  for (int k = 0; k < 6; ++k) v[k] = to_t(P[6 * i + k], T());
-}
-// FP16 blocks: three 32-bit loads of two values each (12-byte records are
-// 4-byte aligned)
-template <>
-__device__ __forceinline__ void bj_load<float, __half>(const __half* __restrict__ P, int64_t i, float v[6]) {
-  const __half2* P2 = reinterpret_cast<const __half2*>(P) + 3 * i;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const float2 f = __half22float2(P2[k]);
-    v[2 * k] = f.x;
-    v[2 * k + 1] = f.y;
-  }
-}
-
-// z = P r for the symmetric 3x3 block of node i (xx yy zz yz xz xy), stored
-// in PT, applied in T
-template <typename T, typename PT>
-__device__ __forceinline__ void bj_apply(const PT* __restrict__ P, int64_t i, const T r[3], T z[3]) {
-  T v[6];
-  bj_load<T, PT>(P, i, v);
-  const T a = v[0], b = v[1], c = v[2], yz = v[3], xz = v[4], xy = v[5];
-  z[0] = a * r[0] + xy * r[1] + xz * r[2];
-  z[1] = xy * r[0] + b * r[1] + yz * r[2];
-  z[2] = xz * r[0] + yz * r[1] + c * r[2];
-}
-
 // Grid for the node-parallel kernels: grid-stride loops over a capped grid
 // (enough workgroups to fill 256 CUs several times over).
 static inline unsigned vgrid(int64_t n) {
@@ -406,15 +371,14 @@ void launch_cg_dir_f32(int64_t n, int par, int iter_abs, int max_iter, const flo
 __device__ __forceinline__ void ctl_prepare_body(CgCtl* ctl, double rtol, int iters) {
   const int i = threadIdx.x;
   if (i < NSLOT) {
-    ctl->pAp[0][i] = ctl->pAp[1][i] = 0.0;
-    ctl->rz[0][i] = ctl->rz[1][i] = 0.0;
-    ctl->rr[0][i] = ctl->rr[1][i] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ctl->pAp[k][i] = ctl->rz[k][i] = ctl->rr[k][i] = 0.0;
   }
   if (i == 0) {
     ctl->tol2 = rtol * rtol * ctl->bb;
     ctl->rr_true = 0.0;
     ctl->done = 0;
-    ctl->iters = iters;
+    ctl->iters = ctl->one_iters[0] = ctl->one_iters[1] = iters;
   }
 }
 __global__ void k_ctl_prepare(CgCtl* ctl, double rtol, int iters) { ctl_prepare_body(ctl, rtol, iters); }

@@ -37,7 +37,7 @@ template <typename T>
 __host__ __device__ constexpr size_t tile_lds_acc(int nmax) {
   return (3 * (size_t)nmax * sizeof(T) + 7) / 8 * 8;
 }
-constexpr int TILE_SUMS = 8;  // wavefronts of the largest workgroup
+constexpr int TILE_SUMS = 24;  // three sums for each wavefront of the largest workgroup
 template <typename T>
 struct TileLds {
   T* xs;
@@ -751,6 +751,170 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
   if (threadIdx.x == 0) atomic_add(&ctl->pAp[par][t % NSLOT], e);
 }
 
+// A whole CG iteration in one kernel.  With the operator applied to the
+// preconditioned residual u_k = P r_k instead of the direction, w_k = A u_k,
+// both sums that iteration k + 1 needs, r_k.u_k and u_k.A u_k, come from one
+// pass (the conjugate gradients of Chronopoulos and Gear, 1989):
+//   beta = rz_k / rz_(k-1),  alpha = rz_k / (u_k.A u_k - beta rz_k / alpha')
+//   p = u_k + beta p,  s = w_k + beta s (= A p),  x += alpha p,  r -= alpha s
+// Kernel k does these updates for its tile's nodes with the sums of kernel
+// k - 1, forms u_k and applies the operator.  A node of several tiles is
+// updated by each of them, in the same arithmetic on the same values, and
+// stored by one (its first), so r and s have two buffers; w has three: read,
+// added into, cleared for the next kernel.  The sums are kept mod 3 alike.
+// stage: 0 the solve's first kernel (no update yet), 1 the second (no
+// previous direction), 2 later ones.
+// Bound by latency, as k_tile_dir, whose chain it has, with more loads in the
+// gather and without the second kernel's launch, sums and pass over the
+// vectors (5 us): a step of 6 tiles 0.97 -> 0.92 ms, of 375 tiles 2.03 ->
+// 1.94, in FP64 of 186 tiles 2.34 -> 2.18.
+template <typename T, typename PT, int NT, int NPT, int WPE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void k_tile_cg(
+    MeshDev m, const uint8_t* __restrict__ emat, const MatDev* __restrict__ mats, TileArgs<T> A, OneCg<T> V,
+    const PT* __restrict__ P, CgCtl* ctl, int ring, int par, int stage, int max_iter) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const TileLds<T> lds(smem_raw, m.max_tile_nodes);
+  const XcdShare share(m.n_tiles);
+  const int t = share.at;
+  const bool lead = blockIdx.x == 0, has_tile = t < share.hi;
+  TileNodes<NT, NPT> N;
+  int own = 0;
+  if (has_tile) {
+    N.load(m, t);
+    own = ldc(m.tile_own_base, t);
+  }
+  const double mat = mat_load(mats, A.n_mat, threadIdx.x);
+  // the previous kernel's sums: the same test in every workgroup, on values
+  // no workgroup of this launch writes
+  const int last = stage == 0 ? 0 : (ring == 0 ? 2 : ring - 1), next = ring == 2 ? 0 : ring + 1;
+  const double tol2 = ctl->tol2, rz_prev = ctl->one_rz[par ^ 1], alpha_prev = ctl->one_alpha[par ^ 1];
+  const int iters = ctl->one_iters[par ^ 1], done = ctl->done;
+  double rr, rz, uAu, unused;
+  slot_sum2(ctl->rr[last], ctl->rz[last], rr, rz);
+  slot_sum2(ctl->pAp[last], ctl->pAp[last], uAu, unused);
+  const double beta_d = stage < 2 ? 0.0 : rz / rz_prev;
+  const double alpha_d = rz / (stage < 2 ? uAu : uAu - beta_d * rz / alpha_prev);
+  const T alpha = (T)alpha_d, beta = (T)beta_d;
+  bool stop = false;  // a NaN stops all but the first iteration
+  if (stage == 0) stop = rr <= tol2;
+  if (stage == 2) stop = !(rr > tol2) || iters >= max_iter;
+  if (done) return;
+  if (stop) {
+    if (lead && threadIdx.x == 0) ctl->done = 1;
+    return;
+  }
+  if (lead) {
+    if (threadIdx.x < NSLOT) {
+      ctl->rz[next][threadIdx.x] = 0.0;
+      ctl->rr[next][threadIdx.x] = 0.0;
+      ctl->pAp[next][threadIdx.x] = 0.0;
+    }
+    if (stage > 0 && threadIdx.x == 0) {
+      ctl->one_rz[par] = rz;
+      ctl->one_alpha[par] = alpha_d;
+      ctl->one_iters[par] = iters + 1;
+    }
+  }
+  if (!has_tile) return;
+  double rz_new = 0.0, rr_new = 0.0;
+  auto gather = [&] {
+    mat_store<T, NT>(mats, A.n_mat, mat, lds.matl);
+    T rv[NPT][3], sv[NPT][3], wv[NPT][3], bl[NPT][6], pv[NPT][3], xv[NPT][3];
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) rv[q][c] = V.r_old[3 * (int64_t)N.g[q] + c];
+      bj_load<T, PT>(P, N.g[q], bl[q]);
+    }
+    if (stage > 0) {
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          wv[q][c] = V.w_old[3 * (int64_t)N.g[q] + c];
+          xv[q][c] = V.x[3 * (int64_t)N.g[q] + c];
+        }
+      }
+    }
+    if (stage > 1) {
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          sv[q][c] = V.s_old[3 * (int64_t)N.g[q] + c];
+          pv[q][c] = V.p[3 * (int64_t)N.g[q] + c];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) sv[q][c] = pv[q][c] = (T)0;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      const int j = threadIdx.x + q * NT;
+      if (j < N.nt) {
+        const int64_t g3 = 3 * (int64_t)N.g[q];
+        const bool mine = j < N.nint || N.g[q] >= own;
+        T r[3], u[3];
+        if (stage > 0) {
+          if (mine) {
+            bj_mul(bl[q], rv[q], u);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              const T p = u[c] + beta * pv[q][c];
+              V.p[g3 + c] = p;
+              V.x[g3 + c] = xv[q][c] + alpha * p;
+            }
+          }
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            sv[q][c] = wv[q][c] + beta * sv[q][c];
+            r[c] = rv[q][c] - alpha * sv[q][c];
+          }
+        } else {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) r[c] = rv[q][c];
+        }
+        bj_mul(bl[q], r, u);
+        lds.gid[j] = N.g[q];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          lds.xs[3 * j + c] = u[c];
+          lds.ys[3 * j + c] = 0.0;
+        }
+        if (mine) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            if (stage > 0) {
+              V.r_new[g3 + c] = r[c];
+              V.s_new[g3 + c] = sv[q][c];
+              rz_new += (double)r[c] * (double)u[c];
+              rr_new += (double)r[c] * (double)r[c];
+            }
+            if (j >= N.nint) V.w_clear[g3 + c] = (T)0;
+          }
+        }
+      }
+    }
+    __syncthreads();
+  };
+  tile_elements<T, NT, sizeof(T) == 4 && NT == 256, sizeof(T) == 4 ? TERMS_A : TERMS_ANY, false>(m, emat, mats, A, t,
+                                                                                                lds, gather);
+  __syncthreads();
+  double energy = tile_scatter<T, NT>(m, A, t, lds);
+  block_sum3<NT>(energy, rz_new, rr_new, lds.sh);
+  if (threadIdx.x == 0) {
+    atomic_add(&ctl->pAp[ring][t % NSLOT], energy);
+    if (stage > 0) {
+      atomic_add(&ctl->rz[ring][t % NSLOT], rz_new);
+      atomic_add(&ctl->rr[ring][t % NSLOT], rr_new);
+    }
+  }
+}
+
 // Workgroups of a pass over n tiles (or items): one each, a multiple of 8 (an
 // eighth per XCD); at most `cap` when cap > 0, each then walking several.
 static unsigned pass_grid(int n, int cap) {
@@ -775,37 +939,31 @@ static void launch_pass(const MeshDev& m, const uint8_t* emat, const MatDev* mat
   hipLaunchKernelGGL((k_tile<T, NT, IN, TERMS, DET, false>), dim3(g), dim3(NT), lds, s, m, emat, mats, a, ctl, iter);
 }
 
-// Whether a solve's iterations run as two kernels (k_tile_dir, k_cg_step)
-// rather than three.  In FP64 always: 1374 us an iteration (share of the
-// step's other work included) against 1597 on 9.6 M tets, 17 against 26 on
-// 3000.  In FP32 up to 4000 tiles: 67 us against 86 at 1500 tiles, 128
-// against 141 at 3000, but 270 against 255 at 6750, where the vectors no
-// longer stay in the caches and the non-temporal accesses of the three
-// kernels gain more.  A cap on the pass's workgroups that binds asks for
-// workgroups that walk several tiles: three kernels.
+// Whether a solve's iterations, past the reach of one kernel, run as two
+// (k_tile_dir, k_cg_step) rather than three.  In FP64 always: 1374 us an
+// iteration (share of the step's other work included) against 1597 on 9.6 M
+// tets.  In FP32 up to 4000 tiles: 128 us against 141 at 3000 tiles, but 270
+// against 255 at 6750, where the vectors no longer stay in the caches and the
+// non-temporal accesses of the three kernels gain more.  A cap on the pass's
+// workgroups that binds asks for workgroups that walk several tiles: three
+// kernels.
 constexpr int TWO_KERNEL_TILES_F32 = 4000;
 bool two_kernel_cg(const MeshDev& m, int grid_cap, bool f32) {
   return !f32 || (m.n_tiles <= TWO_KERNEL_TILES_F32 && (grid_cap == 0 || grid_cap >= m.n_tiles));
 }
 
 // FP32: 512 work-items, one element each in a full tile, two workgroups per
-// compute unit (126 registers: four waves per SIMD): 28.1 us an iteration
-// against 30.1 with 256 at 375 tiles, 48 against 53 at 844, the same at 81.
-// FP64 needs twice the registers, one workgroup of 512 per compute unit, so
-// only while every tile has a compute unit of its own: 19.6 us against 20.1
-// at 6 tiles, but 45.6 against 41.4 at 375.
+// compute unit (four waves per SIMD): 48 us an iteration against 53 with 256
+// at 844 tiles.  FP64 needs twice the registers, room for one workgroup of 512
+// per compute unit: 45.6 us against 41.4 with 256 at 375 tiles.
 template <typename T>
 static void launch_tile_dir(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<T>& a,
                             const T* p_old, T* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
-  const size_t lds = tile_lds<T>(m.max_tile_nodes, a.n_mat);
-  const dim3 grid(pass_grid(m.n_tiles, 0));
   constexpr bool f32 = sizeof(T) == 4;
-  if (f32 || m.n_tiles <= 256)
-    hipLaunchKernelGGL((k_tile_dir<T, 512, f32 ? 4 : 2>), grid, dim3(512), lds, s, m, emat, mats, a, p_old, p, ctl,
-                       iter & 1, iter == 0, max_iter);
-  else if constexpr (!f32)
-    hipLaunchKernelGGL((k_tile_dir<T, 256, 2>), grid, dim3(256), lds, s, m, emat, mats, a, p_old, p, ctl, iter & 1,
-                       iter == 0, max_iter);
+  constexpr int NT = f32 ? 512 : 256;
+  hipLaunchKernelGGL((k_tile_dir<T, NT, f32 ? 4 : 2>), dim3(pass_grid(m.n_tiles, 0)), dim3(NT),
+                     tile_lds<T>(m.max_tile_nodes, a.n_mat), s, m, emat, mats, a, p_old, p, ctl, iter & 1, iter == 0,
+                     max_iter);
 }
 void launch_tile_dir_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                          const double* p_old, double* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
@@ -814,6 +972,49 @@ void launch_tile_dir_f64(const MeshDev& m, const uint8_t* emat, const MatDev* ma
 void launch_tile_dir_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
                          const float* p_old, float* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
   launch_tile_dir<float>(m, emat, mats, a, p_old, p, ctl, iter, max_iter, s);
+}
+
+// Whether a solve's iterations run as one kernel (k_tile_cg), with one
+// workgroup a tile.  Against two kernels, us an iteration (share of the step's
+// other work included): FP32 11.8 / 14.4 at 48 tiles, 16.1 / 18.2 at 256, 24.6
+// / 26.4 at 375, 57.3 / 59.7 at 1266, 72.3 / 74.5 at 1736, but 90.2 / 88.6 at
+// 2187; FP64 11.7 / 14.4 at 48 tiles, 34.8 / 37.1 at 375, 64.6 / 67.4 at 824,
+// but 108 / 92 at 1266: there the vectors and preconditioner blocks of the
+// nodes that several tiles update cost more than the launch saved.
+constexpr int ONE_KERNEL_TILES_F32 = 1800, ONE_KERNEL_TILES_F64 = 900;
+bool one_kernel_cg(const MeshDev& m, int grid_cap, bool f32) {
+  return m.n_tiles <= (f32 ? ONE_KERNEL_TILES_F32 : ONE_KERNEL_TILES_F64) &&
+         (grid_cap == 0 || grid_cap >= m.n_tiles);
+}
+
+// NPT: nodes per work-item, as few as the largest tile needs (a node past the
+// tile's last is loaded all the same): 12.3 us an iteration with three and
+// 11.4 with one at 48 tiles of 64 elements.
+template <typename T, typename PT, int NT, int NPT, int WPE>
+static void launch_tile_cg(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<T>& a,
+                           const OneCg<T>& v, const PT* P, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
+  if constexpr (NPT > 1) {
+    if (m.max_tile_nodes <= NT * (NPT - 1)) {
+      launch_tile_cg<T, PT, NT, NPT - 1, WPE>(m, emat, mats, a, v, P, ctl, iter, max_iter, s);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_tile_cg<T, PT, NT, NPT, WPE>), dim3(pass_grid(m.n_tiles, 0)), dim3(NT),
+                     tile_lds<T>(m.max_tile_nodes, a.n_mat), s, m, emat, mats, a, v, P, ctl, iter % 3, iter & 1,
+                     iter < 2 ? iter : 2, max_iter);
+}
+void launch_tile_cg_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
+                        const OneCg<double>& v, const double* P, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
+  // FP64 leaves room for one workgroup of 512 per compute unit: 4.15 ms a step
+  // against 3.50 with 256 at 375 tiles
+  if (m.n_tiles <= 256)
+    launch_tile_cg<double, double, 512, tile_npt<512>(), 2>(m, emat, mats, a, v, P, ctl, iter, max_iter, s);
+  else
+    launch_tile_cg<double, double, 256, tile_npt<256>(), 2>(m, emat, mats, a, v, P, ctl, iter, max_iter, s);
+}
+void launch_tile_cg_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
+                        const OneCg<float>& v, const __half* P, CgCtl* ctl, int iter, int max_iter, hipStream_t s) {
+  launch_tile_cg<float, __half, 512, tile_npt<512>(), 4>(m, emat, mats, a, v, P, ctl, iter, max_iter, s);
 }
 
 static unsigned node_grid(int64_t n_nodes) {
