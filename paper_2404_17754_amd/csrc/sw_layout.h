@@ -1,6 +1,7 @@
 // Host-side tiled mesh layout (built by sw_mesh.cpp, uploaded by sw_api.cpp).
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <vector>
 
@@ -23,6 +24,20 @@ constexpr int TILE_MAX_ELEMS = 1024;
 // every work-item two.  Measured on the 9.6 M-tet mesh, FP32 pass: 0.409 ms
 // at 512 elements against 0.424 ms at 1024 (node-limited).
 constexpr int TILE_DEFAULT_ELEMS = 512;
+// Smaller ones on meshes whose tiles would not fill the 256 compute units,
+// where a pass takes as long as one tile: 96 tiles of at least 64 and at most
+// 384 elements, then up to 256 tiles.  A step of FP32 iterations / of FP64
+// ones, us: 3072 tets, 512 elements 1480 / 1709, 256 1253 / 1346, 64 1143 /
+// 1149; 24 000 tets, 512 1526 / 1814, 256 1335 / 1431; 98 000 tets, 512 1719 /
+// 2283, 384 1606 / 2165, 256 1741 / 2831.  No smaller on 24 000 tets (128
+// elements: 1229 us): several such cases in a batch fill the chip, and there
+// the nodes shared by more tiles cost time (8 cases, 512 elements 4617 us a
+// step, 256 4545, 128 5258).
+inline int default_tile_elems(int64_t n_tets) {
+  if (n_tets > 256 * (int64_t)TILE_DEFAULT_ELEMS) return TILE_DEFAULT_ELEMS;
+  const int64_t spread = std::min<int64_t>((n_tets + 95) / 96, 384);
+  return (int)std::max<int64_t>(64, std::max(spread, (n_tets + 255) / 256));
+}
 
 struct HostLayout {
   int64_t n_nodes = 0, n_tets = 0, n_faces = 0;

@@ -53,3 +53,14 @@ def test_matches_three_kernels(sw, precision, tile_elems, box):
     # both solve each step to 1e-12 of the right-hand side; the velocity error
     # of a step is that times the condition of the step operator (about 1e2)
     assert np.linalg.norm(w1 - w3) <= 1e-9 * np.linalg.norm(w3)
+
+
+# 96 tiles of 64 to 384 elements, then 256 tiles, then 512 elements
+@pytest.mark.parametrize("box,n_tets,tiles", [((20.0, 20.0, 20.0), 384, 6), ((100.0, 100.0, 50.0), 24000, 96),
+                                              ((110.0, 110.0, 100.0), 58080, 152), ((160.0, 160.0, 80.0), 98304, 256),
+                                              ((160.0, 160.0, 105.0), 129024, 256),
+                                              ((200.0, 200.0, 70.0), 134400, 263)])
+def test_default_tiles(sw, box, n_tets, tiles):
+    mesh = cg.box_mesh(*box, 5.0)
+    assert mesh.n_tets == n_tets
+    assert sw.Mesh(sw.Context(0), mesh).info()[0] == tiles
