@@ -951,13 +951,19 @@ TileArgs<double> args_rhs(const sw_case* c, double* y) {
   A.n_mat = c->n_mat;
   return A;
 }
-int build_rhs(sw_case* c, double* y) {
+// Into y; yu: the interior nodes in the user's node order into yu instead (not
+// in deterministic passes).
+int build_rhs(sw_case* c, double* y, double* yu = nullptr) {
   hipStream_t s = c->ctx->stream;
   const int64_t nd = 3 * c->mesh->n_nodes;
   // the pass stores the interior nodes and adds into the shared ones
   const int64_t ni3 = 3 * c->mesh->dev.n_interior;
   launch_fill_f64(nd - ni3, y + ni3, 0.0, s);
   TileArgs<double> A = args_rhs(c, y);
+  if (yu) {
+    A.map = c->mesh->dev.node_i2u;
+    A.yu = yu;
+  }
   A.vin = c->vin + 3 * (c->step + 1);
   if (!c->det) {
     launch_tile_rhs(c->mesh->dev, c->emat, c->mats, A, s);
@@ -1836,47 +1842,69 @@ extern "C" int sw_case_waveform_device(const sw_case* c, const double** out) {
 
 // The user-order entry points below borrow the case's CG work vectors
 // (p, q, r, z), which hold no state between steps.
+namespace {
+
+// Whether n values at x and n at y share memory: then no tile may read x after
+// another has written y, and the pass runs between copies in the internal
+// order.
+bool overlap(const void* x, const void* y, size_t bytes) {
+  const uintptr_t a = (uintptr_t)x, b = (uintptr_t)y;
+  return a < b ? b - a < bytes : a - b < bytes;
+}
+
+}  // namespace
+
 extern "C" int sw_case_apply(sw_case* c, int32_t op, const double* x, double* y) {
   if (!c || !x || !y) return fail(SW_EINVAL, "NULL argument");
   if (!(op == SW_OP_A || (op > 0 && op < 8))) return fail(SW_EINVAL, "bad operator mask %d", op);
   HIPC(hipSetDevice(c->ctx->device));
   const int64_t nn = c->mesh->n_nodes;
+  const MeshDev& m = c->mesh->dev;
   hipStream_t s = c->ctx->stream;
-  const int64_t ni3 = 3 * c->mesh->dev.n_interior;  // the pass stores the interior nodes, adds into the rest
-  launch_permute_f64(nn, 3, x, c->mesh->dev.node_i2u, c->p, s);
-  launch_fill_f64(3 * nn - ni3, c->q + ni3, 0.0, s);
-  int rc = apply_f64(c, op, c->p, c->q, nullptr, -1);
-  if (rc) return rc;
-  launch_permute_f64(nn, 3, c->q, c->mesh->dev.node_u2i, y, s);
-  launch_fill_f64(3 * nn - ni3, c->q + ni3, 0.0, s);
+  const int64_t ni3 = 3 * m.n_interior;  // the pass stores the interior nodes, adds into the rest
+  if (c->det || overlap(x, y, 24 * (size_t)nn)) {
+    launch_permute_f64(nn, 3, x, m.node_i2u, c->p, s);
+    launch_fill_f64(3 * nn - ni3, c->q + ni3, 0.0, s);
+    int rc = apply_f64(c, op, c->p, c->q, nullptr, -1);
+    if (rc) return rc;
+    launch_permute_f64(nn, 3, c->q, m.node_u2i, y, s);
+    launch_fill_f64(3 * nn - ni3, c->q + ni3, 0.0, s);
+  } else {
+    // z is free between steps
+    launch_fill_f64(3 * nn - ni3, c->z + ni3, 0.0, s);
+    TileArgs<double> A = args_f64(c, op, x, c->z);
+    A.map = m.node_i2u;
+    A.yu = y;
+    launch_tile_f64(m, c->emat, c->mats, A, nullptr, -1, s);
+    launch_shared_out_f64(nn, m.n_interior, c->z, m.node_u2i, y, s);
+  }
   LAUNCHED();
   HIPC(hipStreamSynchronize(s));
   return SW_OK;
 }
-
 extern "C" int sw_case_apply_f32(sw_case* c, int32_t op, const float* x, float* y) {
   if (!c || !x || !y) return fail(SW_EINVAL, "NULL argument");
   if (!(op == SW_OP_A || (op > 0 && op < 8))) return fail(SW_EINVAL, "bad operator mask %d", op);
   HIPC(hipSetDevice(c->ctx->device));
   const int64_t nn = c->mesh->n_nodes;
   hipStream_t s = c->ctx->stream;
-  float* xi = (float*)c->r;  // FP64 vectors hold twice the floats needed
-  float* yi = (float*)c->z;
-  launch_permute_f32(nn, x, c->mesh->dev.node_i2u, xi, s);
-  const int64_t ni3 = 3 * c->mesh->dev.n_interior;
+  const MeshDev& m = c->mesh->dev;
+  float* yi = (float*)c->z;  // FP64 vectors hold twice the floats needed
+  const int64_t ni3 = 3 * m.n_interior;
   launch_fill_f32(3 * nn - ni3, yi + ni3, 0.0f, s);
-  int rc;
-  if (op == SW_OP_A) {
-    // as in an inner CG iteration (past the first): a fresh control block,
-    // so the pass runs in full (the case's inner control block is free
-    // between steps)
-    launch_fill_f64(sizeof(CgCtl) / 8, (double*)c->ctl32, 0.0, s);
-    rc = apply_f32(c, op, xi, yi, c->ctl32, 1);
+  if (overlap(x, y, 12 * (size_t)nn)) {
+    float* xi = (float*)c->r;
+    launch_permute_f32(nn, x, m.node_i2u, xi, s);
+    int rc = apply_f32(c, op, xi, yi, nullptr, -1);
+    if (rc) return rc;
+    launch_permute_f32(nn, yi, m.node_u2i, y, s);
   } else {
-    rc = apply_f32(c, op, xi, yi, nullptr, -1);
+    TileArgs<float> A = args_f32(c, op, x, yi);
+    A.map = m.node_i2u;
+    A.yu = y;
+    launch_tile_f32(m, c->emat, c->mats, A, nullptr, -1, case_grid_cap(c), s);
+    launch_shared_out_f32(nn, m.n_interior, yi, m.node_u2i, y, s);
   }
-  if (rc) return rc;
-  launch_permute_f32(nn, yi, c->mesh->dev.node_u2i, y, s);
   LAUNCHED();
   HIPC(hipStreamSynchronize(s));
   return SW_OK;
@@ -1886,9 +1914,13 @@ extern "C" int sw_case_rhs(sw_case* c, double* y) {
   if (!c || !y) return fail(SW_EINVAL, "NULL argument");
   if (c->step >= c->n_steps) return fail(SW_ESTATE, "no further step in the case capacity");
   HIPC(hipSetDevice(c->ctx->device));
-  int rc = build_rhs(c, c->r);
+  const MeshDev& m = c->mesh->dev;
+  int rc = build_rhs(c, c->r, c->det ? nullptr : y);
   if (rc) return rc;
-  launch_permute_f64(c->mesh->n_nodes, 3, c->r, c->mesh->dev.node_u2i, y, c->ctx->stream);
+  if (c->det)
+    launch_permute_f64(m.n_nodes, 3, c->r, m.node_u2i, y, c->ctx->stream);
+  else
+    launch_shared_out_f64(m.n_nodes, m.n_interior, c->r, m.node_u2i, y, c->ctx->stream);
   LAUNCHED();
   HIPC(hipStreamSynchronize(c->ctx->stream));
   return SW_OK;

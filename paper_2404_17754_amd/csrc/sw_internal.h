@@ -112,6 +112,11 @@ struct TileArgs {
   T* y;
   int accumulate;      // interior nodes: 0 overwrite, 1 add
   int n_mat;           // materials in the table
+  // passes from and to vectors in the user's node order (null otherwise): the
+  // nodes' user ids and the output of the interior nodes, while the shared
+  // ones are added up in y (launch_shared_out moves them)
+  const int32_t* map;
+  T* yu;
   // deterministic FP64 passes: each element's 10 x 3 results and each
   // face's 6 x 3 go here (slot-major), then every node sums its slots in
   // increasing order (null: LDS and global atomics, arrival order)
@@ -320,6 +325,10 @@ void launch_misfit(int n_rec, int64_t n_steps, const double* U, const double* ob
                    double* out2, hipStream_t s);
 
 // dst[i*w + k] = src[map[i]*w + k], i < n, k < w (w = 3 or 6; 3 in FP32)
+void launch_shared_out_f64(int64_t n_nodes, int64_t n_interior, const double* y, const int32_t* u2i, double* yu,
+                           hipStream_t s);
+void launch_shared_out_f32(int64_t n_nodes, int64_t n_interior, const float* y, const int32_t* u2i, float* yu,
+                           hipStream_t s);
 void launch_permute_f64(int64_t n, int w, const double* src, const int32_t* map, double* dst, hipStream_t s);
 void launch_permute_f32(int64_t n, const float* src, const int32_t* map, float* dst, hipStream_t s);
 

@@ -773,6 +773,36 @@ void launch_permute_f32(int64_t n, const float* src, const int32_t* map, float* 
   hipLaunchKernelGGL((k_permute<float, 3>), dim3((nblocks(n) + 7) / 8 * 8), dim3(TPB), 0, s, n, src, map, dst);
 }
 
+// The shared nodes' values of a pass in the user's node order (the pass has
+// stored the others there): yu[i] = y[u2i[i]] where that is past the interior
+// nodes.  9.6 M tets, FP32: 83 us; from the internal order, each node stored
+// on its own, 108.
+template <typename T>
+__global__ __launch_bounds__(TPB) void k_shared_out(int64_t n, int64_t n_int, const T* __restrict__ y,
+                                                    const int32_t* __restrict__ u2i, T* __restrict__ yu) {
+  const int64_t blk = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int64_t i = blk * TPB + threadIdx.x;
+  if (i >= n) return;
+  const int64_t j = u2i[i];
+  if (j < n_int) return;
+  T v[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) v[c] = y[3 * j + c];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) yu[3 * i + c] = v[c];
+}
+template <typename T>
+static void launch_shared_out(int64_t n, int64_t n_int, const T* y, const int32_t* u2i, T* yu, hipStream_t s) {
+  if (n <= n_int) return;
+  hipLaunchKernelGGL(k_shared_out<T>, dim3((nblocks(n) + 7) / 8 * 8), dim3(TPB), 0, s, n, n_int, y, u2i, yu);
+}
+void launch_shared_out_f64(int64_t n, int64_t n_int, const double* y, const int32_t* u2i, double* yu, hipStream_t s) {
+  launch_shared_out(n, n_int, y, u2i, yu, s);
+}
+void launch_shared_out_f32(int64_t n, int64_t n_int, const float* y, const int32_t* u2i, float* yu, hipStream_t s) {
+  launch_shared_out(n, n_int, y, u2i, yu, s);
+}
+
 // ---------------------------------------------------------------- lanes
 //
 // Several cases (lanes) in one launch: grid (blocks per lane, lanes), each

@@ -276,8 +276,9 @@ __device__ __forceinline__ void tile_elements(const MeshDev& m, const uint8_t* _
 // work-item's share of the tile's x.(A x)_tile = sum over the tile's nodes
 // of the input value times the tile's partial sum: summed over the tiles it
 // is x.A x (a node's full value is the sum of its tiles' partials), with one
-// product per node value instead of one per element entry.
-template <typename T, int NT>
+// product per node value instead of one per element entry.  USER: the
+// interior nodes go to A.yu in the user's node order (gid holds their ids).
+template <typename T, int NT, bool USER = false>
 __device__ __forceinline__ double tile_scatter(const MeshDev& m, const TileArgs<T>& A, int t,
                                                const TileLds<T>& lds) {
   const T* xs = lds.xs;
@@ -290,7 +291,10 @@ __device__ __forceinline__ double tile_scatter(const MeshDev& m, const TileArgs<
   for (int k = threadIdx.x; k < 3 * nint; k += NT) {
     const double v = ys[k];
     energy += (double)xs[k] * v;
-    if (A.accumulate)
+    if constexpr (USER) {
+      const int j = k / 3;
+      A.yu[3 * (int64_t)lds.gid[j] + (k - 3 * j)] = (T)v;
+    } else if (A.accumulate)
       y[ib3 + k] += (T)v;
     else
       y[ib3 + k] = (T)v;
@@ -343,17 +347,28 @@ __device__ __forceinline__ void mat_store(const MatDev* __restrict__ mats, int n
   for (int i = threadIdx.x + NT; i < 3 * n_mat; i += NT) matl[i] = (T)mat_load(mats, n_mat, i);
 }
 
-// Input of a pass: x1; a1 x1 + a2 x2; x1 in bfloat16 (x1h).
-enum { IN_ONE = 0, IN_TWO = 1, IN_BF16 = 2 };
+// Input of a pass: x1; a1 x1 + a2 x2; x1 in bfloat16 (x1h); x1 in the user's
+// node order (A.map: the nodes' user ids), the results of the interior nodes
+// then going to A.yu in that order too: that gather and scatter take the place
+// of two kernels that permute the vectors.  9.6 M tets, FP32: this pass 428 us
+// and 83 for the shared nodes' results (k_shared_out), against 326 and 290.
+// (The shared nodes added in the user's order by atomics: 770 in all, the
+// addresses of a wavefront then lying in as many cache lines.)
+enum { IN_ONE = 0, IN_TWO = 1, IN_BF16 = 2, IN_USER = 3 };
 
 template <typename T, int NT, int IN, int NPT>
 __device__ __forceinline__ void tile_gather(const TileArgs<T>& A, const TileNodes<NT, NPT>& N,
                                             const TileLds<T>& lds) {
   // every load before the first is waited for: one memory latency a tile
   T v[NPT][3], u[IN == IN_TWO ? NPT : 1][3];
+  int32_t uid[IN == IN_USER ? NPT : 1];
+  if constexpr (IN == IN_USER) {
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) uid[q] = A.map[N.g[q]];
+  }
 #pragma unroll
   for (int q = 0; q < NPT; ++q) {
-    const int64_t g3 = 3 * (int64_t)N.g[q];
+    const int64_t g3 = 3 * (int64_t)(IN == IN_USER ? uid[q] : N.g[q]);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       if constexpr (IN == IN_BF16)
@@ -367,7 +382,7 @@ __device__ __forceinline__ void tile_gather(const TileArgs<T>& A, const TileNode
   for (int q = 0; q < NPT; ++q) {
     const int j = threadIdx.x + q * NT;
     if (j < N.nt) {
-      lds.gid[j] = N.g[q];
+      lds.gid[j] = IN == IN_USER && j < N.nint ? uid[q] : N.g[q];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         if constexpr (IN == IN_TWO) v[q][c] = A.a1 * v[q][c] + A.a2 * u[q][c];
@@ -395,7 +410,7 @@ __device__ __forceinline__ double tile_body(const MeshDev& m, const uint8_t* __r
   });
   if constexpr (DET) return 0.0;
   __syncthreads();
-  return tile_scatter<T, NT>(m, A, t, lds);
+  return tile_scatter<T, NT, IN == IN_USER>(m, A, t, lds);
 }
 
 // One tile of the right-hand side pass,
@@ -403,8 +418,9 @@ __device__ __forceinline__ double tile_body(const MeshDev& m, const uint8_t* __r
 // the mass on its input, then the stiffness on the other, which waits in
 // registers (30 of the mass loop's spare ones) for its turn in the LDS.  Two
 // passes gather v and add every shared node to global memory twice: with the
-// permutation of the result 1.55 ms on 9.6 M tets, this pass 1.15.
-template <int NT>
+// permutation of the result 1.55 ms on 9.6 M tets, this pass 1.08, with the
+// interior nodes stored in the user's order (USER, as in tile_scatter) 1.04.
+template <int NT, bool USER>
 __device__ __forceinline__ void tile_rhs(const MeshDev& m, const uint8_t* __restrict__ emat,
                                          const MatDev* __restrict__ mats, const TileArgs<double>& A, int t,
                                          const TileLds<double>& lds) {
@@ -416,6 +432,11 @@ __device__ __forceinline__ void tile_rhs(const MeshDev& m, const uint8_t* __rest
   tile_element_loop<double, NT, false, false, true, false, false>(m, emat, A, t, lds, [&] {
     mat_store<double, NT>(mats, A.n_mat, mat, lds.matl);
     double v1[NPT][3], v2[NPT][3];
+    int32_t uid[USER ? NPT : 1];
+    if constexpr (USER) {
+#pragma unroll
+      for (int q = 0; q < NPT; ++q) uid[q] = A.map[N.g[q]];
+    }
 #pragma unroll
     for (int q = 0; q < NPT; ++q) {
       const int64_t g3 = 3 * (int64_t)N.g[q];
@@ -433,6 +454,9 @@ __device__ __forceinline__ void tile_rhs(const MeshDev& m, const uint8_t* __rest
       for (int c = 0; c < 3; ++c) kv[q][c] += A.k2 * v2[q][c];
       if (j < N.nt) {
         lds.gid[j] = N.g[q];
+        if constexpr (USER) {
+          if (j < N.nint) lds.gid[j] = uid[q];
+        }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           lds.xs[3 * j + c] = A.a1 * v1[q][c] + A.a2 * v2[q][c];
@@ -456,7 +480,7 @@ __device__ __forceinline__ void tile_rhs(const MeshDev& m, const uint8_t* __rest
     __syncthreads();
   });
   __syncthreads();
-  tile_scatter<double, NT>(m, A, t, lds);
+  tile_scatter<double, NT, USER>(m, A, t, lds);
 }
 
 // Share of n tiles (or work items) of workgroup b: XCD x = b mod 8
@@ -563,13 +587,13 @@ __global__ __launch_bounds__(TPB) void k_dot_slots(int64_t n, const double* __re
   if (threadIdx.x == 0) slots[blockIdx.x] = acc;
 }
 
-template <int NT>
+template <int NT, bool USER>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_tile_rhs(
     MeshDev m, const uint8_t* __restrict__ emat, const MatDev* __restrict__ mats, TileArgs<double> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const TileLds<double> lds(smem_raw, m.max_tile_nodes);
   const XcdShare share(m.n_tiles);
-  if (share.at < share.hi) tile_rhs<NT>(m, emat, mats, A, share.at, lds);
+  if (share.at < share.hi) tile_rhs<NT, USER>(m, emat, mats, A, share.at, lds);
 }
 
 // A lane's tables and vectors as pointers to global memory (as_global).
@@ -617,7 +641,7 @@ __global__ __launch_bounds__(NT) void k_tile_lanes(const TileLane<T>* __restrict
   const TileLane<T> L = lane_of(lanes, w.x);
   const TileLds<T> lds(smem_raw, L.m.max_tile_nodes);
   if constexpr (RHS)
-    tile_rhs<NT>(L.m, L.emat, L.mats, L.A, w.y, lds);
+    tile_rhs<NT, false>(L.m, L.emat, L.mats, L.A, w.y, lds);
   else
     tile_body<T, NT, IN_ONE, TERMS_ANY, false>(L.m, L.emat, L.mats, L.A, w.y, lds);
 }
@@ -1025,7 +1049,10 @@ static unsigned node_grid(int64_t n_nodes) {
 void launch_tile_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                      CgCtl* ctl, int iter, hipStream_t s) {
   if (!a.eout) {
-    launch_pass<double, IN_ONE, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, 0, s);
+    if (a.map)
+      launch_pass<double, IN_USER, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, 0, s);
+    else
+      launch_pass<double, IN_ONE, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, 0, s);
     return;
   }
   // deterministic: element and face slots, the node pass in slot order, and
@@ -1045,8 +1072,12 @@ void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, 
   if (a.sK != 0.0f && a.sM != 0.0f) {
     if (a.x1h)
       launch_pass<float, IN_BF16, TERMS_A, false>(m, emat, mats, a, ctl, iter, grid_cap, s);
+    else if (a.map)
+      launch_pass<float, IN_USER, TERMS_A, false>(m, emat, mats, a, ctl, iter, grid_cap, s);
     else
       launch_pass<float, IN_ONE, TERMS_A, false>(m, emat, mats, a, ctl, iter, grid_cap, s);
+  } else if (a.map) {
+    launch_pass<float, IN_USER, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, grid_cap, s);
   } else {
     launch_pass<float, IN_ONE, TERMS_ANY, false>(m, emat, mats, a, ctl, iter, grid_cap, s);
   }
@@ -1054,8 +1085,12 @@ void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, 
 
 void launch_tile_rhs(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                      hipStream_t s) {
-  hipLaunchKernelGGL(k_tile_rhs<256>, dim3(pass_grid(m.n_tiles, 0)), dim3(256),
-                     tile_lds<double>(m.max_tile_nodes, a.n_mat), s, m, emat, mats, a);
+  const dim3 grid(pass_grid(m.n_tiles, 0));
+  const size_t lds = tile_lds<double>(m.max_tile_nodes, a.n_mat);
+  if (a.map)
+    hipLaunchKernelGGL((k_tile_rhs<256, true>), grid, dim3(256), lds, s, m, emat, mats, a);
+  else
+    hipLaunchKernelGGL((k_tile_rhs<256, false>), grid, dim3(256), lds, s, m, emat, mats, a);
 }
 
 void launch_tile_lanes_f64(const TileLane<double>* lanes, const int2* work, int n_work, int max_tile_nodes, int max_mat,
