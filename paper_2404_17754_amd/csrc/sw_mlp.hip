@@ -286,12 +286,21 @@ void launch_mlp_collect(const MlpFeat& F, const double* du, int count, uint64_t 
 // gradients, 32 cycles each: 3.5 us; the rest is latency (the rows, weights
 // and accumulators of a workgroup that has one pass to make).
 // 8192 rows, with the Adam step: 406 us as one work-item per sample in scalar
-// loops, 33 so.
+// loops, 29 so (33 with the weights fetched one load after the other and the
+// sums of a wavefront four to an LDS bank); 10 of them are the additions of
+// 128 workgroups to one gradient (100 rows: 19 us).
 // FP32 sums run over at most GFLUSH * 16 = 128 samples, then in FP64.
 constexpr int GW = 4, GS = 16, GFLUSH = 8;
 constexpr int GLD = 17, GLD2 = 65, GLDX = 13;  // row strides that spread the LDS banks
+// the workgroup's sums in the order of theta, the rows of W2 apart by GACC
+// (lanes 16 apart add into rows four apart: 4 * GACC doubles are half the banks)
+constexpr int GACC = 68, GRAD_ACC = MLP_NP + MLP_H * (GACC - MLP_H);
+__device__ __forceinline__ int grad_at(int j) {
+  return j < MLP_OFF_W2 ? j : j < MLP_OFF_W2 + MLP_H * MLP_H ? j + (j - MLP_OFF_W2) / MLP_H * (GACC - MLP_H)
+                                                               : j + MLP_H * (GACC - MLP_H);
+}
 struct GradLds {
-  double acc[MLP_NP + 1];
+  double acc[GRAD_ACC + (GRAD_ACC & 1)];
   float w1[MLP_H * GLD], w2[MLP_H * GLD2], b1[MLP_H], b2[MLP_H], w3[MLP_H];
   struct {
     float h1[MLP_H * GLD], d1[MLP_H * GLD], d2[MLP_H * GLD], x[GS * GLDX];
@@ -331,10 +340,31 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
     return x;
   };
   floatx4 xr = load_row(c0 + wv * GS + r);
-  for (int j = tid; j < MLP_NP + 1; j += 64 * GW) L.acc[j] = 0.0;
-  for (int j = tid; j < MLP_H * MLP_H; j += 64 * GW) L.w2[(j / MLP_H) * GLD2 + j % MLP_H] = theta[MLP_OFF_W2 + j];
-  for (int j = tid; j < MLP_H * 16; j += 64 * GW)
-    L.w1[(j / 16) * GLD + j % 16] = j % 16 < MLP_IN ? theta[MLP_OFF_W1 + (j / 16) * MLP_IN + j % 16] : 0.0f;
+  // the weights, every load before the first is waited for
+  constexpr int N2 = MLP_H * MLP_H / (4 * 64 * GW), N1 = MLP_H * 16 / (64 * GW);
+  floatx4 t2[N2];
+  float t1[N1];
+#pragma unroll
+  for (int k = 0; k < N2; ++k)
+    t2[k] = *reinterpret_cast<const float4u*>(theta + MLP_OFF_W2 + 4 * (tid + k * 64 * GW));
+#pragma unroll
+  for (int k = 0; k < N1; ++k) {
+    const int j = tid + k * 64 * GW;
+    t1[k] = theta[MLP_OFF_W1 + (j / 16) * MLP_IN + (j % 16 < MLP_IN ? j % 16 : 0)];
+  }
+#pragma unroll 4
+  for (int j = tid; j < GRAD_ACC; j += 64 * GW) L.acc[j] = 0.0;
+#pragma unroll
+  for (int k = 0; k < N2; ++k) {
+    const int j = 4 * (tid + k * 64 * GW);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) L.w2[(j / MLP_H) * GLD2 + j % MLP_H + c] = t2[k][c];
+  }
+#pragma unroll
+  for (int k = 0; k < N1; ++k) {
+    const int j = tid + k * 64 * GW;
+    L.w1[(j / 16) * GLD + j % 16] = j % 16 < MLP_IN ? t1[k] : 0.0f;
+  }
   if (tid < MLP_H) {
     L.b1[tid] = theta[MLP_OFF_B1 + tid];
     L.b2[tid] = theta[MLP_OFF_B2 + tid];
@@ -363,17 +393,17 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
       for (int j = 0; j < 4; ++j) {
         const int u = 16 * c + 4 * q + j;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) atomicAdd(&L.acc[MLP_OFF_W2 + u * MLP_H + 16 * b + r], (double)g2[c][b][j]);
+        for (int b = 0; b < 4; ++b) atomicAdd(&L.acc[MLP_OFF_W2 + u * GACC + 16 * b + r], (double)g2[c][b][j]);
         if (r <= MLP_IN)  // column 10 of the inputs is one: the bias
-          atomicAdd(&L.acc[r < MLP_IN ? MLP_OFF_W1 + u * MLP_IN + r : MLP_OFF_B1 + u], (double)g1[c][j]);
+          atomicAdd(&L.acc[grad_at(r < MLP_IN ? MLP_OFF_W1 + u * MLP_IN + r : MLP_OFF_B1 + u)], (double)g1[c][j]);
         const float sb = row_sum(gb2[c][j]), sw = row_sum(gw3[c][j]);
         if (r == 0) {
-          atomicAdd(&L.acc[MLP_OFF_B2 + u], (double)sb);
-          atomicAdd(&L.acc[MLP_OFF_W3 + u], (double)sw);
+          atomicAdd(&L.acc[grad_at(MLP_OFF_B2 + u)], (double)sb);
+          atomicAdd(&L.acc[grad_at(MLP_OFF_W3 + u)], (double)sw);
         }
       }
     const float s3 = row_sum(gb3);
-    if (l == 0) atomicAdd(&L.acc[MLP_OFF_B3], (double)s3);
+    if (l == 0) atomicAdd(&L.acc[grad_at(MLP_OFF_B3)], (double)s3);
     clear();
   };
   clear();
@@ -474,8 +504,11 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
     atomic_add(&loss2[1], ww);
   }
   __syncthreads();
-  for (int j = tid; j < MLP_NP; j += 64 * GW)
-    if (L.acc[j] != 0.0) atomic_add(&grad[j], L.acc[j]);
+#pragma unroll 4
+  for (int j = tid; j < MLP_NP; j += 64 * GW) {
+    const double a = L.acc[grad_at(j)];
+    if (a != 0.0) atomic_add(&grad[j], a);
+  }
 }
 
 void launch_mlp_grad(const float* S, int64_t n, int64_t nb, uint64_t seed, int64_t batch, const float* theta,
