@@ -252,7 +252,7 @@ struct sw_mlp {
 struct sw_batch {
   sw_ctx* ctx;
   std::vector<sw_case*> cases;
-  hipGraphExec_t cg_graph = nullptr;  // captured pair of FP32 CG iterations
+  hipGraphExec_t cg_graph = nullptr;  // captured GRAPH_ITERS FP32 CG iterations
   int cg_graph_cap = -1;
   int grid_cap = -1;                  // chosen by sw_batch_autotune (-1: the context's)
   int schedule = 0;                   // work-item order (see batch_items)
@@ -2486,7 +2486,7 @@ int batch_gather(sw_batch* b) {
 
 // One FP32 CG iteration of every refining lane on stream s (dev_index: the
 // direction kernels take the iteration index from the lanes' control
-// blocks, as in a captured pair).
+// blocks, as in a captured graph).
 void batch_cg_iteration(sw_batch* b, int i, bool dev_index, hipStream_t s, bool prof) {
   sw_ctx* cx = b->ctx;
   const int n = b->n;
@@ -2502,8 +2502,8 @@ void batch_cg_iteration(sw_batch* b, int i, bool dev_index, hipStream_t s, bool 
   if (prof) prof_end(cx, ev);
 }
 
-// The batch's captured pair of FP32 CG iterations (see cg_pair_graph).
-int batch_pair_graph(sw_batch* b, hipGraphExec_t* out) {
+// The batch's captured graph of GRAPH_ITERS FP32 CG iterations (see cg_graph).
+int batch_cg_graph(sw_batch* b, hipGraphExec_t* out) {
   if (b->cg_graph && b->cg_graph_cap == batch_grid_cap(b)) {
     *out = b->cg_graph;
     return SW_OK;
@@ -2516,7 +2516,7 @@ int batch_pair_graph(sw_batch* b, hipGraphExec_t* out) {
   int rc = capture_stream(b->ctx, &cs);
   if (rc) return rc;
   HIPC(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-  for (int k = 0; k < 2; ++k) batch_cg_iteration(b, 2 + k, true, cs, false);
+  for (int k = 0; k < GRAPH_ITERS; ++k) batch_cg_iteration(b, 2 + k, true, cs, false);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(cs, &g);
   if (e != hipSuccess) return fail(SW_EHIP, "batch CG graph capture failed: %s", hipGetErrorString(e));
@@ -2536,7 +2536,7 @@ int batch_step_once(sw_batch* b) {
   sw_ctx* cx = b->ctx;
   hipStream_t s = cx->stream;
   const int n = b->n;
-  std::vector<int> g(n), iters(n, 0), outer(n, 0), flags(n, 0), est(n), stopped(n, 0), first(n, 1);
+  std::vector<int> g(n), iters(n, 0), outer(n, 0), flags(n, 0), est(n), round(n, 0), stopped(n, 0), first(n, 1);
   std::vector<double> rel(n, 0.0);
   for (int l = 0; l < n; ++l) {
     sw_case* c = b->cases[l];
@@ -2648,33 +2648,41 @@ int batch_step_once(sw_batch* b) {
     launch_lanes(LANE_CG_INIT32, n, b->max_nodes, b->d_lanes, b->d_st, nullptr, s);
     LAUNCHED();
     // inner CG of every refining lane in lockstep; converged lanes' work
-    // items return at once.  The first chunk has an even count; the chunks
-    // of two after it replay the batch's captured pair of iterations.
-    int chunk = 2;
-    for (int l = 0; l < n; ++l)
-      if (b->st[l].active) chunk = std::max(chunk, est[l] + (est[l] & 1));
+    // items return at once.  Chunks as in cg_loop: first the iterations
+    // expected of the slowest lane, then two at a time.
+    int end = 2;
+    for (int l = 0; l < n; ++l) {
+      if (!b->st[l].active) continue;
+      const sw_case* c = b->cases[l];
+      if (round[l] < sw_case::MAX_ROUNDS && c->round_iters[round[l]] > 0) est[l] = c->round_iters[round[l]];
+      end = std::max(end, est[l] + (est[l] & 1));
+    }
     for (int it = 0;;) {
-      hipGraphExec_t g = nullptr;
-      if (it > 0 && chunk == 2 && cx->graphs && !cx->prof.on && (rc = batch_pair_graph(b, &g))) return rc;
-      if (g) {
-        HIPC(hipGraphLaunch(g, s));
-      } else {
-        for (int k = 0; k < chunk; ++k) batch_cg_iteration(b, it + k, false, s, true);
+      while (it < end) {
+        hipGraphExec_t g = nullptr;
+        if (it > 0 && end - it >= GRAPH_ITERS && cx->graphs && !cx->prof.on && (rc = batch_cg_graph(b, &g))) return rc;
+        if (g) {
+          HIPC(hipGraphLaunch(g, s));
+          it += GRAPH_ITERS;
+          continue;
+        }
+        for (int k = 0; k < 2; ++k, ++it) batch_cg_iteration(b, it, false, s, true);
       }
       LAUNCHED();
-      it += chunk;
       if ((rc = batch_gather(b))) return rc;
       bool all = true;
       for (int l = 0; l < n; ++l)
         if (b->st[l].active && !b->info[l].done32) all = false;
       if (all) break;
-      chunk = 2;
+      end = it + 2;
     }
     for (int l = 0; l < n; ++l) {
       if (!b->st[l].active) continue;
+      sw_case* c = b->cases[l];
       const int itl = std::max(0, b->info[l].iters32 - b->st[l].iter_base);
       iters[l] += itl;
       est[l] = std::max(1, itl);
+      if (round[l] < sw_case::MAX_ROUNDS) c->round_iters[round[l]++] = est[l];
     }
     launch_lanes(LANE_IR_UPDATE, n, b->max_nodes, b->d_lanes, b->d_st, nullptr, s);
     LAUNCHED();
