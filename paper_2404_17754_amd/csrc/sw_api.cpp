@@ -1340,11 +1340,9 @@ int cg_loop(sw_case* c, CgCtl* ctl, int iter_base, int expected, int* iters_out)
   if (one) {
     // kernel k finds the residual of iteration k: one kernel more
     ++expected;
+    // (the first w is clear: in FP32 from the round's first kernel)
     const int64_t nd = 3 * c->mesh->n_nodes, ni3 = 3 * c->mesh->dev.n_interior;
-    if (F32)
-      launch_fill_f32(nd - ni3, c->one32[2] + ni3, 0.0f, s);
-    else
-      launch_fill_f64(nd - ni3, c->one64[2] + ni3, 0.0, s);
+    if (!F32) launch_fill_f64(nd - ni3, c->one64[2] + ni3, 0.0, s);
   }
   int end = std::max(2, expected + (expected & 1));
   CgCtl h;
@@ -1388,21 +1386,18 @@ int cg_loop(sw_case* c, CgCtl* ctl, int iter_base, int expected, int* iters_out)
   return SW_OK;
 }
 
-// FP64 true residual of x: q = A x, r = b - q, rr_true into ctl64.  q keeps
-// A x unless zero_q is set; then its shared nodes are cleared, which is all
-// the next operator pass into q needs (it stores the interior nodes and
-// adds into the shared ones).
-int true_residual(sw_case* c, CgCtl* hctl, bool zero_q) {
+// FP64 true residual of x: q = A x, r = b - q, rr_true into ctl64 (cleared
+// here if asked for, else by the kernel before).  q keeps A x unless zero_q
+// is set; then its shared nodes are cleared, which is all the next operator
+// pass into q needs (it stores the interior nodes and adds into the shared
+// ones).
+int true_residual(sw_case* c, CgCtl* hctl, bool zero_q, bool clear) {
   hipStream_t s = c->ctx->stream;
   const int64_t nd = 3 * c->mesh->n_nodes;
-  launch_fill_f64(1, &c->ctl64->rr_true, 0.0, s);
+  if (clear) launch_fill_f64(1, &c->ctl64->rr_true, 0.0, s);
   int rc = apply_f64(c, SW_OP_A, c->x, c->q, nullptr, -1);
   if (rc) return rc;
-  launch_true_residual(nd, c->b, c->q, c->r, c->ctl64, s, c->det);
-  if (zero_q) {
-    const int64_t ni3 = 3 * c->mesh->dev.n_interior;
-    launch_fill_f64(nd - ni3, c->q + ni3, 0.0, s);
-  }
+  launch_true_residual(nd, c->b, c->q, c->r, zero_q ? 3 * c->mesh->dev.n_interior : nd, c->ctl64, s, c->det);
   LAUNCHED();
   return read_ctl(c, c->ctl64, hctl);
 }
@@ -1629,7 +1624,7 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
       rc = cg_loop<false>(c, c->ctl64, *iters, c->last_iters - *iters, &it);
       if (rc) return rc;
       *iters += it;
-      rc = true_residual(c, &h, false);
+      rc = true_residual(c, &h, false, false);  // cleared with the control block
       if (rc) return rc;
       ++*outer;
       bool stop = false;
@@ -1669,6 +1664,7 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
     bool first = true;
     // a projected guess comes with its residual from the stored images
     bool image_res = projected(g);
+    bool rr_set = image_res;  // rr_true holds a value
     bool recursive = false;  // residual from the flexible recurrence
     int k = 0;               // flexible iterations since the last true residual
     for (;;) {
@@ -1679,7 +1675,8 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
       if (from_images || from_rec) {
         rc = read_ctl(c, c->ctl64, &h);
       } else {
-        rc = true_residual(c, &h, true);
+        rc = true_residual(c, &h, true, rr_set);
+        rr_set = true;
         k = 0;
       }
       if (rc) return rc;
@@ -1710,10 +1707,9 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
       // needs only a smaller reduction of the current residual
       const double need = c->rtol * std::sqrt(h.bb / h.rr_true);
       const double tol = std::min(0.5, std::max(c->inner_rtol, 0.9 * need));
-      launch_fill_f64(sizeof(CgCtl) / 8, (double*)c->ctl32, 0.0, s);
-      launch_fill_f64(1, &c->ctl32->bb, 1.0, s);
-      launch_ctl_prepare(c->ctl32, tol, *iters, s);
-      launch_ir_begin(nn, c->r, c->pinv16, c->r32, c->z32, c->p32, c->p16, c->d32, c->ctl64, c->ctl32, s);
+      launch_ctl_begin(c->ctl32, tol, *iters, s);
+      launch_ir_begin(nn, ni3 / 3, c->r, c->pinv16, c->r32, c->z32, c->p32, c->p16, c->d32, c->one32[2], c->ctl64,
+                      c->ctl32, s);
       LAUNCHED();
       int it = 0;
       if (round < sw_case::MAX_ROUNDS && c->round_iters[round] > 0) inner_est = c->round_iters[round];
@@ -1724,6 +1720,7 @@ int solve_step(sw_case* c, int* iters, int* outer, double* relres, int* flags) {
       if (round < sw_case::MAX_ROUNDS) c->round_iters[round++] = inner_est;
       if (!flex) {
         launch_ir_update(nd, c->x, c->d32, c->ctl64, s);
+        rr_set = false;
         LAUNCHED();
         continue;
       }

@@ -289,19 +289,20 @@ void launch_cg_dir_h(int64_t n_nodes, int par, int iter_abs, int max_iter, const
 
 // ctl setup: bb must already be in ctl; sets tol2 = rtol^2 bb and the step's
 // iterations so far, clears the rest
+void launch_ctl_begin(CgCtl* ctl, double rtol, int iters, hipStream_t s);
 void launch_ctl_prepare(CgCtl* ctl, double rtol, int iters, hipStream_t s);
 // *out += x.x (det: one workgroup, a fixed-order sum)
 void launch_norm2(int64_t n, const double* x, double* out, hipStream_t s, bool det = false);
 
 // r = b - q, rr_true -> ctl (det: one workgroup)
-void launch_true_residual(int64_t n, const double* b, const double* q, double* r, CgCtl* ctl, hipStream_t s,
-                          bool det = false);
+void launch_true_residual(int64_t n, const double* b, double* q, double* r, int64_t zero_from, CgCtl* ctl,
+                          hipStream_t s, bool det);
 // r32 = r64 / ||r64|| (||r64|| from ctl->rr_true, kept in ctl->scale), z32 and
 // the first direction (into p16 in bfloat16 when given, else p32), d32 = 0
-void launch_ir_begin(int64_t n_nodes, const double* r64, const __half* P, float* r32, float* z32, float* p32,
-                     uint16_t* p16, float* d32, CgCtl* ctl64, CgCtl* ctl32, hipStream_t s);
+void launch_ir_begin(int64_t n_nodes, int64_t n_int, const double* r64, const __half* P, float* r32, float* z32,
+                     float* p32, uint16_t* p16, float* d32, float* w, CgCtl* ctl64, CgCtl* ctl32, hipStream_t s);
 // x64 += ctl->scale * d32
-void launch_ir_update(int64_t n, double* x64, const float* d32, const CgCtl* ctl, hipStream_t s);
+void launch_ir_update(int64_t n, double* x64, const float* d32, CgCtl* ctl, hipStream_t s);
 // flexible outer CG (see sw_kernels.hip)
 void launch_fcg_begin(int64_t n, const float* d32, const CgCtl* ctl64, const double* q_prev, double* z,
                       double* dots, hipStream_t s);

@@ -382,6 +382,19 @@ __device__ __forceinline__ void ctl_prepare_body(CgCtl* ctl, double rtol, int it
   }
 }
 __global__ void k_ctl_prepare(CgCtl* ctl, double rtol, int iters) { ctl_prepare_body(ctl, rtol, iters); }
+// A fresh control block for a system of unit right-hand side.
+__global__ __launch_bounds__(TPB) void k_ctl_begin(CgCtl* ctl, double rtol, int iters) {
+  for (int i = threadIdx.x; i < (int)(sizeof(CgCtl) / 8); i += TPB) reinterpret_cast<double*>(ctl)[i] = 0.0;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    ctl->bb = 1.0;
+    ctl->tol2 = rtol * rtol;
+    ctl->iters = ctl->one_iters[0] = ctl->one_iters[1] = iters;
+  }
+}
+void launch_ctl_begin(CgCtl* ctl, double rtol, int iters, hipStream_t s) {
+  hipLaunchKernelGGL(k_ctl_begin, dim3(1), dim3(TPB), 0, s, ctl, rtol, iters);
+}
 void launch_ctl_prepare(CgCtl* ctl, double rtol, int iters, hipStream_t s) {
   hipLaunchKernelGGL(k_ctl_prepare, dim3(1), dim3(64), 0, s, ctl, rtol, iters);
 }
@@ -408,34 +421,37 @@ void launch_norm2(int64_t n, const double* x, double* out, hipStream_t s, bool d
   hipLaunchKernelGGL(k_norm2, dim3(norm_grid(n, det)), dim3(NORM_NT), 0, s, n, x, out);
 }
 
-// r = b - q (n doubles), rr_true += r.r (ctl->rr_true cleared by the caller)
+// r = b - q (n doubles), rr_true += r.r (ctl->rr_true cleared by the caller),
+// q = 0 from value zero_from on
 __global__ __launch_bounds__(NORM_NT) void k_true_res(int64_t n, const double* __restrict__ b,
-                                                      const double* __restrict__ q, double* __restrict__ r,
-                                                      CgCtl* ctl) {
+                                                      double* __restrict__ q, double* __restrict__ r,
+                                                      int64_t zero_from, CgCtl* ctl) {
   __shared__ double sh[NORM_NT / 64];
   double acc = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * NORM_NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NORM_NT) {
     const double t = b[i] - q[i];
     r[i] = t;
+    if (i >= zero_from) q[i] = 0.0;
     acc += t * t;
   }
   acc = block_sum_n<NORM_NT>(acc, sh);
   if (threadIdx.x == 0) atomic_add(&ctl->rr_true, acc);
 }
-void launch_true_residual(int64_t n, const double* b, const double* q, double* r, CgCtl* ctl, hipStream_t s,
-                          bool det) {
-  hipLaunchKernelGGL(k_true_res, dim3(norm_grid(n, det)), dim3(NORM_NT), 0, s, n, b, q, r, ctl);
+void launch_true_residual(int64_t n, const double* b, double* q, double* r, int64_t zero_from, CgCtl* ctl,
+                          hipStream_t s, bool det) {
+  hipLaunchKernelGGL(k_true_res, dim3(norm_grid(n, det)), dim3(NORM_NT), 0, s, n, b, q, r, zero_from, ctl);
 }
 
 // Start of a refinement round in one pass: the FP32 inner system's
 // right-hand side r32 = r / ||r|| (||r||^2 = rr_true of ctl64, kept as its
 // scale), the inner solution d32 = 0, and the CG start z = P r32, p = z
-// with r32.z and r32.r32 into slot ring 0 of ctl32 (cleared beforehand).
-__global__ __launch_bounds__(TPB) void k_ir_begin(int64_t n_nodes, const double* __restrict__ r64,
+// with r32.z and r32.r32 into slot ring 0 of ctl32 (cleared beforehand).  w
+// (one-kernel iterations): cleared from node n_int on.
+__global__ __launch_bounds__(TPB) void k_ir_begin(int64_t n_nodes, int64_t n_int, const double* __restrict__ r64,
                                                   const __half* __restrict__ P, float* __restrict__ r32,
                                                   float* __restrict__ z32, float* __restrict__ p32,
-                                                  uint16_t* __restrict__ p16, float* __restrict__ d32, CgCtl* ctl64,
-                                                  CgCtl* ctl32) {
+                                                  uint16_t* __restrict__ p16, float* __restrict__ d32,
+                                                  float* __restrict__ w, CgCtl* ctl64, CgCtl* ctl32) {
   __shared__ double sh[2 * TPB / 64];
   const double nr = sqrt(ctl64->rr_true);
   const double inv = nr > 0.0 ? 1.0 / nr : 0.0;
@@ -455,6 +471,7 @@ __global__ __launch_bounds__(TPB) void k_ir_begin(int64_t n_nodes, const double*
       else
         p32[3 * i + c] = zv[c];
       d32[3 * i + c] = 0.0f;
+      if (w && i >= n_int) w[3 * i + c] = 0.0f;
       rz += (double)rv[c] * (double)zv[c];
       rr += (double)rv[c] * (double)rv[c];
     }
@@ -465,19 +482,21 @@ __global__ __launch_bounds__(TPB) void k_ir_begin(int64_t n_nodes, const double*
     atomic_add(&ctl32->rr[0][blockIdx.x % NSLOT], rr);
   }
 }
-void launch_ir_begin(int64_t n_nodes, const double* r64, const __half* P, float* r32, float* z32, float* p32,
-                     uint16_t* p16, float* d32, CgCtl* ctl64, CgCtl* ctl32, hipStream_t s) {
-  hipLaunchKernelGGL(k_ir_begin, dim3(vgrid(n_nodes)), dim3(TPB), 0, s, n_nodes, r64, P, r32, z32, p32, p16, d32,
-                     ctl64, ctl32);
+void launch_ir_begin(int64_t n_nodes, int64_t n_int, const double* r64, const __half* P, float* r32, float* z32,
+                     float* p32, uint16_t* p16, float* d32, float* w, CgCtl* ctl64, CgCtl* ctl32, hipStream_t s) {
+  hipLaunchKernelGGL(k_ir_begin, dim3(vgrid(n_nodes)), dim3(TPB), 0, s, n_nodes, n_int, r64, P, r32, z32, p32, p16,
+                     d32, w, ctl64, ctl32);
 }
 
+// x += scale d; clears rr_true for the true residual that follows
 __global__ __launch_bounds__(TPB) void k_ir_update(int64_t n, double* __restrict__ x, const float* __restrict__ d,
-                                                   const CgCtl* ctl) {
+                                                   CgCtl* ctl) {
   const double sc = ctl->scale;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctl->rr_true = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB)
     x[i] += sc * (double)d[i];
 }
-void launch_ir_update(int64_t n, double* x64, const float* d32, const CgCtl* ctl, hipStream_t s) {
+void launch_ir_update(int64_t n, double* x64, const float* d32, CgCtl* ctl, hipStream_t s) {
   unsigned g = nblocks(n);
   if (g > 8192) g = 8192;
   hipLaunchKernelGGL(k_ir_update, dim3(g), dim3(TPB), 0, s, n, x64, d32, ctl);
