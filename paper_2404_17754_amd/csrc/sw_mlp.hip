@@ -277,16 +277,19 @@ void launch_mlp_collect(const MlpFeat& F, const double* du, int count, uint64_t 
 // Gradient kernel: a wavefront takes 16 samples at a time through FP32 matrix
 // instructions (16x16x4: products and sums as in scalar FP32 code), four
 // wavefronts to a workgroup.  Hidden units are rows and samples columns, so
-// that a layer's output (lane (q, r): rows 16 b + 4 q + j of sample r) is the
-// next one's right operand as it stands: the instruction (b, j) sums over the
-// units 16 b + 4 q + j, and the weights are read in that order.  Only the
+// that a layer's output is the next one's right operand as it stands.  The
+// rows of a block are in the order grad_unit, which gives lane (q, r) the units
+// 16 b + 4 j + q of sample r: the instruction (b, j) sums over four consecutive
+// units (features), and a unit's input is the same chain of additions as in
+// scalar code (so the units at the edge of the rectifier are on the same side
+// of it; in another order some of a batch's half million are not).  Only the
 // weight gradients, sums over the samples, need the activations with the
 // samples across the lanes: they go through the LDS.  Per wavefront and 16
-// samples 16 + 64 instructions forward, 64 back, 64 + 16 for the weight
+// samples 12 + 64 + 16 instructions forward, 64 back, 64 + 16 for the weight
 // gradients, 32 cycles each: 3.5 us; the rest is latency (the rows, weights
 // and accumulators of a workgroup that has one pass to make).
 // 8192 rows, with the Adam step: 406 us as one work-item per sample in scalar
-// loops, 29 so (33 with the weights fetched one load after the other and the
+// loops, 28.7 so (33 with the weights fetched one load after the other and the
 // sums of a wavefront four to an LDS bank); 10 of them are the additions of
 // 128 workgroups to one gradient (100 rows: 19 us).
 // FP32 sums run over at most GFLUSH * 16 = 128 samples, then in FP64.
@@ -307,6 +310,9 @@ struct GradLds {
   } wave[GW];
 };
 
+// the unit of a block of 16 in its row r
+__device__ __forceinline__ int grad_unit(int r) { return 4 * (r & 3) + (r >> 2); }
+
 // sum over the 16 lanes of a row, in every lane
 __device__ __forceinline__ float row_sum(float v) {
   auto add = [](float a, int moved) { return a + __int_as_float(moved); };
@@ -326,16 +332,18 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
   extern __shared__ __align__(16) unsigned char smem_raw[];
   GradLds& L = *reinterpret_cast<GradLds*>(smem_raw);
   const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6, q = l >> 4, r = l & 15;
+  const int ru = grad_unit(r);
   const int64_t total = nb > 0 ? nb : n, step = (int64_t)gridDim.x * GW * GS;
   int64_t c0 = (int64_t)blockIdx.x * GW * GS;
-  // features 4q .. 4q+3 of sample r (q = 2: the last two, target and weight)
+  // values q, 4 + q and 8 + q of sample r (10 and 11: target and weight)
   auto load_row = [&](int64_t k) {
     floatx4 x = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (k < total && q < 3) {
+    if (k < total) {
       int64_t i = k;
       if (nb > 0) i = (int64_t)(splitmix64(seed ^ splitmix64((uint64_t)batch * 0x100000001B3ull + (uint64_t)k)) %
                                 (uint64_t)n);
-      x = *reinterpret_cast<const float4u*>(S + i * MLP_ROW + 4 * q);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) x[j] = S[i * MLP_ROW + 4 * j + q];
     }
     return x;
   };
@@ -398,8 +406,9 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
           atomicAdd(&L.acc[grad_at(r < MLP_IN ? MLP_OFF_W1 + u * MLP_IN + r : MLP_OFF_B1 + u)], (double)g1[c][j]);
         const float sb = row_sum(gb2[c][j]), sw = row_sum(gw3[c][j]);
         if (r == 0) {
-          atomicAdd(&L.acc[grad_at(MLP_OFF_B2 + u)], (double)sb);
-          atomicAdd(&L.acc[grad_at(MLP_OFF_W3 + u)], (double)sw);
+          const int v = 16 * c + 4 * j + q;
+          atomicAdd(&L.acc[grad_at(MLP_OFF_B2 + v)], (double)sb);
+          atomicAdd(&L.acc[grad_at(MLP_OFF_W3 + v)], (double)sw);
         }
       }
     const float s3 = row_sum(gb3);
@@ -412,42 +421,39 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
     const bool live = c0 + wv * GS + r < total;
     const floatx4 x = xr;
     xr = load_row(c0 + step + wv * GS + r);
-    const float xf[4] = {x.x, x.y, q == 2 ? 0.0f : x.z, q == 2 ? 0.0f : x.w};
-    const float target = __shfl(x.z, 32 + r, 64), weight = __shfl(x.w, 32 + r, 64);
+    const float xf[3] = {x.x, x.y, q < 2 ? x.z : 0.0f};
+    const float target = __shfl(x.z, 32 + r, 64), weight = __shfl(x.z, 48 + r, 64);
     floatx4 h1[4], h2[4], d2[4], z;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) z[j] = L.b1[16 * b + 4 * q + j];
+      for (int j = 0; j < 4; ++j) z[j] = L.b1[16 * b + 4 * j + q];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w1[(16 * b + r) * GLD + 4 * q + j], xf[j], z, 0, 0, 0);
+      for (int j = 0; j < 3; ++j)
+        z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w1[(16 * b + ru) * GLD + 4 * j + q], xf[j], z, 0, 0, 0);
 #pragma unroll
       for (int j = 0; j < 4; ++j) h1[b][j] = fmaxf(z[j], 0.0f);
     }
-    double y = 0.0;  // the output and its error in FP64
+    floatx4 y = {b3, b3, b3, b3};  // the output, in every row alike
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) z[j] = L.b2[16 * c + 4 * q + j];
+      for (int j = 0; j < 4; ++j) z[j] = L.b2[16 * c + 4 * j + q];
 #pragma unroll
       for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w2[(16 * c + r) * GLD2 + 16 * b + 4 * q + j], h1[b][j], z, 0, 0, 0);
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w2[(16 * c + ru) * GLD2 + 16 * b + 4 * j + q], h1[b][j], z, 0, 0, 0);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         h2[c][j] = fmaxf(z[j], 0.0f);
-        y += (double)L.w3[16 * c + 4 * q + j] * (double)h2[c][j];
+        y = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w3[16 * c + 4 * j + q], h2[c][j], y, 0, 0, 0);
       }
     }
-    y += __shfl_xor(y, 16, 64);
-    y += __shfl_xor(y, 32, 64);
-    y += (double)b3;
-    const double e = y - (double)target;
-    const float dy = live ? (float)(2.0 * (double)weight * e) : 0.0f;
+    const float e = y[0] - target;
+    const float dy = live ? 2.0f * weight * e : 0.0f;
     if (live && q == 0) {
-      lw += (double)weight * e * e;
+      lw += (double)weight * (double)e * (double)e;
       ww += (double)weight;
       gb3 += dy;
     }
@@ -455,7 +461,7 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
     for (int c = 0; c < 4; ++c)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int u = 16 * c + 4 * q + j;
+        const int u = 16 * c + 4 * j + q;
         d2[c][j] = h2[c][j] > 0.0f ? dy * L.w3[u] : 0.0f;
         gb2[c][j] += d2[c][j];
         gw3[c][j] += live ? dy * h2[c][j] : 0.0f;
@@ -469,14 +475,12 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
       for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w2[(16 * c + 4 * q + j) * GLD2 + 16 * b + r], d2[c][j], z, 0, 0, 0);
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w2[(16 * c + 4 * j + q) * GLD2 + 16 * b + ru], d2[c][j], z, 0, 0, 0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) W.d1[(16 * b + 4 * q + j) * GLD + r] = h1[b][j] > 0.0f ? z[j] : 0.0f;
+      for (int j = 0; j < 4; ++j) W.d1[(16 * b + 4 * j + q) * GLD + r] = h1[b][j] > 0.0f ? z[j] : 0.0f;
     }
-    if (q < 3) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) W.x[r * GLDX + 4 * q + j] = 4 * q + j == MLP_IN ? 1.0f : xf[j];
-    }
+    for (int j = 0; j < 3; ++j) W.x[r * GLDX + 4 * j + q] = 4 * j + q == MLP_IN ? 1.0f : xf[j];
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
