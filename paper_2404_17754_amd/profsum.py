@@ -47,7 +47,7 @@ def trace(db, out, command, top=16):
                      f"{100.0 * tot / total:6.1f}")
     lines.append(f"(total kernel time {total / 1e6:.1f} ms over {sum(r[1] for r in rows)} dispatches)")
     # full launches of the tile kernels (early exits after convergence left out)
-    for pat in ("k_tile_pipe<", "k_tile_lanes_pipe<", "k_tile_dir<", "k_tile_lanes_cg<", "k_tile<float", "k_tile<double"):
+    for pat in ("k_tile_pipe<", "k_tile_lanes_pipe<", "k_tile_cg<", "k_tile_dir<", "k_tile_lanes_cg<", "k_tile<float", "k_tile<double"):
         d = [r[0] for r in con.execute("select end - start from kernels where name like ?", (f"%{pat}%",))]
         if d:
             mx = max(d)
@@ -58,7 +58,7 @@ def trace(db, out, command, top=16):
     # interval within the span from the first to the last launch of the
     # operator pass (host decisions, synchronisations and launch gaps are
     # the idle rest)
-    for pat in ("k_tile_pipe<", "k_tile_lanes_pipe<", "k_tile_dir<", "k_tile_lanes_cg<", "k_tile<float"):
+    for pat in ("k_tile_pipe<", "k_tile_lanes_pipe<", "k_tile_cg<", "k_tile_dir<", "k_tile_lanes_cg<", "k_tile<float"):
         w = con.execute("select min(start), max(end) from kernels where name like ?", (f"%{pat}%",)).fetchone()
         if not w or w[0] is None:
             continue
