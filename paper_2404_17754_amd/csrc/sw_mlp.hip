@@ -289,9 +289,9 @@ void launch_mlp_collect(const MlpFeat& F, const double* du, int count, uint64_t 
 // gradients, 32 cycles each: 3.5 us; the rest is latency (the rows, weights
 // and accumulators of a workgroup that has one pass to make).
 // 8192 rows, with the Adam step: 406 us as one work-item per sample in scalar
-// loops, 28.7 so (33 with the weights fetched one load after the other and the
-// sums of a wavefront four to an LDS bank); 10 of them are the additions of
-// 128 workgroups to one gradient (100 rows: 19 us).
+// loops, 21.3 so (33 with the weights fetched one load after the other and the
+// sums of a wavefront four to an LDS bank, 28.7 with an addition of the loss
+// per wavefront instead of one per workgroup).
 // FP32 sums run over at most GFLUSH * 16 = 128 samples, then in FP64.
 constexpr int GW = 4, GS = 16, GFLUSH = 8;
 constexpr int GLD = 17, GLD2 = 65, GLDX = 13;  // row strides that spread the LDS banks
@@ -304,6 +304,7 @@ __device__ __forceinline__ int grad_at(int j) {
 }
 struct GradLds {
   double acc[GRAD_ACC + (GRAD_ACC & 1)];
+  double loss[2 * GW];
   float w1[MLP_H * GLD], w2[MLP_H * GLD2], b1[MLP_H], b2[MLP_H], w3[MLP_H];
   struct {
     float h1[MLP_H * GLD], d1[MLP_H * GLD], d2[MLP_H * GLD], x[GS * GLDX];
@@ -504,10 +505,16 @@ __global__ __launch_bounds__(64 * GW) void k_mlp_grad(const float* __restrict__ 
   lw = wave_sum(lw);
   ww = wave_sum(ww);
   if (l == 0) {
-    atomic_add(&loss2[0], lw);
-    atomic_add(&loss2[1], ww);
+    L.loss[wv] = lw;
+    L.loss[GW + wv] = ww;
   }
   __syncthreads();
+  if (tid < 2) {  // one addition a workgroup to each (12 ns apiece on one address)
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < GW; ++k) t += L.loss[GW * tid + k];
+    atomic_add(&loss2[tid], t);
+  }
 #pragma unroll 4
   for (int j = tid; j < MLP_NP; j += 64 * GW) {
     const double a = L.acc[grad_at(j)];
