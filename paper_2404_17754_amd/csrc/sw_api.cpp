@@ -1283,8 +1283,8 @@ int capture_stream(sw_ctx* cx, hipStream_t* out) {
 
 // Iterations of a captured graph: even (the kernels' arguments repeat with the
 // iteration's parity).  The host needs 4-5 us to launch a kernel directly and
-// about as much for a whole graph, while an iteration of a small mesh takes
-// 14 us on the GPU and a skipped one 4 us.
+// about as much for a whole graph, as long as an iteration of one kernel takes
+// on a small mesh.
 constexpr int GRAPH_ITERS = 8;
 // the same for one-kernel iterations, whose arguments repeat every six
 constexpr int GRAPH_ITERS_ONE = 6;

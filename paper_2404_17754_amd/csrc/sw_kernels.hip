@@ -253,10 +253,10 @@ __global__ __launch_bounds__(NT) void k_cg_step(int64_t n, int64_t n_int, int pa
   }
   // Each XCD's nodes (workgroup b runs on XCD b mod 8): an eighth of the
   // interior nodes and an eighth of the shared ones, about those of the tiles
-  // the operator pass gives it, so that z, p and q stay in its L2: 26.0 us an
-  // iteration against 27.0 at 0.27 M nodes, 46.3 against 48.4 at 0.6 M.  Past
-  // STEP_XCD_NODES, where the caches no longer hold them, one stream over all
-  // nodes (FP64 at 2.1 M nodes: 215 us against 222).
+  // the operator pass gives it, so that z, p and q stay in its L2: 46.3 us an
+  // iteration against 48.4 at 0.6 M nodes.  Past STEP_XCD_NODES, where the
+  // caches no longer hold them, one stream over all nodes (FP64 at 2.1 M
+  // nodes: 215 us against 222).
   int64_t i0 = 0, ci = n_int, s0 = n_int, cs = n - n_int;
   int64_t l = (int64_t)blockIdx.x * NT + threadIdx.x, stride = (int64_t)gridDim.x * NT;
   if (n <= STEP_XCD_NODES) {
