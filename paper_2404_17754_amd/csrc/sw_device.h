@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace sw {
 
 constexpr int TPB = 256;
@@ -119,6 +121,44 @@ __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, doub
       c += sh[2 * NT / 64 + i];
     }
   }
+}
+
+// Sums over the times of records that lie pair by pair within a time:
+// workgroups of PAIR_NT work-items with MP neighbouring pairs side by side
+// (work-item t: pair t % MP), so that a load of many pairs is whole lines and a
+// few long records still have many work-items each.  MP by the pairs (misfit
+// call, us, at MP = 1 / 4 / 8 / 16): 6 pairs of 20000 steps 38 / 48 / 63 / 97,
+// 18 of 100000 253 / 283 / 295 / 426, 60 of 20000 80 / 78 / 91 / 116, 300 of
+// 5000 68 / 46 / 48 / 54, 1200 of 20000 586 / 269 / 146 / 171, 9000 of 500
+// 135 / 92 / 75 / 68.
+constexpr int PAIR_NT = 1024;
+template <typename F>
+void by_pair_width(int n_pairs, F&& launch) {
+  if (n_pairs <= 24)
+    launch(std::integral_constant<int, 1>());
+  else if (n_pairs <= 300)
+    launch(std::integral_constant<int, 4>());
+  else if (n_pairs <= 1500)
+    launch(std::integral_constant<int, 8>());
+  else
+    launch(std::integral_constant<int, 16>());
+}
+
+// The sums of such a workgroup's values, valid on the first MP work-items; sh
+// holds PAIR_NT / 64 * MP doubles.
+template <int MP>
+__device__ __forceinline__ double pair_sum(double v, double* sh) {
+#pragma unroll
+  for (int off = MP; off < 64; off *= 2) v += __shfl_xor(v, off, 64);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (lane < MP) sh[wid * MP + lane] = v;
+  __syncthreads();
+  if (threadIdx.x < MP) {
+    v = 0.0;
+#pragma unroll
+    for (int k = 0; k < PAIR_NT / 64; ++k) v += sh[k * MP + threadIdx.x];
+  }
+  return v;
 }
 
 // A pointer read from a table in memory, known to point to global memory: its

@@ -17,27 +17,23 @@
 
 namespace sw {
 
-// o2[pair] = sum_t obs[t][pair]^2: 16 pairs by 64 times a workgroup, so that a
-// load of the records, which lie pair by pair within a time, is whole lines
-constexpr int NP = 16, NTIME = 64;
-__global__ __launch_bounds__(NP* NTIME) void k_fit_pair_norms(int n_pairs, int64_t n_steps,
-                                                              const double* __restrict__ obs,
-                                                              double* __restrict__ o2) {
-  __shared__ double sh[NTIME][NP + 1];
-  const int px = threadIdx.x % NP, ty = threadIdx.x / NP, pr = blockIdx.x * NP + px;
+// o2[pair] = sum_t obs[t][pair]^2: MP neighbouring pairs by PAIR_NT / MP times a
+// workgroup (by_pair_width)
+template <int MP>
+__global__ __launch_bounds__(PAIR_NT) void k_fit_pair_norms(int n_pairs, int64_t n_steps,
+                                                            const double* __restrict__ obs, double* __restrict__ o2) {
+  __shared__ double sh[PAIR_NT / 64 * MP];
+  const int pr = blockIdx.x * MP + threadIdx.x % MP;
   double s = 0.0;
-  if (pr < n_pairs)
-    for (int64_t t = ty; t < n_steps; t += NTIME) {
+  if (pr < n_pairs) {
+#pragma unroll 4
+    for (int64_t t = threadIdx.x / MP; t < n_steps; t += PAIR_NT / MP) {
       const double o = obs[t * n_pairs + pr];
       s += o * o;
     }
-  sh[ty][px] = s;
-  __syncthreads();
-  if (threadIdx.x < NP && pr < n_pairs) {
-    s = 0.0;
-    for (int k = 0; k < NTIME; ++k) s += sh[k][px];
-    o2[pr] = s;
   }
+  s = pair_sum<MP>(s, sh);
+  if (threadIdx.x < MP && pr < n_pairs) o2[pr] = s;
 }
 
 // w[pair] = 1 / o2[pair], zero for pairs whose norm is <= 1e-12 of the
@@ -211,8 +207,11 @@ __global__ __launch_bounds__(TPB) void k_fit_response(FitSrc S, int n_shift, con
 }
 
 void launch_fit_weights(int n_pairs, int64_t n_steps, const double* obs, double* o2, double* w, hipStream_t s) {
-  hipLaunchKernelGGL(k_fit_pair_norms, dim3((n_pairs + NP - 1) / NP), dim3(NP * NTIME), 0, s, n_pairs, n_steps, obs,
-                     o2);
+  by_pair_width(n_pairs, [&](auto w) {
+    constexpr int MP = decltype(w)::value;
+    hipLaunchKernelGGL(k_fit_pair_norms<MP>, dim3((n_pairs + MP - 1) / MP), dim3(PAIR_NT), 0, s, n_pairs, n_steps, obs,
+                       o2);
+  });
   hipLaunchKernelGGL(k_fit_weights, dim3(1), dim3(TPB), 0, s, n_pairs, o2, w);
 }
 

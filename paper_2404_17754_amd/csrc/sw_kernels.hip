@@ -670,32 +670,27 @@ void launch_record(int n_rec, const int32_t* rec, const double* v, double* row, 
 // --------------------------------------------------------------- misfit
 
 // pair_buf[2 * pair] = sum_t (U - obs)^2, pair_buf[2 * pair + 1] = sum_t obs^2:
-// 16 pairs by 64 times a workgroup, so that a load of the records, which lie
-// pair by pair within a time, is whole lines (1200 pairs of 1000 steps: 23 us
-// with one workgroup per pair, 8 so)
-constexpr int MP = 16, MTIME = 64;
-__global__ __launch_bounds__(MP* MTIME) void k_misfit_pairs(int n_pairs, int64_t n_steps,
-                                                            const double* __restrict__ U,
-                                                            const double* __restrict__ obs,
-                                                            double* __restrict__ buf) {
-  __shared__ double sd[MTIME][MP + 1], so[MTIME][MP + 1];
-  const int px = threadIdx.x % MP, ty = threadIdx.x / MP, pr = blockIdx.x * MP + px;
+// MP neighbouring pairs by PAIR_NT / MP times a workgroup (by_pair_width)
+template <int MP>
+__global__ __launch_bounds__(PAIR_NT) void k_misfit_pairs(int n_pairs, int64_t n_steps, const double* __restrict__ U,
+                                                          const double* __restrict__ obs, double* __restrict__ buf) {
+  __shared__ double sd[PAIR_NT / 64 * MP], so[PAIR_NT / 64 * MP];
+  const int pr = blockIdx.x * MP + threadIdx.x % MP;
   double d2 = 0.0, o2 = 0.0;
-  if (pr < n_pairs)
-    for (int64_t t = ty; t < n_steps; t += MTIME) {
+  if (pr < n_pairs) {
+#pragma unroll 4
+    for (int64_t t = threadIdx.x / MP; t < n_steps; t += PAIR_NT / MP) {
       const double o = obs[t * n_pairs + pr];
       const double d = U[t * n_pairs + pr] - o;
       d2 += d * d;
       o2 += o * o;
     }
-  sd[ty][px] = d2;
-  so[ty][px] = o2;
-  __syncthreads();
-  if (threadIdx.x < 2 * MP && pr < n_pairs) {
-    const double(*sh)[MP + 1] = threadIdx.x < MP ? sd : so;
-    double t = 0.0;
-    for (int k = 0; k < MTIME; ++k) t += sh[k][px];
-    buf[2 * pr + (threadIdx.x < MP ? 0 : 1)] = t;
+  }
+  d2 = pair_sum<MP>(d2, sd);
+  o2 = pair_sum<MP>(o2, so);
+  if (threadIdx.x < MP && pr < n_pairs) {
+    buf[2 * pr] = d2;
+    buf[2 * pr + 1] = o2;
   }
 }
 
@@ -736,7 +731,11 @@ __global__ __launch_bounds__(TPB) void k_misfit_final(int n_pairs, const double*
 void launch_misfit(int n_rec, int64_t n_steps, const double* U, const double* obs, double* pair_buf, double* out2,
                    hipStream_t s) {
   const int np = 3 * n_rec;
-  hipLaunchKernelGGL(k_misfit_pairs, dim3((np + MP - 1) / MP), dim3(MP * MTIME), 0, s, np, n_steps, U, obs, pair_buf);
+  by_pair_width(np, [&](auto w) {
+    constexpr int MP = decltype(w)::value;
+    hipLaunchKernelGGL(k_misfit_pairs<MP>, dim3((np + MP - 1) / MP), dim3(PAIR_NT), 0, s, np, n_steps, U, obs,
+                       pair_buf);
+  });
   hipLaunchKernelGGL(k_misfit_final, dim3(1), dim3(TPB), 0, s, np, pair_buf, out2);
 }
 
