@@ -75,9 +75,10 @@ __device__ __forceinline__ const double* fit_col(const FitSrc& S, int col) {
 }
 
 // C = X^T diag(w) X for the 4 nb block columns, on the FP64 matrix
-// instructions (16x16x4), 64 x 64 output tiles (the upper ones), rows in
-// chunks of FK pairs at one time r, which are contiguous in the records.  A
-// workgroup takes a share (blockIdx.y) of the chunks, and the shares' results
+// instructions (16x16x4), 64 x 64 output tiles (the upper ones).  The m times
+// of a block by the pairs are one contiguous run of rows in the records, taken
+// in chunks of FK across the times (with chunks that ended at each time, three
+// pairs filled 3 of a chunk's 32 rows).  A workgroup takes a share (blockIdx.y) of the chunks, and the shares' results
 // are added in their order by k_fit_sum, since the few tiles of a fit (10 at
 // 200 columns) would leave most of the chip idle.  Four wavefronts of 32 x 32.
 // 200 columns of 24000 rows: 1354 us with one output per work-item and rows
@@ -92,9 +93,9 @@ __global__ __launch_bounds__(256) void k_fit_gram(FitSrc S, const double* __rest
   while (rest >= nt - ta) rest -= nt - ta++;
   const int tb = ta + rest;
   const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
-  const int pchunks = (S.n_pairs + FK - 1) / FK, chunks = S.m * pchunks;
-  const int c0 = (int)((int64_t)chunks * blockIdx.y / gridDim.y), c1 = (int)((int64_t)chunks * (blockIdx.y + 1) / gridDim.y);
-  // each work-item loads pair kk of columns row0, row0 + 8, ...
+  const int64_t rows = (int64_t)S.m * S.n_pairs, chunks = (rows + FK - 1) / FK;
+  const int64_t c0 = chunks * blockIdx.y / gridDim.y, c1 = chunks * (blockIdx.y + 1) / gridDim.y;
+  // each work-item loads row kk of a chunk of columns row0, row0 + 8, ...
   const int kk = tid % FK, row0 = tid / FK;
   constexpr int PER = FT * FK / 256;
   const double *pa[PER], *pb[PER];  // null past the last column
@@ -105,11 +106,15 @@ __global__ __launch_bounds__(256) void k_fit_gram(FitSrc S, const double* __rest
     pb[q] = cb < ncol ? fit_col(S, cb) : nullptr;
   }
   double ra[PER], rb[PER];
-  auto load = [&](int c) {
-    const int r = c / pchunks, pair = (c - r * pchunks) * FK + kk;
-    const bool in = pair < S.n_pairs;
+  // the row's pair, moved along from chunk to chunk
+  int pair = (int)((c0 * FK + kk) % S.n_pairs);
+  const int pair_step = FK % S.n_pairs;
+  auto load = [&](int64_t c) {
+    const int64_t at = c * FK + kk;
+    const bool in = at < rows;
     const double wp = in ? w[pair] : 0.0;
-    const int64_t at = (int64_t)r * S.n_pairs + pair;
+    pair += pair_step;
+    if (pair >= S.n_pairs) pair -= S.n_pairs;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       ra[q] = in && pa[q] ? wp * pa[q][at] : 0.0;
@@ -119,7 +124,7 @@ __global__ __launch_bounds__(256) void k_fit_gram(FitSrc S, const double* __rest
   doublex4 acc[2][2] = {};
   const int a0 = (wv >> 1) * 32 + (l & 15), b0 = (wv & 1) * 32 + (l & 15), k0 = l >> 4;
   if (c0 < c1) load(c0);
-  for (int c = c0; c < c1; ++c) {
+  for (int64_t c = c0; c < c1; ++c) {
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -221,7 +226,7 @@ void launch_fit_gram(const double* const g[3], const double* obs, int n_pairs, i
   const int ncol = 4 * nb, nt = (ncol + FT - 1) / FT, tiles = nt * (nt + 1) / 2;
   // shares: two workgroups per compute unit, as far as there are chunks and
   // room for the shares' results
-  const int64_t chunks = (int64_t)m * ((n_pairs + FK - 1) / FK), room = scratch_len / ((int64_t)ncol * ncol);
+  const int64_t chunks = ((int64_t)m * n_pairs + FK - 1) / FK, room = scratch_len / ((int64_t)ncol * ncol);
   int64_t shares = (512 + tiles - 1) / tiles;
   shares = shares < chunks ? shares : chunks;
   shares = shares < room ? shares : room;

@@ -1,0 +1,52 @@
+"""The rows of the input estimation's Gram matrix, the times of a block by the
+pairs, in chunks of 32 across the times: pairs that do not divide a chunk, more
+pairs than a chunk has rows, ragged last chunks, shares that start within a
+time; and few receivers with long blocks no slower than many with short ones."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import inversion as inv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sw():
+    import paper_2404_17754_amd as sw
+    return sw
+
+
+@pytest.mark.parametrize("n_rec,stride,blocks,shifts", [(1, 11, 4, 4), (1, 200, 3, 2), (3, 64, 5, 3), (10, 13, 4, 4),
+                                                        (11, 31, 3, 3), (21, 50, 2, 2), (43, 3, 6, 5), (7, 97, 12, 12)])
+def test_coefficients(sw, n_rec, stride, blocks, shifts):
+    rng = np.random.default_rng(n_rec * stride)
+    n = stride * blocks
+    G = [rng.standard_normal((n, n_rec, 3)) for _ in range(3)]
+    obs = rng.standard_normal((n, n_rec, 3)) * rng.uniform(0.3, 3.0, (n_rec, 3))  # the pairs' weights differ
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    got = sw.fit_input(sw.Context(0), [dev(g) for g in G], dev(obs), stride, shifts)[0]
+    want = np.asarray(inv.fit(G, obs, stride, shifts)[0]).reshape(3, shifts)
+    # random records: a Gram matrix of condition below 100; sums of n rows
+    assert np.linalg.norm(got - want) <= 100 * n ** 0.5 * 2.3e-16 * np.linalg.norm(want) + 1e-13
+
+
+def test_few_receivers_with_long_blocks(sw):
+    """9600 rows a block both times, so the same products."""
+    ctx = sw.Context(0)
+    t = {}
+    for n_rec, stride in ((1, 3200), (32, 100)):
+        g = torch.Generator("cuda").manual_seed(1)
+        G = [torch.randn(stride * 20, n_rec, 3, dtype=torch.float64, device="cuda", generator=g) for _ in range(3)]
+        obs = torch.randn(stride * 20, n_rec, 3, dtype=torch.float64, device="cuda", generator=g)
+        best = []
+        for _ in range(10):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            sw.fit_input(ctx, G, obs, stride, 2)
+            best.append(time.perf_counter() - t0)
+        t[n_rec] = min(best)
+    print(t)
+    assert t[1] <= 2 * t[32]
