@@ -162,15 +162,19 @@ __global__ __launch_bounds__(256) void k_fit_gram(FitSrc S, const double* __rest
 
 // C's upper triangle = the sum of the shares in their order, mirrored (the
 // (a, b) and (b, a) products round differently: one of them serves both).
-// part may be C itself when there is one share.
+// part may be C itself when there is one share.  A row of workgroups takes
+// every SUM_ROWS-th row: the second grid dimension ends at 65535.
+constexpr int SUM_ROWS = 1024;
 __global__ __launch_bounds__(TPB) void k_fit_sum(int ncol, int shares, const double* part, double* C) {
-  const int col = blockIdx.x * TPB + threadIdx.x, row = blockIdx.y;
-  if (col >= ncol || col < row) return;
-  const size_t at = (size_t)row * ncol + col;
-  double s = 0.0;
-  for (int k = 0; k < shares; ++k) s += part[(size_t)k * ncol * ncol + at];
-  C[at] = s;
-  C[(size_t)col * ncol + row] = s;
+  const int col = blockIdx.x * TPB + threadIdx.x;
+  for (int row = blockIdx.y; row < ncol; row += SUM_ROWS) {
+    if (col >= ncol || col < row) continue;
+    const size_t at = (size_t)row * ncol + col;
+    double s = 0.0;
+    for (int k = 0; k < shares; ++k) s += part[(size_t)k * ncol * ncol + at];
+    C[at] = s;
+    C[(size_t)col * ncol + row] = s;
+  }
 }
 
 // U[t][pair] = sum_j sum_{l <= t/m, l < n_shift} c[j][l] G_j[t - l m][pair]:
@@ -233,7 +237,8 @@ void launch_fit_gram(const double* const g[3], const double* obs, int n_pairs, i
   double* part = shares > 1 ? scratch : C;
   if (shares < 1) shares = 1;
   hipLaunchKernelGGL(k_fit_gram, dim3(tiles, (unsigned)shares), dim3(256), 0, s, S, w, ncol, nt, part);
-  hipLaunchKernelGGL(k_fit_sum, dim3((ncol + TPB - 1) / TPB, ncol), dim3(TPB), 0, s, ncol, (int)shares, part, C);
+  hipLaunchKernelGGL(k_fit_sum, dim3((ncol + TPB - 1) / TPB, ncol < SUM_ROWS ? ncol : SUM_ROWS), dim3(TPB), 0, s, ncol,
+                     (int)shares, part, C);
 }
 
 void launch_fit_response(const double* const g[3], int n_pairs, int m, int n_shift, int64_t n_steps,

@@ -50,3 +50,14 @@ def test_few_receivers_with_long_blocks(sw):
         t[n_rec] = min(best)
     print(t)
     assert t[1] <= 2 * t[32]
+
+
+def test_more_columns_than_rows_of_workgroups(sw):
+    """1200 block columns: their sums in more than one round of 1024 rows."""
+    rng = np.random.default_rng(3)
+    G = [rng.standard_normal((600, 2, 3)) for _ in range(3)]
+    obs = rng.standard_normal((600, 2, 3))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    got = sw.fit_input(sw.Context(0), [dev(g) for g in G], dev(obs), 2, 4)[0]
+    want = np.asarray(inv.fit(G, obs, 2, 4)[0]).reshape(3, 4)
+    assert np.linalg.norm(got - want) <= 100 * 600 ** 0.5 * 2.3e-16 * np.linalg.norm(want) + 1e-13
