@@ -2327,7 +2327,7 @@ extern "C" int sw_mlp_train(sw_mlp* o, const float* S, int64_t n, int32_t steps,
   if (!o || !S || n <= 0 || steps < 0 || batch <= 0 || !(lr > 0.0f)) return fail(SW_EINVAL, "bad arguments");
   HIPC(hipSetDevice(o->ctx->device));
   hipStream_t s = o->ctx->stream;
-  std::vector<double> l2(loss ? 2 * (size_t)std::min(steps, LOSS_RING) : 0);
+  double l2[2 * LOSS_RING];
   for (int k0 = 0; k0 < steps; k0 += LOSS_RING) {
     const int m = std::min(LOSS_RING, steps - k0);
     launch_fill_f64(2 * m, o->loss2, 0.0, s);
@@ -2338,7 +2338,7 @@ extern "C" int sw_mlp_train(sw_mlp* o, const float* S, int64_t n, int32_t steps,
     }
     LAUNCHED();
     if (loss) {
-      HIPC(hipMemcpyAsync(l2.data(), o->loss2, 16 * (size_t)m, hipMemcpyDeviceToHost, s));
+      HIPC(hipMemcpyAsync(l2, o->loss2, 16 * (size_t)m, hipMemcpyDeviceToHost, s));
       HIPC(hipStreamSynchronize(s));
       for (int k = 0; k < m; ++k) loss[k0 + k] = l2[2 * k + 1] > 0.0 ? (float)(l2[2 * k] / l2[2 * k + 1]) : 0.0f;
     }
