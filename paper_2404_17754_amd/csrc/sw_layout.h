@@ -25,18 +25,24 @@ constexpr int TILE_MAX_ELEMS = 1024;
 // at 512 elements against 0.424 ms at 1024 (node-limited).
 constexpr int TILE_DEFAULT_ELEMS = 512;
 // Smaller ones on meshes whose tiles would not fill the 256 compute units,
-// where a pass takes as long as one tile: 96 tiles of at least 64 and at most
-// 384 elements, then up to 256 tiles.  A step of FP32 iterations / of FP64
-// ones, us: 3072 tets, 512 elements 1480 / 1709, 256 1253 / 1346, 64 1143 /
-// 1149; 24 000 tets, 512 1526 / 1814, 256 1335 / 1431; 98 000 tets, 512 1719 /
-// 2283, 384 1606 / 2165, 256 1741 / 2831.  No smaller on 24 000 tets (128
-// elements: 1229 us): several such cases in a batch fill the chip, and there
-// the nodes shared by more tiles cost time (8 cases, 512 elements 4617 us a
-// step, 256 4545, 128 5258).
+// where a pass takes as long as one tile: about ten tiles of 64 elements or
+// more, up to 192 elements, then 96 tiles of up to 384, then up to 256 tiles.
+// In a batch of many cases the chip is full and the nodes shared by more tiles
+// cost time, so the sizes are those that serve both.  Four steps of one mixed
+// case / of a batch of 64 (24 000 tets and less: 128), ms:
+//   tets     elements 64         128         192         256         512
+//     1296       4.52/40.6   4.53/35.8   4.63/35.2               5.72/34.5
+//     3072       4.59/59.3   4.66/49.5   4.68/46.1   5.01/44.7   5.86/43.2
+//     6912   (72) 4.57/51.2  4.55/42.3   4.57/37.3   4.94/37.8   5.76/36.9
+//    15360  (160) 4.74/62.7              4.74/59.6   5.06/54.9   5.73/52.6
+//    24000                   4.79/174    4.91/148    5.21/137    5.94/121
+// (6912 and 15360: batches of 64).  98 000 tets, one step: 512 elements 1719 us,
+// 384 1606, 256 1741.
 inline int default_tile_elems(int64_t n_tets) {
   if (n_tets > 256 * (int64_t)TILE_DEFAULT_ELEMS) return TILE_DEFAULT_ELEMS;
+  const int64_t few = std::max<int64_t>(64, std::min<int64_t>(n_tets / 10, 192));
   const int64_t spread = std::min<int64_t>((n_tets + 95) / 96, 384);
-  return (int)std::max<int64_t>(64, std::max(spread, (n_tets + 255) / 256));
+  return (int)std::max(few, std::max(spread, (n_tets + 255) / 256));
 }
 
 struct HostLayout {
