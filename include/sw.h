@@ -459,6 +459,11 @@ SW_API int sw_batch_autotune(sw_batch* b, int32_t reps, int32_t* choice, double*
  * inside the operator pass keeps one workgroup per tile for its march.
  * Synchronous. */
 SW_API int sw_case_autotune(sw_case* c, int32_t reps, int32_t* choice, double* ms);
+/* How the case's next step would run now (either pointer may be NULL): kernels
+ * per CG iteration (1: all in the operator pass, 2: the direction in it, 3) and
+ * the workgroup cap of its FP32 operator pass (0: one per tile, and in FP64).
+ * For tests and tuning. */
+SW_API int sw_case_schedule(const sw_case* c, int32_t* kernels, int32_t* max_workgroups);
 /* Statistics of every lane (out: n entries, lane order; as
  * sw_case_stats_get of each case). */
 SW_API int sw_batch_stats(const sw_batch* b, sw_case_stats* out);

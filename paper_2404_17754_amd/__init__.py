@@ -248,6 +248,13 @@ class Case:
         L.check(self.ctx.lib.sw_case_autotune(self.h, int(reps), C.byref(ch), _ptr(ms)))
         return ch.value, ms
 
+    def schedule(self):
+        """(kernels per CG iteration, workgroup cap of the FP32 pass) of the
+        next step (sw_case_schedule)."""
+        k, cap = C.c_int32(), C.c_int32()
+        L.check(self.ctx.lib.sw_case_schedule(self.h, C.byref(k), C.byref(cap)))
+        return k.value, cap.value
+
     def rhs(self):
         torch = _torch()
         y = torch.empty(self.n_dof, dtype=torch.float64, device=self.ctx.device)

@@ -107,6 +107,7 @@ SIGNATURES = {
     "sw_batch_stats": (VP, C.POINTER(CaseStats)),
     "sw_batch_autotune": (VP, I32, C.POINTER(I32), VP),
     "sw_case_autotune": (VP, I32, C.POINTER(I32), VP),
+    "sw_case_schedule": (VP, C.POINTER(I32), C.POINTER(I32)),
     "sw_batch_apply_f32": (VP, C.POINTER(VP), C.POINTER(VP)),
     "sw_batch_destroy": (VP,),
 }

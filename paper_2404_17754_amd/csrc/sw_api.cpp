@@ -2931,22 +2931,37 @@ extern "C" int sw_case_autotune(sw_case* c, int32_t reps, int32_t* choice, doubl
   // launch runs in full; the inner-solve vectors are free between steps
   launch_fill_f32(nd, c->p32, 0.0f, s);
   launch_fill_f32(nd, c->q32, 0.0f, s);
+  if (c->p16) launch_fill_f32((nd + 1) / 2, (float*)c->p16, 0.0f, s);  // its place ends at a multiple of 256 bytes
   const int caps[3] = {0, 8 * std::max(1, 2 * n_cu / 8), 8 * std::max(1, n_cu / 8)};
   double ms[3];
   int best = 0;
   for (int k = 0; k < 3; ++k) {
     c->grid_cap = caps[k];
     launch_fill_f64(sizeof(CgCtl) / 8, (double*)c->ctl32, 0.0, s);
-    int rc = time_launches(s, reps, [&] { apply_f32(c, SW_OP_A, c->p32, c->q32, c->ctl32, 1); }, &ms[k]);
+    // the pass that the case's iterations launch
+    int rc = time_launches(s, reps, [&] {
+      c->p16 ? apply_f32_h(c, c->p16, c->q32, c->ctl32, 1, s) : apply_f32(c, SW_OP_A, c->p32, c->q32, c->ctl32, 1);
+    }, &ms[k]);
     if (rc) return rc;
     if (ms[k] < ms[best]) best = k;
   }
   LAUNCHED();
-  // one- and two-kernel iterations have one workgroup per tile
-  c->grid_cap = two_kernel_cg(c->mesh->dev, 0, true) ? 0 : caps[best];
+  // one- and two-kernel iterations have one workgroup per tile; 16-bit cases
+  // run three kernels on meshes of any size
+  c->grid_cap = !c->p16 && two_kernel_cg(c->mesh->dev, 0, true) ? 0 : caps[best];
   if (choice) *choice = best;
   if (ms_out)
     for (int k = 0; k < 3; ++k) ms_out[k] = ms[k];
+  return SW_OK;
+}
+
+extern "C" int sw_case_schedule(const sw_case* c, int32_t* kernels, int32_t* max_workgroups) {
+  if (!c) return fail(SW_EINVAL, "NULL case");
+  const bool f32 = c->precision != SW_FP64;
+  const bool one = f32 ? one_kernel<true>(c) : one_kernel<false>(c);
+  const bool two = f32 ? two_kernel<true>(c) : two_kernel<false>(c);
+  if (kernels) *kernels = one ? 1 : two ? 2 : 3;
+  if (max_workgroups) *max_workgroups = f32 ? case_grid_cap(c) : 0;
   return SW_OK;
 }
 
