@@ -18,12 +18,17 @@ from __future__ import annotations
 import collections
 import hashlib
 import os
+import re
 import sqlite3
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # the sources that define the operator kernels and the layout they read
 KERNEL_SOURCES = ["sw_tile.hip", "sw_elem.h", "sw_device.h", "sw_layout.h", "sw_mesh.cpp", "sw_bf16.h"]
+
+# tile kernels outside the CG iterations: the diagonal, the right-hand side, the
+# true residuals
+ONCE_A_STEP = {"k_tile_diag<", "k_tile_rhs<", "k_tile<double", "k_tile_lanes<double"}
 
 
 def kernel_hash():
@@ -46,23 +51,28 @@ def trace(db, out, command, top=16):
         lines.append(f"{short:62s} {n:7d} {avg / 1e3:10.1f} {mn / 1e3:9.1f} {mx / 1e3:9.1f} {tot / 1e6:10.2f} "
                      f"{100.0 * tot / total:6.1f}")
     lines.append(f"(total kernel time {total / 1e6:.1f} ms over {sum(r[1] for r in rows)} dispatches)")
-    # full launches of the tile kernels (early exits after convergence left out)
-    for pat in ("k_tile_pipe<", "k_tile_lanes_pipe<", "k_tile_cg<", "k_tile_dir<", "k_tile_lanes_cg<", "k_tile<float", "k_tile<double"):
-        d = [r[0] for r in con.execute("select end - start from kernels where name like ?", (f"%{pat}%",))]
-        if d:
-            mx = max(d)
-            full = [x for x in d if x >= 0.5 * mx]
-            lines.append(f"{pat}: {len(d)} launches, mean over all {sum(d) / len(d) / 1e3:.1f} us, "
+    # full launches of the tile kernels (early exits after convergence left
+    # out), every instance by itself: a launch under half the longest of another
+    # instance's (a capped grid, the autotuner's candidates) is no early exit
+    tiles = collections.defaultdict(dict)
+    for name in sorted({r[0] for r in rows}):
+        m = re.search(r"k_tile\w*<(?:float|double)?", name)
+        if m:
+            d = con.execute("select end - start from kernels where name = ?", (name,)).fetchall()
+            tiles[m.group(0)][name] = [r[0] for r in d]
+    for pat in sorted(tiles):
+        for name, d in tiles[pat].items():
+            label = pat if len(tiles[pat]) == 1 else name.split("(")[0].replace("void ", "").replace("sw::", "")
+            full = [x for x in d if x >= 0.5 * max(d)]
+            lines.append(f"{label}: {len(d)} launches, mean over all {sum(d) / len(d) / 1e3:.1f} us, "
                          f"mean over {len(full)} full launches {sum(full) / len(full) / 1e3:.1f} us")
     # device busy fraction over the march: the union of every kernel's
     # interval within the span from the first to the last launch of the
     # operator pass (host decisions, synchronisations and launch gaps are
     # the idle rest)
-    for pat in ("k_tile_pipe<", "k_tile_lanes_pipe<", "k_tile_cg<", "k_tile_dir<", "k_tile_lanes_cg<", "k_tile<float"):
-        w = con.execute("select min(start), max(end) from kernels where name like ?", (f"%{pat}%",)).fetchone()
-        if not w or w[0] is None:
-            continue
-        t0, t1 = w
+    for pat in sorted(set(tiles) - ONCE_A_STEP):
+        t0, t1 = con.execute("select min(start), max(end) from kernels where name in (%s)" % ",".join("?" * len(tiles[pat])),
+                             list(tiles[pat])).fetchone()
         iv = con.execute("select start, end from kernels where end > ? and start < ? order by start",
                          (t0, t1)).fetchall()
         busy, cur_s, cur_e = 0, None, None
