@@ -2492,10 +2492,10 @@ void batch_cg_iteration(sw_batch* b, int i, bool dev_index, hipStream_t s, bool 
                         batch_grid_cap(b), s);
   if (prof) prof_end(cx, ev);
   ev = prof ? prof_begin(cx, SW_PROF_UPDATE_F32) : -1;
-  launch_lanes_cg(true, false, n, b->max_nodes, b->d_lanes, b->d_st, i, s, dev_index);
+  launch_lanes_cg(false, n, b->max_nodes, b->d_lanes, b->d_st, i, s, dev_index);
   if (prof) prof_end(cx, ev);
   ev = prof ? prof_begin(cx, SW_PROF_DIR_F32) : -1;
-  launch_lanes_cg(true, true, n, b->max_nodes, b->d_lanes, b->d_st, i, s, dev_index);
+  launch_lanes_cg(true, n, b->max_nodes, b->d_lanes, b->d_st, i, s, dev_index);
   if (prof) prof_end(cx, ev);
 }
 

@@ -110,7 +110,7 @@ struct TileArgs {
   T k2;
   const double* vin;   // 3 values or nullptr
   T* y;
-  int accumulate;      // interior nodes: 0 overwrite, 1 add
+  int accumulate;      // deterministic passes: 0 overwrite, 1 add
   int n_mat;           // materials in the table
   // passes from and to vectors in the user's node order (null otherwise): the
   // nodes' user ids and the output of the interior nodes, while the shared
@@ -204,17 +204,16 @@ enum LaneOp {
   LANE_TRUE_RES,     // r = b - q, rr_true; q = 0 when zero_q
   LANE_TO_F32,       // r32 = r / |r|, scale; ctl32 reset with tol; d32 = 0
   LANE_CG_INIT32,    // FP32 CG start on r32
-  LANE_CG_INIT64,    // FP64 CG start on r = b - q (q cleared)
   LANE_IR_UPDATE,    // x += scale d32
-  LANE_ZERO_Q,       // q = 0
   LANE_NEWMARK,      // Newmark update, increment ring
   LANE_RECORD,       // receivers, step log
   LANE_GATHER,       // LaneInfo of every lane
 };
 void launch_lanes(LaneOp op, int n_lanes, int64_t max_nodes, const LaneDev* lanes, const LaneState* st,
                   LaneInfo* info, hipStream_t s);
-void launch_lanes_cg(bool f32, bool dir, int n_lanes, int64_t max_nodes, const LaneDev* lanes, const LaneState* st,
-                     int iter, hipStream_t s, bool dev_index = false);
+// Update (dir false) or direction kernel of every lane's FP32 CG iteration.
+void launch_lanes_cg(bool dir, int n_lanes, int64_t max_nodes, const LaneDev* lanes, const LaneState* st, int iter,
+                     hipStream_t s, bool dev_index = false);
 
 // Launches (sw_kernels.hip).  iter >= 0: CG iteration `iter` of the solve in
 // ctl (early exit when done, p.Ap accumulated into ctl); iter < 0: plain.
@@ -231,14 +230,17 @@ void launch_tile_rhs(const MeshDev& m, const uint8_t* emat, const MatDev* mats, 
 // walking several tiles); 0: one per tile.
 void launch_tile_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
                      CgCtl* ctl, int iter, int grid_cap, hipStream_t s);
-// Two-kernel CG iterations: whether a solve's iterations run so, the operator
-// pass (a.x1 = z; forms and stores p = z + beta p_old, a.y = A p) and the
-// vector kernel after it (x += alpha p, r -= alpha q, z = P r).
+// One-kernel CG iterations: whether a solve's iterations run so, and the kernel
+// (updates the vectors v with the sums of the kernel before, applies A to the
+// preconditioned residual, a.y = A P r).
 bool one_kernel_cg(const MeshDev& m, int grid_cap, bool f32);
 void launch_tile_cg_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                         const OneCg<double>& v, const double* pinv, CgCtl* ctl, int iter, int max_iter, hipStream_t s);
 void launch_tile_cg_f32(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<float>& a,
                         const OneCg<float>& v, const __half* pinv, CgCtl* ctl, int iter, int max_iter, hipStream_t s);
+// Two-kernel CG iterations: whether a solve's iterations run so if not as one,
+// the operator pass (a.x1 = z; forms and stores p = z + beta p_old, a.y = A p)
+// and the vector kernel after it (x += alpha p, r -= alpha q, z = P r).
 bool two_kernel_cg(const MeshDev& m, int grid_cap, bool f32);
 void launch_tile_dir_f64(const MeshDev& m, const uint8_t* emat, const MatDev* mats, const TileArgs<double>& a,
                          const double* p_old, double* p, CgCtl* ctl, int iter, int max_iter, hipStream_t s);
@@ -268,8 +270,6 @@ void launch_invert_blocks(int64_t n_nodes, const double* diag6, double* pinv64, 
 // (a fixed-order reduction; fewer workgroups than the default grid).
 void launch_cg_init_f64(int64_t n_nodes, const double* b, const double* q, const double* pinv, double* r, double* z,
                         double* p, double* qz, CgCtl* ctl, hipStream_t s, bool det = false);
-void launch_cg_init_f32(int64_t n_nodes, const float* b, const float* q, const __half* pinv, float* r, float* z,
-                        float* p, float* qz, CgCtl* ctl, hipStream_t s);
 // update: r -= alpha q, z = P r, dot products; direction: x += alpha p,
 // then p = z + beta p unless the solve stops (each iteration launches the
 // update, then the direction kernel)

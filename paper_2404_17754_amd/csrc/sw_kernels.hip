@@ -4,9 +4,9 @@
 // update, receiver recording and the ERR misfit of Eq. (eqerr).
 //
 // Every vector is node-major [node][3] in the mesh's internal node order.
-// Partial dot products are reduced across the 64-wide wavefront with
-// shuffles, across the workgroup through LDS, and across the grid with one
-// FP64 atomic per workgroup into a device control block.
+// Partial dot products are reduced across the 64-wide wavefront with lane
+// moves in the vector registers, across the workgroup through LDS, and across
+// the grid with one FP64 atomic per workgroup into a device control block.
 #include <hip/hip_runtime.h>
 
 #include "sw_bf16.h"
@@ -122,8 +122,8 @@ template <typename T>
 __device__ __forceinline__ void cg_dir_body(int64_t n, int par, int iter_abs, int max_iter, const T* __restrict__ z,
                                             T* __restrict__ p, T* __restrict__ x, CgCtl* ctl) {
   if (!ctl->live) return;
-  // iter_abs < 0: the iteration index from the control block (graph replays
-  // launch the same arguments for every pair of iterations)
+  // iter_abs < 0: the iteration index from the control block (every replay of a
+  // graph launches the same arguments)
   if (iter_abs < 0) iter_abs = ctl->iter_cur;
   const double rr = slot_sum<NSLOT>(ctl->rr[par ^ 1]);
   const bool stop = !(rr > ctl->tol2) || (iter_abs + 1 >= max_iter);  // NaN stops too
@@ -324,10 +324,6 @@ void launch_cg_init_f64(int64_t n, const double* b, const double* q, const doubl
                         double* qz, CgCtl* ctl, hipStream_t s, bool det) {
   hipLaunchKernelGGL((k_cg_init<double, double>), dim3(det ? NSLOT : vgrid(n)), dim3(TPB), 0, s, n, b, q, P, r, z, p,
                      qz, ctl);
-}
-void launch_cg_init_f32(int64_t n, const float* b, const float* q, const __half* P, float* r, float* z, float* p,
-                        float* qz, CgCtl* ctl, hipStream_t s) {
-  hipLaunchKernelGGL((k_cg_init<float, __half>), dim3(vgrid(n)), dim3(TPB), 0, s, n, b, q, P, r, z, p, qz, ctl);
 }
 void launch_cg_update_f64(int64_t n, int par, const double* P, double* r, double* z, double* q, CgCtl* ctl,
                           hipStream_t s, bool det) {
@@ -919,13 +915,9 @@ __global__ __launch_bounds__(TPB) void k_lane_op(const LaneDev* __restrict__ lan
     }
   } else if constexpr (OP == LANE_CG_INIT32) {
     cg_init_body<float, __half>(nn, L.r32, nullptr, L.pinv16, L.r32, L.z32, L.p32, nullptr, L.ctl32);
-  } else if constexpr (OP == LANE_CG_INIT64) {
-    cg_init_body<double, double>(nn, L.b, L.q, L.pinv64, L.r, L.z, L.p, L.q, L.ctl64);
   } else if constexpr (OP == LANE_IR_UPDATE) {
     const double sc = L.ctl64->scale;
     for (int64_t i = i0; i < nd; i += stride) L.x[i] += sc * (double)L.d32[i];
-  } else if constexpr (OP == LANE_ZERO_Q) {
-    for (int64_t i = i0; i < nd; i += stride) L.q[i] = 0.0;
   } else if constexpr (OP == LANE_NEWMARK) {
     newmark_body(nd, L.dt, L.x, L.u, L.v, L.a, L.hist + (int64_t)((L.hist_head + 1) & 3) * nd);
   } else if constexpr (OP == LANE_RECORD) {
@@ -951,10 +943,10 @@ __global__ __launch_bounds__(TPB) void k_lane_op(const LaneDev* __restrict__ lan
 }
 
 // CG update (DIR false) or direction (DIR true) kernel of iteration `iter`
-// of every active lane's current solve (FP32 inner or FP64).
+// of every active lane's FP32 inner solve.
 // dev_index: the iteration's index in the step comes from each lane's
 // control block (graph replays), not from iter_base + iter.
-template <typename T, bool DIR>
+template <bool DIR>
 __global__ __launch_bounds__(TPB) void k_lane_cg(const LaneDev* __restrict__ lanes, const LaneState* __restrict__ st,
                                                  int iter, int dev_index) {
   const int l = blockIdx.y;
@@ -962,17 +954,10 @@ __global__ __launch_bounds__(TPB) void k_lane_cg(const LaneDev* __restrict__ lan
   const LaneDev L = lane_of(lanes, l);
   const int par = iter & 1;
   const int iabs = dev_index ? -1 : st[l].iter_base + iter;
-  if constexpr (sizeof(T) == 4) {
-    if constexpr (DIR)
-      cg_dir_body<float>(L.n_nodes, par, iabs, L.max_iter, L.z32, L.p32, L.d32, L.ctl32);
-    else
-      cg_update_body<float, __half>(L.n_nodes, L.n_interior, par, L.pinv16, L.r32, L.z32, L.q32, L.ctl32);
-  } else {
-    if constexpr (DIR)
-      cg_dir_body<double>(L.n_nodes, par, iabs, L.max_iter, L.z, L.p, L.x, L.ctl64);
-    else
-      cg_update_body<double, double>(L.n_nodes, 0, par, L.pinv64, L.r, L.z, L.q, L.ctl64);
-  }
+  if constexpr (DIR)
+    cg_dir_body<float>(L.n_nodes, par, iabs, L.max_iter, L.z32, L.p32, L.d32, L.ctl32);
+  else
+    cg_update_body<float, __half>(L.n_nodes, L.n_interior, par, L.pinv16, L.r32, L.z32, L.q32, L.ctl32);
 }
 
 // Blocks per lane: enough in total to fill the chip several times over,
@@ -1004,9 +989,7 @@ void launch_lanes(LaneOp op, int n_lanes, int64_t max_nodes, const LaneDev* lane
     SW_LANE_CASE(LANE_TRUE_RES, bs)
     SW_LANE_CASE(LANE_TO_F32, bd)
     SW_LANE_CASE(LANE_CG_INIT32, bn)
-    SW_LANE_CASE(LANE_CG_INIT64, bn)
     SW_LANE_CASE(LANE_IR_UPDATE, bd)
-    SW_LANE_CASE(LANE_ZERO_Q, bd)
     SW_LANE_CASE(LANE_NEWMARK, bd)
     SW_LANE_CASE(LANE_RECORD, 8)
     SW_LANE_CASE(LANE_GATHER, 1)
@@ -1014,22 +997,14 @@ void launch_lanes(LaneOp op, int n_lanes, int64_t max_nodes, const LaneDev* lane
   }
 }
 
-void launch_lanes_cg(bool f32, bool dir, int n_lanes, int64_t max_nodes, const LaneDev* lanes, const LaneState* st,
-                     int iter, hipStream_t s, bool dev_index) {
-  const unsigned bn = lane_blocks(n_lanes, max_nodes, 2048);
-  const dim3 g(bn, n_lanes);
+void launch_lanes_cg(bool dir, int n_lanes, int64_t max_nodes, const LaneDev* lanes, const LaneState* st, int iter,
+                     hipStream_t s, bool dev_index) {
+  const dim3 g(lane_blocks(n_lanes, max_nodes, 2048), n_lanes);
   const int dv = dev_index ? 1 : 0;
-  if (f32) {
-    if (dir)
-      hipLaunchKernelGGL((k_lane_cg<float, true>), g, dim3(TPB), 0, s, lanes, st, iter, dv);
-    else
-      hipLaunchKernelGGL((k_lane_cg<float, false>), g, dim3(TPB), 0, s, lanes, st, iter, dv);
-  } else {
-    if (dir)
-      hipLaunchKernelGGL((k_lane_cg<double, true>), g, dim3(TPB), 0, s, lanes, st, iter, dv);
-    else
-      hipLaunchKernelGGL((k_lane_cg<double, false>), g, dim3(TPB), 0, s, lanes, st, iter, dv);
-  }
+  if (dir)
+    hipLaunchKernelGGL(k_lane_cg<true>, g, dim3(TPB), 0, s, lanes, st, iter, dv);
+  else
+    hipLaunchKernelGGL(k_lane_cg<false>, g, dim3(TPB), 0, s, lanes, st, iter, dv);
 }
 
 }  // namespace sw

@@ -294,10 +294,9 @@ __device__ __forceinline__ double tile_scatter(const MeshDev& m, const TileArgs<
     if constexpr (USER) {
       const int j = k / 3;
       A.yu[3 * (int64_t)lds.gid[j] + (k - 3 * j)] = (T)v;
-    } else if (A.accumulate)
-      y[ib3 + k] += (T)v;
-    else
+    } else {
       y[ib3 + k] = (T)v;
+    }
   }
   // shared nodes: address-sorted global atomics
   for (int k = 3 * nint + threadIdx.x; k < 3 * nt; k += NT) {
