@@ -228,8 +228,8 @@ def batched_study(sw, cg, ctx, per_mesh, steps, proj_dim, legs=("seq", "batched"
             b = sw.Batch(ctx, lanes)
             choice, ms = b.autotune(reps=3)
             tuned.update({"choice": int(choice), "candidates_ms": [round(float(v), 4) for v in ms],
-                          "candidates": ["mesh after mesh, 3 workgroups/CU", "mesh after mesh, 2/CU",
-                                         "meshes interleaved tile by tile, 3/CU", "interleaved, 2/CU"]})
+                          "candidates": ["mesh after mesh, one workgroup per tile", "mesh after mesh, 2/CU",
+                                         "meshes interleaved tile by tile, one per tile", "interleaved, 2/CU"]})
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         if batched:
@@ -578,7 +578,7 @@ def main():
         gc.attach_mlp(net)
     # set-up-time choice of the FP32 pass's workgroups per CU (not timed)
     tune_choice, tune_ms = gc.autotune(reps=5)
-    case_tune = {"choice": ["3 workgroups/CU", "2/CU", "1/CU"][int(tune_choice)],
+    case_tune = {"choice": ["one workgroup per tile", "2/CU", "1/CU"][int(tune_choice)],
                  "candidates_ms": [round(float(v), 4) for v in tune_ms]}
     if args.calibrate_copy_mib > 0:
         src = torch.ones(args.calibrate_copy_mib << 18, dtype=torch.float32, device="cuda")
