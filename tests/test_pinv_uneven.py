@@ -70,3 +70,46 @@ def test_rows_of_zeros(lib):
     kept, t = _solve(lib.pinv, a, h, 1e-6)
     assert kept == 20 and not t[:5].any() and not t[25:].any()
     assert np.allclose(t[5:25], np.linalg.solve(g @ g.T, h[5:25]), rtol=1e-12, atol=0)
+
+
+def _exact(b, d, h):
+    """Solution of (d b d) x = d h in extended precision (Cholesky of b)."""
+    n = len(h)
+    l = np.zeros((n, n), np.longdouble)
+    b = b.astype(np.longdouble)
+    for j in range(n):
+        l[j, j] = np.sqrt(b[j, j] - l[j, :j] @ l[j, :j])
+        l[j + 1:, j] = (b[j + 1:, j] - l[j + 1:, :j] @ l[j, :j]) / l[j, j]
+    y = h.astype(np.longdouble)
+    for j in range(n):
+        y[j] = (y[j] - l[j, :j] @ y[:j]) / l[j, j]
+    for j in range(n - 1, -1, -1):
+        y[j] = (y[j] - l[j + 1:, j] @ y[j + 1:]) / l[j, j]
+    return y / d
+
+
+@pytest.mark.parametrize("order", ["falling", "rising"])
+def test_no_further_off_on_the_whole(lib, order):
+    """Rows that fall or rise by up to the ratio that still takes the fast way:
+    the geometric mean of the errors is no larger than the general path's."""
+    ratio = []
+    for n in (12, 20, 36, 64):
+        bits = int(np.floor(np.log2(n / 2) / 2))   # largest power of 4 up to n / 2
+        for seed in range(25):
+            rng = np.random.default_rng(1000 * n + seed)
+            g = rng.standard_normal((n, 4 * n))
+            b = g @ g.T
+            b = (b + b.T) / 2
+            b /= np.sqrt(np.outer(np.diag(b), np.diag(b)))
+            b = (b + b.T) / 2
+            np.fill_diagonal(b, 1.0)
+            k = np.arange(n) if order == "falling" else np.arange(n)[::-1]
+            d = 2.0 ** -np.round(bits * k / (n - 1))
+            h = rng.standard_normal(n)
+            a, r = np.ascontiguousarray(b * d[:, None] * d), np.ascontiguousarray(h * d)
+            want = _exact(b, d, h)
+            err = [float(np.linalg.norm(_solve(f, a, r, 1e-6)[1] - want)) for f in (lib.pinv, lib.tsolve)]
+            assert not np.array_equal(_solve(lib.pinv, a, r, 1e-6)[1], _solve(lib.tsolve, a, r, 1e-6)[1])
+            ratio.append(err[0] / err[1])
+    print(order, np.exp(np.mean(np.log(ratio))), max(ratio))
+    assert np.exp(np.mean(np.log(ratio))) <= 1.0
