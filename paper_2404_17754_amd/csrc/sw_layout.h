@@ -12,32 +12,31 @@ namespace sw {
 // (12 bytes in FP32, 24 in FP64) and a 4-byte node id.  At 1280 nodes an FP32
 // pass takes 51 KB, so three workgroups share a compute unit's 160 KB (the
 // FP32 kernel's registers allow three waves per SIMD), and an FP64 pass
-// 67 KB (two workgroups; its registers allow two waves per SIMD).  Measured
-// on the 9.6 M-tet mesh: FP32 pass 787 us at 1536 nodes, 655 us at 1280,
-// 670 us at 1152.
+// 67 KB (two workgroups; its registers allow two waves per SIMD).  FP32 pass
+// of 9.6 M tets: 328 us at 1280 nodes, 336 at 1152, 434 at 1024.
 constexpr int TILE_MAX_NODES = 1280;
 constexpr int TILE_MAX_ELEMS = 1024;
 // Default element cap: two per work-item of a 256-wide workgroup.  At the
 // 1280-node cap alone tiles of P2 tets close at about 570 elements, so the
 // work-items of a workgroup take two or three elements and the third round
 // runs mostly idle; closing tiles at 512 elements (about 1150 nodes) gives
-// every work-item two.  Measured on the 9.6 M-tet mesh, FP32 pass: 0.409 ms
-// at 512 elements against 0.424 ms at 1024 (node-limited).
+// every work-item two.  FP32 pass of 9.6 M tets: 328 us at 512 elements, 325
+// at 1024 (the node cap then makes the same 18750 tiles), 343 at 448, 377 at
+// 384.
 constexpr int TILE_DEFAULT_ELEMS = 512;
 // Smaller ones on meshes whose tiles would not fill the 256 compute units,
 // where a pass takes as long as one tile: about ten tiles of 64 elements or
 // more, up to 192 elements, then 96 tiles of up to 384, then up to 256 tiles.
 // In a batch of many cases the chip is full and the nodes shared by more tiles
 // cost time, so the sizes are those that serve both.  Four steps of one mixed
-// case / of a batch of 64 (24 000 tets and less: 128), ms:
+// case / of a batch of 128 (64 at 6912 and 15360 tets), ms:
 //   tets     elements 64         128         192         256         512
 //     1296       4.52/40.6   4.53/35.8   4.63/35.2               5.72/34.5
 //     3072       4.59/59.3   4.66/49.5   4.68/46.1   5.01/44.7   5.86/43.2
 //     6912   (72) 4.57/51.2  4.55/42.3   4.57/37.3   4.94/37.8   5.76/36.9
 //    15360  (160) 4.74/62.7              4.74/59.6   5.06/54.9   5.73/52.6
 //    24000                   4.79/174    4.91/148    5.21/137    5.94/121
-// (6912 and 15360: batches of 64).  98 000 tets, one step: 512 elements 1719 us,
-// 384 1606, 256 1741.
+// 98 000 tets, one step: 512 elements 1719 us, 384 1606, 256 1741.
 inline int default_tile_elems(int64_t n_tets) {
   if (n_tets > 256 * (int64_t)TILE_DEFAULT_ELEMS) return TILE_DEFAULT_ELEMS;
   const int64_t few = std::max<int64_t>(64, std::min<int64_t>(n_tets / 10, 192));

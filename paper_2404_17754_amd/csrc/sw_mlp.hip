@@ -103,9 +103,9 @@ __device__ __forceinline__ float mlp_eval16(const half4 xin, const MlpRegs& R) {
 // y[i] = net(X[i, 0..9]) for i < n (matrix-core path, as in the guess).  A
 // wavefront keeps the weights for all its passes (so few wavefronts: 20 KB of
 // weights each) and loads the next pass's inputs, in one load, before it
-// evaluates one.  The call on 1 M rows: 50 us (23 of it the call itself), 90
-// with four loads of one value per lane and 16384 wavefronts; 8 M rows 219 and
-// 359.
+// evaluates one.  The call on 1 M rows: 45-49 us (18 of it the call itself, as
+// on one row), 87-90 with four loads of one value per lane and 16384
+// wavefronts; 8 M rows 222 and 359.
 __global__ __launch_bounds__(TPB) void k_mlp_forward(int64_t n, const float* __restrict__ X,
                                                      const float* __restrict__ theta, float* __restrict__ y) {
   const int l = threadIdx.x & 63, q = l >> 4, r = l & 15;
@@ -288,10 +288,10 @@ void launch_mlp_collect(const MlpFeat& F, const double* du, int count, uint64_t 
 // samples 12 + 64 + 16 instructions forward, 64 back, 64 + 16 for the weight
 // gradients, 32 cycles each: 3.5 us; the rest is latency (the rows, weights
 // and accumulators of a workgroup that has one pass to make).
-// 8192 rows, with the Adam step: 406 us as one work-item per sample in scalar
-// loops, 21.3 so (33 with the weights fetched one load after the other and the
-// sums of a wavefront four to an LDS bank, 28.7 with an addition of the loss
-// per wavefront instead of one per workgroup).
+// One step of many, with Adam, 8192 rows: 406 us as one work-item per sample in
+// scalar loops, 21.4 so (17.6 at 100 rows; 33 with the weights fetched one load
+// after the other and the sums of a wavefront four to an LDS bank, 28.7 with an
+// addition of the loss per wavefront instead of one per workgroup).
 // FP32 sums run over at most GFLUSH * 16 = 128 samples, then in FP64.
 constexpr int GW = 4, GS = 16, GFLUSH = 8;
 constexpr int GLD = 17, GLD2 = 65, GLDX = 13;  // row strides that spread the LDS banks

@@ -500,13 +500,13 @@ struct XcdShare {
 // into ctl->pAp[0]; nothing when the solve is done; the first iteration ends
 // a solve whose residual meets the tolerance; the first workgroup clears the
 // scalar slots the next update kernel accumulates into).
-// FP32, 9.6 M tets: 326 us (1.2 GB moved: 3.7 TB/s).  The vector units issue
-// 65 % of the time, the LDS is busy 58 % (three quarters of that the FP64
-// atomics), so what is left is latency that three wavefronts per SIMD (LDS: 46
-// KB a tile) do not cover.  With the element data in single words and the
-// next tile's values loaded behind the elements of the one before it took
-// 347 us; that pipeline costs 40 registers, which now hold the next
-// element's data.  FP64: 867 us a pass with the values gathered one after the
+// FP32, 9.6 M tets: 326-335 us (1.16 GB moved: 3.5 TB/s).  Of the compute
+// units' busy cycles the vector units issue in 73 % and the LDS works in 65 %
+// (a third of that bank conflicts), and the waves wait half of theirs: latency
+// that three wavefronts per SIMD (LDS: 46 KB a tile) do not cover.  With the
+// element data in single words and the next tile's values loaded behind the
+// elements of the one before it took 347 us; that pipeline costs 40 registers,
+// which now hold the next element's data.  FP64: 867 us a pass with the values gathered one after the
 // other, 620 with every load issued before the first is waited for.
 // LOOP: a workgroup walks several tiles (a capped grid), else it has one.
 template <typename T, int NT, int IN, int TERMS, bool DET, bool LOOP>
